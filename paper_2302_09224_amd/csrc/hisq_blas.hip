@@ -415,12 +415,48 @@ __global__ void k_norm2_f64(const char *v, size_t n, double *partial) {
 // CG vector updates
 // ---------------------------------------------------------------------------
 
+// r -= alpha A p with alpha = rho / <p,Ap>, every block adding up the <p,Ap>
+// partials of the preceding Dslash itself (Sums): one launch instead of a
+// one-block kernel and this one.
 template <int SF, class R>
-__global__ void k_cg_axpy(char *r, const char *ap, const double *alpha, size_t n, double *partial, Guard gd,
-                          char *r_copy) {
-    __shared__ double lds[32];
+__global__ void __launch_bounds__(BLAS_BLOCK) k_cg_axpy(char *r, const char *ap, SolverCtrl *ctl, Sums pap, size_t n,
+                                                        double *partial, int jb, Guard gd, char *r_copy) {
+    __shared__ double lds[2 * (BLAS_BLOCK / 64)];
     if (!gd.pass()) return;
-    const R a = (R)(*alpha);
+    double pv[1];
+    all_sums<1>(pap.p, pap.n, pv, lds);
+    const double pi = pv[0], rho = ctl->rho;
+    const bool bad = !(pi > 0.0) || !__builtin_isfinite(pi);
+    const double alpha = rho / pi;
+    if (blockIdx.x == 0) {
+        const int t = threadIdx.x;
+        if (t < ctl->nshift) {
+            ctl->o_zeta[t] = ctl->zeta[t];
+            ctl->o_zeta_prev[t] = ctl->zeta_prev[t];
+        }
+        if (t == 0) {
+            ctl->pi = pi;
+            if (bad) {
+                ctl->stop = gd.j - 1;
+                ctl->reason = STOP_BREAKDOWN;
+                ctl->breakdown = 1;
+            } else {
+                ctl->alpha = alpha;
+                ctl->alpha_buf[jb] = alpha;
+                ctl->o_k = ctl->k;
+                ctl->o_rho = rho;
+                ctl->o_rmax2 = ctl->rmax2;
+                ctl->o_dev = ctl->dev;
+                ctl->o_rnorm_prev = ctl->rnorm_prev;
+                ctl->o_anorm = ctl->anorm;
+                ctl->o_active_mask = ctl->active_mask;
+                ctl->o_alpha_prev = ctl->alpha_prev;
+                ctl->o_beta_prev = ctl->beta_prev;
+            }
+        }
+    }
+    if (bad) return;
+    const R a = (R)alpha;
     double acc[2] = {0.0, 0.0};
     for (size_t s = gtid(); s < n; s += gstride()) {
         CVec<R> ro = SpinorIO<SF, R>::load(r, n, s);
@@ -446,12 +482,152 @@ __global__ void k_cg_axpy(char *r, const char *ap, const double *alpha, size_t n
     }
 }
 
+// beta and the decisions of one iteration (multi-shift: the zeta recurrences,
+// lane i for shift i), computed alike by every wave of the launch from the o_
+// copies; `writer` (one wave) records them.  Returns whether the block of
+// iterations goes on.
+__device__ __forceinline__ bool cg_scalars(SolverCtrl *c, double rn, double g, const double *pp, int j, int multishift,
+                                           int jb, bool writer, double &beta_out) {
+    const int lane = threadIdx.x & 63;
+    const int k = c->o_k + 1;
+    const double rho = c->o_rho;
+    if (!__builtin_isfinite(rn) || !__builtin_isfinite(g)) {
+        if (writer && lane == 0) {
+            c->k = k;
+            c->rho_new = rn;
+            c->gamma = g;
+            c->stop = j;
+            c->reason = STOP_BREAKDOWN;
+            c->breakdown = 1;
+        }
+        return false;
+    }
+    const double beta = c->pr ? (rn - g) / rho : rn / rho;
+    beta_out = beta;
+    int reason = STOP_NONE;
+    if (multishift) {
+        const double a = c->alpha, ap = c->o_alpha_prev, bp = c->o_beta_prev;
+        const int old = c->o_active_mask;
+        const int i = lane;
+        const bool up = i >= 1 && i < c->nshift && ((old >> (i & 31)) & 1);
+        bool out = false;
+        if (up) {
+            const double z = c->o_zeta[i], zp = c->o_zeta_prev[i], s = c->sh[i];
+            const double zn = z * zp * ap / (ap * zp * (1.0 + a * s) + a * bp * (zp - z));
+            const double ratio = zn / z;
+            out = zn * zn * rn <= fmax(c->tol2_i[i], c->floor2) * c->b2;
+            if (writer) {
+                c->alpha_i[i] = a * ratio;
+                c->ai_buf[jb][i] = a * ratio;
+                c->beta_i[i] = beta * ratio * ratio;
+                c->zb_buf[jb][i] = zn;
+                c->bb_buf[jb][i] = beta * ratio * ratio;
+                c->zeta_prev[i] = z;
+                c->zeta[i] = zn;
+                if (out) c->shift_stop_k[i] = k;
+            }
+        }
+        const int emask = (int)__ballot(up), rm = (int)__ballot(out), amask = old & ~rm;
+        if (writer && lane == 0) {
+            c->e_mask = emask;
+            c->rm_mask = rm;
+            c->eb_buf[jb] = emask;
+            c->rmb_buf[jb] = rm;
+            c->active_mask = amask;
+            c->alpha_prev = a;
+            c->beta_prev = beta;
+        }
+        if ((amask & ~1) == 0) reason = STOP_MSDONE;
+    }
+    const double rmax2 = fmax(c->o_rmax2, rn);
+    bool ru;
+    double dev = 0.0, rnorm = 0.0, anorm = 0.0;
+    if (c->ru_est) {
+        // Error estimate of the iterated residual (residual replacement in the manner of
+        // van der Vorst and Ye): each sloppy update r -= alpha A p makes an error of about
+        // eps_s (|r| + |alpha| |A| |p|); the errors of successive iterations are independent,
+        // so they are accumulated in quadrature.  A reliable update is due when the estimate
+        // crosses sqrt(eps_s) |r| from below and has grown past 1.1x its value after the
+        // previous update.
+        const double p2 = *pp;   // |p_k|^2 from the update that produced p_k
+        rnorm = sqrt(rn);
+        anorm = p2 > 0.0 ? fmax(c->o_anorm, c->pi / p2) : c->o_anorm;
+        const double e = c->eps_s * (rnorm + fabs(c->alpha) * anorm * sqrt(p2));
+        dev = sqrt(c->o_dev * c->o_dev + e * e);
+        const double th = sqrt(c->eps_s);
+        ru = c->o_dev <= th * c->o_rnorm_prev && dev > th * rnorm && dev > 1.1 * c->dev_init;
+    } else {
+        ru = c->delta2 > 0.0 && rn < c->delta2 * rmax2;
+    }
+    if (reason == STOP_NONE) {
+        if (ru)
+            reason = STOP_RU;
+        else if (!multishift && rn <= c->tol2 * c->b2)
+            reason = STOP_CONV;
+    }
+    if (reason == STOP_NONE && k >= c->maxiter) reason = STOP_MAXITER;
+    if (writer && lane == 0) {
+        c->k = k;
+        c->rho_new = rn;
+        c->gamma = g;
+        c->beta = beta;
+        c->rmax2 = rmax2;
+        if (c->ru_est) {
+            c->anorm = anorm;
+            c->dev = dev;
+            c->rnorm_prev = rnorm;
+        }
+        c->rho_prev = rho;
+        c->rho = rn;
+        if (reason != STOP_NONE) {
+            c->reason = reason;
+            c->stop = j;
+        }
+    }
+    return reason == STOP_NONE;
+}
+
+// per-block |p|^2 of a gradient update, blas_blocks(n) entries whatever the grid
+__device__ __forceinline__ void store_ppart(double *ppart, size_t n, double (&acc)[1], double *lds) {
+    block_sum<1>(acc, lds);
+    if (threadIdx.x) return;
+    const size_t nb = (n + BLAS_BLOCK - 1) / BLAS_BLOCK;
+    const int np = nb > BLAS_MAX_BLOCKS ? BLAS_MAX_BLOCKS : (int)nb;
+    for (int b = blockIdx.x; b < np; b += gridDim.x) ppart[b] = b == (int)blockIdx.x ? acc[0] : 0.0;
+}
+
+// p_dst = pa r + pb p_src after a reliable update (pa complex: the
+// re-projection), every block forming the scalars from the partials of
+// k_ru_convert itself.
+// mode 0: reliable update inside CG (Polak-Ribiere against the previous iterated residual)
+// mode 1: fresh start (p = r)
+// mode 2: continuation of a gradient vector from another solve (Fletcher-Reeves against rho_prev)
 template <int SF, class R>
-__global__ void k_cg_pupdate(char *pd, const char *r, const char *ps, const SolverCtrl *ctrl, size_t n, double *ppart,
-                             Guard gd) {
-    __shared__ double lds[8];
+__global__ void __launch_bounds__(BLAS_BLOCK) k_ru_pupdate(char *pd, const char *r, const char *ps, SolverCtrl *ctl,
+                                                           Sums ru, int mode, size_t n, double *ppart, Guard gd) {
+    __shared__ double lds[4 * (BLAS_BLOCK / 64)];
     if (!gd.pass()) return;
-    const R ar = (R)ctrl->pa_re, ai = (R)ctrl->pa_im, b = (R)ctrl->pb;
+    double v[4];
+    all_sums<4>(ru.p, ru.n, v, lds);
+    const double rho = v[0], rho_prev = ctl->rho_prev;
+    double beta = 0.0, cr = 0.0, ci = 0.0;
+    if (mode != 1) {
+        if (ctl->reproject && rho > 0.0) {
+            cr = v[1] / rho;  // <r,p>/<r,r>: p <- p - (<r,p>/<r,r>) r
+            ci = v[2] / rho;
+        }
+        beta = (mode == 0 && ctl->pr) ? (rho - v[3]) / rho_prev : rho / rho_prev;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        ctl->beta = beta;
+        ctl->rho = rho;
+        ctl->rmax2 = rho;
+        ctl->dev = ctl->dev_init = ctl->eps_s * sqrt(rho);   // rounding of the freshly stored residual
+        ctl->rnorm_prev = sqrt(rho);
+        ctl->reason = STOP_NONE;
+        ctl->stop = STOP_NEVER;
+    }
+    const R ar = (R)(1.0 - beta * cr), ai = (R)(-beta * ci), b = (R)beta;
     double acc[1] = {0.0};
     for (size_t s = gtid(); s < n; s += gstride()) {
         CVec<R> rv = SpinorIO<SF, R>::load(r, n, s);
@@ -468,10 +644,7 @@ __global__ void k_cg_pupdate(char *pd, const char *r, const char *ps, const Solv
             for (int c = 0; c < 3; c++) acc[0] += (double)st.re[c] * st.re[c] + (double)st.im[c] * st.im[c];
         }
     }
-    if (ppart) {
-        block_sum<1>(acc, lds);
-        if (threadIdx.x == 0) ppart[blockIdx.x] = acc[0];
-    }
+    if (ppart) store_ppart(ppart, n, acc, lds);
 }
 
 // Buffered-vector loops load a group of vectors before using the first, so that
@@ -509,6 +682,66 @@ __global__ void k_flush_x(char *x64, SpinorList p, int count, const double *alph
         }
         SpinorIO<SF_F64, double>::store(x64, n, s, x);
     }
+}
+
+// The iteration's scalars and decisions (cg_scalars, in every block), then
+// p_dst = r + beta p_src.  FLUSH (the last slot of the ring): the buffered
+// solution update of the whole ring in the same pass, which has p_src in
+// registers as the ring's last vector.
+template <int SF, class R, bool FLUSH>
+__global__ void __launch_bounds__(BLAS_BLOCK) k_cg_pupdate(char *pd, const char *r, const char *ps, SolverCtrl *ctl,
+                                                           Sums rr, const double *pp, size_t n, double *ppart,
+                                                           char *x64, SpinorList ring, int count, int multishift,
+                                                           int jb, Guard gd) {
+    __shared__ double lds[2 * (BLAS_BLOCK / 64)];
+    if (!gd.pass()) return;
+    double v[2], beta = 0.0;
+    all_sums<2>(rr.p, rr.n, v, lds);
+    if (!cg_scalars(ctl, v[0], v[1], pp, gd.j, multishift, jb, blockIdx.x == 0 && threadIdx.x < 64, beta)) return;
+    const R b = (R)beta;
+    double acc[1] = {0.0};
+    for (size_t s = gtid(); s < n; s += gstride()) {
+        const CVec<R> rv = SpinorIO<SF, R>::load(r, n, s);
+        CVec<R> pv;
+        if constexpr (FLUSH) {
+            constexpr int LOAD_GROUP = load_group<SF>();
+            CVec<double> x = SpinorIO<SF_F64, double>::load(x64, n, s);
+            for (int i0 = 0; i0 < count; i0 += LOAD_GROUP) {
+                CVec<R> gv[LOAD_GROUP];
+                double a[LOAD_GROUP];
+#pragma unroll
+                for (int k = 0; k < LOAD_GROUP; k++) {
+                    const int i = min(i0 + k, count - 1);
+                    gv[k] = SpinorIO<SF, R>::load(ring.p[i], n, s);
+                    a[k] = i0 + k < count ? ctl->alpha_buf[i] : 0.0;
+                }
+#pragma unroll
+                for (int k = 0; k < LOAD_GROUP; k++) {
+#pragma unroll
+                    for (int c = 0; c < 3; c++) {
+                        x.re[c] = fma(a[k], (double)gv[k].re[c], x.re[c]);
+                        x.im[c] = fma(a[k], (double)gv[k].im[c], x.im[c]);
+                    }
+                }
+                pv = gv[LOAD_GROUP - 1];   // of the last group: the ring's last vector
+            }
+            SpinorIO<SF_F64, double>::store(x64, n, s, x);
+        } else {
+            pv = SpinorIO<SF, R>::load(ps, n, s);
+        }
+        CVec<R> o;
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            o.re[c] = fma(R(1), rv.re[c], b * pv.re[c]);
+            o.im[c] = fma(R(1), rv.im[c], b * pv.im[c]);
+        }
+        const CVec<R> st = SpinorIO<SF, R>::store(pd, n, s, o);
+        if (ppart) {
+#pragma unroll
+            for (int c = 0; c < 3; c++) acc[0] += (double)st.re[c] * st.re[c] + (double)st.im[c] * st.im[c];
+        }
+    }
+    if (ppart) store_ppart(ppart, n, acc, lds);
 }
 
 template <int SF, class R>
@@ -564,7 +797,7 @@ __global__ void k_ru_convert(char *rs, const char *r64, const char *p, const cha
 // same iteration, and the shifted solutions x_i += alpha_i p_i; the solutions
 // are updated once per block (buffered, Sec. 3.1 item 1).  So a shift's
 // gradient vector is stored only at the block's start: the block's base
-// residuals r_{k+1} are kept in a ring (rr.p[q], q < count), the finalize
+// residuals r_{k+1} are kept in a ring (rr.p[q], q < count), the gradient
 // kernel records the shifts' scalars of every iteration (slot q), and this
 // kernel replays the block's updates in registers, loading each residual once
 // per group of G shifts.  A shift that stops in slot q takes its x update of
@@ -923,16 +1156,26 @@ hipError_t launch_norm2_f64(const char *v, size_t n, double *partial, int *nbloc
     return hipGetLastError();
 }
 
-hipError_t launch_cg_axpy(char *r, const char *ap, const double *alpha, size_t n, int sf, int compute, double *partial,
-                          Guard gd, hipStream_t st, char *r_copy) {
-    HISQ_DISPATCH_SC(sf, compute, hipLaunchKernelGGL((k_cg_axpy<SFc, Rc>), dim3(blas_blocks(n)), dim3(BLAS_BLOCK), 0, st, r, ap, alpha, n, partial, gd, r_copy));
+hipError_t launch_cg_axpy(char *r, const char *ap, SolverCtrl *c, const Sums &pap, size_t n, int sf, int compute,
+                          double *partial, int jb, Guard gd, hipStream_t st, char *r_copy) {
+    HISQ_DISPATCH_SC(sf, compute, hipLaunchKernelGGL((k_cg_axpy<SFc, Rc>), dim3(blas_blocks(n)), dim3(BLAS_BLOCK), 0, st, r, ap, c, pap, n, partial, jb, gd, r_copy));
     return hipGetLastError();
 }
 
-hipError_t launch_cg_pupdate(char *p_dst, const char *r, const char *p_src, const SolverCtrl *ctrl, double *ppart,
-                             size_t n, int sf,
-                             int compute, Guard gd, hipStream_t st) {
-    HISQ_DISPATCH_SC(sf, compute, hipLaunchKernelGGL((k_cg_pupdate<SFc, Rc>), dim3(blas_blocks(n)), dim3(BLAS_BLOCK), 0, st, p_dst, r, p_src, ctrl, n, ppart, gd));
+hipError_t launch_cg_pupdate(char *p_dst, const char *r, const char *p_src, SolverCtrl *c, const Sums &rr,
+                             const double *pp, double *ppart, char *x64, const SpinorList &ring, int count,
+                             int multishift, int jb, size_t n, int sf, int compute, Guard gd, hipStream_t st) {
+    const int nb = cg_pupdate_grid(n, sf, compute, count > 0);
+    if (count > 0)
+        HISQ_DISPATCH_SC(sf, compute, hipLaunchKernelGGL((k_cg_pupdate<SFc, Rc, true>), dim3(nb), dim3(BLAS_BLOCK), 0, st, p_dst, r, p_src, c, rr, pp, n, ppart, x64, ring, count, multishift, jb, gd));
+    else
+        HISQ_DISPATCH_SC(sf, compute, hipLaunchKernelGGL((k_cg_pupdate<SFc, Rc, false>), dim3(nb), dim3(BLAS_BLOCK), 0, st, p_dst, r, p_src, c, rr, pp, n, ppart, x64, ring, 0, multishift, jb, gd));
+    return hipGetLastError();
+}
+
+hipError_t launch_ru_pupdate(char *p_dst, const char *r, const char *p_src, SolverCtrl *c, const Sums &ru, int mode,
+                             double *ppart, size_t n, int sf, int compute, Guard gd, hipStream_t st) {
+    HISQ_DISPATCH_SC(sf, compute, hipLaunchKernelGGL((k_ru_pupdate<SFc, Rc>), dim3(blas_blocks(n)), dim3(BLAS_BLOCK), 0, st, p_dst, r, p_src, c, ru, mode, n, ppart, gd));
     return hipGetLastError();
 }
 
@@ -977,11 +1220,23 @@ hipError_t shift_replay_kernel(int sf, int compute, const void **fn) {
     HISQ_DISPATCH_SC(sf, compute, *fn = reinterpret_cast<const void *>(&k_shift_replay<SFc, Rc, REPLAY_GROUP>));
     return hipSuccess;
 }
+hipError_t cg_pupdate_kernel(int sf, int compute, const void **fn) {
+    HISQ_DISPATCH_SC(sf, compute, *fn = reinterpret_cast<const void *>(&k_cg_pupdate<SFc, Rc, true>));
+    return hipSuccess;
+}
 hipError_t flush_x_kernel(int sf, int compute, const void **fn) {
     HISQ_DISPATCH_SC(sf, compute, *fn = reinterpret_cast<const void *>(&k_flush_x<SFc, Rc>));
     return hipSuccess;
 }
 }  // namespace
+
+// the gradient update with the ring's solution update is capped at the resident
+// blocks like the other buffered-vector kernels
+int cg_pupdate_grid(size_t n, int sf, int compute, bool flush) {
+    if (!flush) return blas_blocks(n);
+    const void *fn = nullptr;
+    return resident_grid(cg_pupdate_kernel(sf, compute, &fn) == hipSuccess ? fn : nullptr, n);
+}
 
 int shift_replay_grid(size_t n, int sf, int compute) {
     const void *fn = nullptr;

@@ -529,6 +529,53 @@ template <int NV> __device__ __forceinline__ void block_sum(double (&v)[NV], dou
     }
 }
 
+// Sums over the block partials partial[b * NV + k], b < n, delivered to every
+// thread of the block (n == 1: the sums are already formed).  Every block adds
+// in the same order (strided shares four loads at a time, in index order, then
+// lanes, then waves), so all blocks of a launch get the same bits.  lds: NV
+// doubles per wave.
+template <int NV> __device__ __forceinline__ void all_sums(const double *partial, int n, double (&v)[NV], double *lds) {
+    if (n == 1) {
+#pragma unroll
+        for (int k = 0; k < NV; k++) v[k] = partial[k];
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < NV; k++) v[k] = 0.0;
+    const int step = blockDim.x;
+    int b = threadIdx.x;
+    for (; b + 3 * step < n; b += 4 * step) {
+        double q[4][NV];
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+#pragma unroll
+            for (int k = 0; k < NV; k++) q[u][k] = partial[(size_t)(b + u * step) * NV + k];
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+#pragma unroll
+            for (int k = 0; k < NV; k++) v[k] += q[u][k];
+    }
+    for (; b < n; b += step) {
+#pragma unroll
+        for (int k = 0; k < NV; k++) v[k] += partial[(size_t)b * NV + k];
+    }
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+#pragma unroll
+    for (int k = 0; k < NV; k++) v[k] = wave_sum(v[k]);
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < NV; k++) lds[w * NV + k] = v[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NV; k++) {
+        double t = 0.0;
+        for (int j = 0; j < nw; j++) t += lds[j * NV + k];
+        v[k] = t;
+    }
+    __syncthreads();
+}
+
 // Solver iteration guard: a kernel that belongs to iteration j of a block of
 // iterations runs iff j < *stop (strict) or j <= *stop; the solver's scalar
 // kernels lower *stop to end a block early (reliable update, convergence).

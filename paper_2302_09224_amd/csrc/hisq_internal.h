@@ -226,6 +226,14 @@ struct SolverCtrl {
     int eb_buf[HISQ_MAX_GRAD_BUFFER];   // shifts updated in each iteration of the block
     int rmb_buf[HISQ_MAX_GRAD_BUFFER];  // shifts that stopped in each iteration of the block
     int rm_mask;     // multi-shift: shifts that stopped in this iteration
+    // The recurrence state as the iteration's residual update found it.  Every
+    // block of the gradient update derives the iteration's scalars from these
+    // copies while its first block writes the new values above, so no block
+    // reads what another one writes in the same launch.
+    int o_k, o_active_mask;
+    double o_rho, o_rmax2, o_dev, o_rnorm_prev, o_anorm, o_alpha_prev, o_beta_prev;
+    double o_zeta[HISQ_MAX_SHIFTS], o_zeta_prev[HISQ_MAX_SHIFTS];
+    double red[8];   // sums of block partials too many for every consumer block to add up (SUMS_* offsets)
     int shift_stop_k[HISQ_MAX_SHIFTS];
     // batched CG: per right-hand side scalars
     double brho[16], brho_prev[16], brho_new[16], bgamma[16], bpi[16], balpha[16], bbeta[16];
@@ -247,14 +255,35 @@ struct SpinorList {
     char *p[HISQ_MAX_SHIFTS];
 };
 
-// r = r - alpha*ap; partial (|r'|^2, Re<r', r>); r_copy (optional): the new r
-// stored a second time there (the multi-shift ring of base residuals)
-hipError_t launch_cg_axpy(char *r, const char *ap, const double *alpha, size_t n, int sf, int compute,
-                          double *partial, Guard gd, hipStream_t st, char *r_copy = nullptr);
-// p_dst = pa*r + pb*p_src, (pa, pb) from the control block
-// (ppart: optional per-block |p_dst|^2 of the stored values)
-hipError_t launch_cg_pupdate(char *p_dst, const char *r, const char *p_src, const SolverCtrl *ctrl, double *ppart,
-                             size_t n, int sf, int compute, Guard gd, hipStream_t st);
+// Block partials of NV sums each that the next kernel's blocks add up
+// themselves, or (sums in SolverCtrl::red, n == 1) that k_fin_sum added up.
+// The line between the two: every block of the consumer reads n * NV doubles,
+// so with g blocks the launch reads g n NV * 8 bytes from L2 on top of its own
+// traffic, against a one-block launch of its own (4-5 us with its gap).
+struct Sums {
+    const double *p;
+    int n;
+};
+constexpr int SUMS_DIRECT = 2048;      // n * NV up to which the consumer adds the partials up
+enum { SUMS_PAP = 0, SUMS_RR = 1, SUMS_PP = 3, SUMS_RU = 4 };   // places in SolverCtrl::red
+// r = r - alpha*ap with alpha = rho / sum(pap); partial (|r'|^2, Re<r', r>);
+// r_copy (optional): the new r stored a second time there (the multi-shift ring
+// of base residuals).  A breakdown (<p,Ap> <= 0) stops the block.
+hipError_t launch_cg_axpy(char *r, const char *ap, SolverCtrl *c, const Sums &pap, size_t n, int sf, int compute,
+                          double *partial, int jb, Guard gd, hipStream_t st, char *r_copy);
+// The scalars and decisions of one iteration from rr = (|r'|^2, Re<r',r>), then
+// (unless the block stops here) p_dst = r + beta p_src; with count > 0 also
+// x64 += sum_i alpha_buf[i] ring.p[i], i < count (p_src is ring.p[count - 1]).
+// ppart (optional): |p_dst|^2 of the stored values per block, blas_blocks(n)
+// entries; pp: the same of p_src when the error-estimate trigger runs.
+hipError_t launch_cg_pupdate(char *p_dst, const char *r, const char *p_src, SolverCtrl *c, const Sums &rr,
+                             const double *pp, double *ppart, char *x64, const SpinorList &ring, int count,
+                             int multishift, int jb, size_t n, int sf, int compute, Guard gd, hipStream_t st);
+// after r = pack(b - A x): new rho, re-projection and beta from the sums of
+// launch_ru_convert (mode as in k_ru_pupdate), and p_dst from them
+hipError_t launch_ru_pupdate(char *p_dst, const char *r, const char *p_src, SolverCtrl *c, const Sums &ru, int mode,
+                             double *ppart, size_t n, int sf, int compute, Guard gd, hipStream_t st);
+int cg_pupdate_grid(size_t n, int sf, int compute, bool flush);
 // x64 += sum_i alpha_buf[i] p_i, i < count
 hipError_t launch_flush_x(char *x64, const SpinorList &p, int count, const double *alpha_buf, size_t n,
                           int sf, int compute, Guard gd, hipStream_t st);

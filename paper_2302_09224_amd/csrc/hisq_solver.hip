@@ -1,25 +1,28 @@
 // hisq_solver.hip -- stabilised mixed-precision CG and multi-shift CG (Sec. 3).
 //
 // Design (MI355X): every scalar of the recurrences lives on the device in a
-// SolverCtrl block and is produced by one-block "finalize" kernels that sum
-// the per-block partials of the preceding fused kernel in a fixed order.  No
+// SolverCtrl block and is formed by the vector kernel that needs it first, from
+// the per-block partials of the preceding kernel summed in a fixed order.  No
 // iteration needs the host: the host enqueues blocks of `chunk` iterations
 // (optionally as one captured hipGraph replayed per block) and polls the
-// control block once per block.  A finalize kernel that decides to leave the
+// control block once per block.  A kernel that decides to leave the
 // loop (reliable update due, convergence candidate, multi-shift phase done,
 // breakdown, iteration cap) lowers ctrl->stop, and every later kernel of the
 // block sees its guard fail and returns at once.  The host then performs the
 // reliable update (FP64 Dslash on the FP64 solution) and starts a new block.
 //
-// One CG iteration j of a block (slot jb = j mod N_b of the gradient buffer):
+// One CG iteration j of a block (slot jb = j mod N_b of the gradient buffer), four launches:
 //   t     = D_oe p[jb]                                       (sloppy Dslash)
 //   Ap    = c p[jb] - D_eo t,  partial Re<p,Ap>              (sloppy Dslash, fused xpay + dot)
-//   alpha = rho / <p,Ap>                                     (finalize)
-//   r    -= alpha Ap,  partial |r'|^2, Re<r',r>              (fused axpy + two dots)
-//   beta  = (|r'|^2 - Re<r',r>) / |r|^2  (Polak-Ribiere, Sec. 3.1 item 3), RU / stop decisions
-//   [multi-shift: x_i += alpha_i p_i, p_i = zeta_i r' + beta_i p_i for all shifts, one launch]
-//   [x64 += sum_j alpha_j p_j every N_b iterations: buffered FP64 solution update, Sec. 3.1 item 1]
-//   p[jb+1] = r' + beta p[jb]
+//   alpha = rho / <p,Ap>;  r -= alpha Ap,  partial |r'|^2, Re<r',r>
+//   beta  = (|r'|^2 - Re<r',r>) / |r|^2  (Polak-Ribiere, Sec. 3.1 item 3), RU / stop decisions;
+//           p[jb+1] = r' + beta p[jb]; at the last slot x64 += sum_j alpha_j p_j in the same
+//           pass (buffered FP64 solution update, Sec. 3.1 item 1)
+//   [multi-shift, at the last slot: x_i += alpha_i p_i, p_i = zeta_i r' + beta_i p_i replayed
+//    for all shifts, one launch]
+// Every block of the two vector kernels adds up the partials of the preceding
+// kernel and forms the scalars itself; its first block records them.  On large
+// lattices a one-block launch adds the partials up first (SUMS_DIRECT).
 // Reliable update (Sec. 3 and its footnote, delta = 0.1): flush the buffered
 // gradients into x64, r64 = b - A x64 with the FP64 operator, r = pack(r64),
 // re-project p against the new r (Sec. 3.1 item 2), then continue.
@@ -77,118 +80,15 @@ __global__ void k_fin_b2(SolverCtrl *c, const double *partial, int n) {
     if (threadIdx.x == 0) c->b2 = v[0];
 }
 
-// alpha = rho / <p, A p>
-__global__ void k_fin_alpha(SolverCtrl *c, const double *partial, int n, int jb, Guard gd) {
-    __shared__ double lds[FIN_THREADS / 64];
+// sums of block partials too many for every block of the consumer to add up
+template <int NV> __global__ void k_fin_sum(const double *partial, int n, double *out, Guard gd) {
+    __shared__ double lds[NV * (FIN_THREADS / 64)];
     if (!gd.pass()) return;
-    double v[1];
-    fin_sums<1>(partial, n, v, lds);
+    double v[NV];
+    fin_sums<NV>(partial, n, v, lds);
     if (threadIdx.x) return;
-    const double pi = v[0];
-    c->pi = pi;
-    if (!(pi > 0.0) || !__builtin_isfinite(pi)) {
-        c->stop = gd.j - 1;
-        c->reason = STOP_BREAKDOWN;
-        c->breakdown = 1;
-        return;
-    }
-    const double a = c->rho / pi;
-    c->alpha = a;
-    c->alpha_buf[jb] = a;
-}
-
-// beta and the decisions of one iteration; multi-shift: zeta recurrences
-__global__ void k_fin_beta(SolverCtrl *c, const double *partial, int n, Guard gd, int multishift, int jb,
-                           const double *ppart, int npp) {
-    __shared__ double lds[2 * (FIN_THREADS / 64)], lds2[FIN_THREADS / 64];
-    if (!gd.pass()) return;
-    double v[2];
-    fin_sums<2>(partial, n, v, lds);
-    double pv[1] = {0.0};   // |p_k|^2 from the update that produced p_k
-    if (c->ru_est) fin_sums<1>(ppart, npp, pv, lds2);
-    if (threadIdx.x) return;
-    const double rn = v[0], g = v[1];
-    const int k = c->k + 1;
-    c->k = k;
-    c->rho_new = rn;
-    c->gamma = g;
-    if (!__builtin_isfinite(rn) || !__builtin_isfinite(g)) {
-        c->stop = gd.j;
-        c->reason = STOP_BREAKDOWN;
-        c->breakdown = 1;
-        return;
-    }
-    const double rho = c->rho;
-    const double beta = c->pr ? (rn - g) / rho : rn / rho;
-    c->beta = beta;
-    c->pa_re = 1.0;
-    c->pa_im = 0.0;
-    c->pb = beta;
-    int reason = STOP_NONE;
-    if (multishift) {
-        const double a = c->alpha, ap = c->alpha_prev, bp = c->beta_prev;
-        int amask = c->active_mask, emask = 0, rm = 0;
-        for (int i = 1; i < c->nshift; i++) {
-            if (!((amask >> i) & 1)) continue;
-            const double z = c->zeta[i], zp = c->zeta_prev[i], s = c->sh[i];
-            const double zn = z * zp * ap / (ap * zp * (1.0 + a * s) + a * bp * (zp - z));
-            const double ratio = zn / z;
-            c->alpha_i[i] = a * ratio;
-            c->ai_buf[jb][i] = a * ratio;
-            c->beta_i[i] = beta * ratio * ratio;
-            c->zb_buf[jb][i] = zn;
-            c->bb_buf[jb][i] = beta * ratio * ratio;
-            c->zeta_prev[i] = z;
-            c->zeta[i] = zn;
-            emask |= 1 << i;
-            if (zn * zn * rn <= fmax(c->tol2_i[i], c->floor2) * c->b2) {
-                amask &= ~(1 << i);
-                rm |= 1 << i;
-                c->shift_stop_k[i] = k;
-            }
-        }
-        c->e_mask = emask;
-        c->rm_mask = rm;
-        c->eb_buf[jb] = emask;
-        c->rmb_buf[jb] = rm;
-        c->active_mask = amask;
-        c->alpha_prev = a;
-        c->beta_prev = beta;
-        if ((amask & ~1) == 0) reason = STOP_MSDONE;
-    }
-    c->rmax2 = fmax(c->rmax2, rn);
-    bool ru;
-    if (c->ru_est) {
-        // Error estimate of the iterated residual (residual replacement in the manner of
-        // van der Vorst and Ye): each sloppy update r -= alpha A p makes an error of about
-        // eps_s (|r| + |alpha| |A| |p|); the errors of successive iterations are independent,
-        // so they are accumulated in quadrature.  A reliable update is due when the estimate
-        // crosses sqrt(eps_s) |r| from below and has grown past 1.1x its value after the
-        // previous update.
-        const double rnorm = sqrt(rn);
-        if (pv[0] > 0.0) c->anorm = fmax(c->anorm, c->pi / pv[0]);
-        const double e = c->eps_s * (rnorm + fabs(c->alpha) * c->anorm * sqrt(pv[0]));
-        const double dnew = sqrt(c->dev * c->dev + e * e);
-        const double th = sqrt(c->eps_s);
-        ru = c->dev <= th * c->rnorm_prev && dnew > th * rnorm && dnew > 1.1 * c->dev_init;
-        c->dev = dnew;
-        c->rnorm_prev = rnorm;
-    } else {
-        ru = c->delta2 > 0.0 && rn < c->delta2 * c->rmax2;
-    }
-    if (reason == STOP_NONE) {
-        if (ru)
-            reason = STOP_RU;
-        else if (!multishift && rn <= c->tol2 * c->b2)
-            reason = STOP_CONV;
-    }
-    if (reason == STOP_NONE && k >= c->maxiter) reason = STOP_MAXITER;
-    c->rho_prev = rho;
-    c->rho = rn;
-    if (reason != STOP_NONE) {
-        c->reason = reason;
-        c->stop = gd.j;
-    }
+#pragma unroll
+    for (int k = 0; k < NV; k++) out[k] = v[k];
 }
 
 // |b - A x|^2 from the FP64 operator; done when below tol^2 |b|^2
@@ -208,37 +108,6 @@ __global__ void k_fin_ru_check(SolverCtrl *c, const double *partial, int n) {
     const int done = r2 <= c->tol2 * c->b2;
     c->done = done;
     c->stop = done ? -1 : STOP_NEVER;
-}
-
-// after r = pack(b - A x): new rho, re-projection and beta of the next p update.
-// mode 0: reliable update inside CG (Polak-Ribiere against the previous iterated residual)
-// mode 1: fresh start (p = r)
-// mode 2: continuation of a gradient vector from another solve (Fletcher-Reeves against rho_prev)
-__global__ void k_fin_ru_finish(SolverCtrl *c, const double *partial, int n, int mode, Guard gd) {
-    __shared__ double lds[4 * (FIN_THREADS / 64)];
-    if (!gd.pass()) return;
-    double v[4];
-    fin_sums<4>(partial, n, v, lds);
-    if (threadIdx.x) return;
-    const double rho = v[0];
-    double beta = 0.0, cr = 0.0, ci = 0.0;
-    if (mode != 1) {
-        if (c->reproject && rho > 0.0) {
-            cr = v[1] / rho;  // <r,p>/<r,r>: p <- p - (<r,p>/<r,r>) r
-            ci = v[2] / rho;
-        }
-        beta = (mode == 0 && c->pr) ? (rho - v[3]) / c->rho_prev : rho / c->rho_prev;
-    }
-    c->pa_re = 1.0 - beta * cr;
-    c->pa_im = -beta * ci;
-    c->pb = beta;
-    c->beta = beta;
-    c->rho = rho;
-    c->rmax2 = rho;
-    c->dev = c->dev_init = c->eps_s * sqrt(rho);   // rounding of the freshly stored residual
-    c->rnorm_prev = sqrt(rho);
-    c->reason = STOP_NONE;
-    c->stop = STOP_NEVER;
 }
 
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -371,6 +240,7 @@ struct Run {
     int nb, chunk;
     bool graph;
     bool multishift;
+    bool ru_est;
     int nshift;
     CgBuffers *B;
     hipStream_t st;
@@ -394,6 +264,7 @@ struct Run {
         nb_64 = dslash_tile_blocks(g, plan_64.tile[0]);
         // occupancy queries of the capped-grid kernels, before any capture
         (void)flush_x_grid(vh, fmt.spinor, fmt.compute);
+        (void)cg_pupdate_grid(vh, fmt.spinor, fmt.compute, true);
         if (multishift) (void)shift_replay_grid(vh, fmt.spinor, fmt.compute);
     }
 
@@ -416,7 +287,7 @@ struct Run {
     hisq_status enq_iteration(int j) {
         const int jb = j % nb, jn = (j + 1) % nb;
         SolverCtrl *c = B->ctrl;
-        const Guard gns{&c->stop, j, 0}, gs_{&c->stop, j, 1};
+        const Guard gns{&c->stop, j, 0};
         DslashArgs A = dargs(gs, B->ts, B->p[jb], 1);
         A.guard = gns;
         HISQ_TRY_HIP(launch_dslash(A, fmt, plan_s, st, nullptr));
@@ -428,21 +299,35 @@ struct Run {
         Bk.partial = B->partial;
         Bk.guard = gns;
         HISQ_TRY_HIP(launch_dslash(Bk, fmt, plan_s, st, nullptr));
-        hipLaunchKernelGGL(k_fin_alpha, dim3(1), dim3(FIN_THREADS), 0, st, c, B->partial,
-                           nb_s, jb, gns);
-        HISQ_TRY_HIP(hipGetLastError());
-        HISQ_TRY_HIP(launch_cg_axpy(B->rs, B->aps, &c->alpha, vh, fmt.spinor, fmt.compute, B->partial, gns, st,
+        Sums pap, rr, pp{nullptr, 0};
+        HISQ_TRY(enq_sums<1>(B->partial, nb_s, SUMS_PAP, gns, &pap));
+        HISQ_TRY_HIP(launch_cg_axpy(B->rs, B->aps, c, pap, vh, fmt.spinor, fmt.compute, rpart(), jb, gns, st,
                                     multishift ? B->rr[jb] : nullptr));
-        hipLaunchKernelGGL(k_fin_beta, dim3(1), dim3(FIN_THREADS), 0, st, c, B->partial, blas_blocks(vh), gns,
-                           multishift ? 1 : 0, jb, B->ppart, blas_blocks(vh));
-        HISQ_TRY_HIP(hipGetLastError());
+        HISQ_TRY(enq_sums<2>(rpart(), blas_blocks(vh), SUMS_RR, gns, &rr));
+        // |p_k|^2 is summed before the update that overwrites its partials
+        if (ru_est) HISQ_TRY(enq_sums<1>(B->ppart, blas_blocks(vh), SUMS_PP, gns, &pp, true));
+        SpinorList pl;
+        for (int i = 0; i < HISQ_MAX_SHIFTS; i++) pl.p[i] = i < nb ? B->p[i] : nullptr;
+        HISQ_TRY_HIP(launch_cg_pupdate(B->p[jn], B->rs, B->p[jb], c, rr, pp.p, ru_est ? B->ppart : nullptr, B->x64, pl,
+                                       jb == nb - 1 ? nb : 0, multishift ? 1 : 0, jb, vh, fmt.spinor, fmt.compute, gns,
+                                       st));
         if (multishift && jb == nb - 1) HISQ_TRY(enq_shift_replay(nb, gns));
-        if (jb == nb - 1) {
-            SpinorList pl;
-            for (int i = 0; i < HISQ_MAX_SHIFTS; i++) pl.p[i] = i < nb ? B->p[i] : nullptr;
-            HISQ_TRY_HIP(launch_flush_x(B->x64, pl, nb, c->alpha_buf, vh, fmt.spinor, fmt.compute, gs_, st));
+        return HISQ_OK;
+    }
+    // partials of the residual update, apart from the Dslash's that its blocks read
+    double *rpart() const { return B->partial + 8192; }
+
+    // block partials for the next kernel: as they are when few, else added up in a launch
+    template <int NV>
+    hisq_status enq_sums(const double *partial, int n, int place, Guard gd, Sums *out, bool always = false) {
+        if (!always && n * NV <= SUMS_DIRECT) {
+            *out = Sums{partial, n};
+            return HISQ_OK;
         }
-        HISQ_TRY_HIP(launch_cg_pupdate(B->p[jn], B->rs, B->p[jb], c, B->ppart, vh, fmt.spinor, fmt.compute, gs_, st));
+        double *red = B->ctrl->red + place;
+        hipLaunchKernelGGL((k_fin_sum<NV>), dim3(1), dim3(FIN_THREADS), 0, st, partial, n, red, gd);
+        HISQ_TRY_HIP(hipGetLastError());
+        *out = Sums{red, 1};
         return HISQ_OK;
     }
     double c_ = 0.0;
@@ -504,10 +389,10 @@ struct Run {
         const Guard g0{&c->stop, 0, 0};
         HISQ_TRY_HIP(launch_ru_convert(B->rs, B->r64, mode == 1 ? nullptr : p_src, mode == 0 ? B->aps : nullptr,
                                        &c->alpha, vh, fmt.spinor, fmt.compute, B->partial, g0, st));
-        hipLaunchKernelGGL(k_fin_ru_finish, dim3(1), dim3(FIN_THREADS), 0, st, c, B->partial, blas_blocks(vh), mode, g0);
-        HISQ_TRY_HIP(hipGetLastError());
-        HISQ_TRY_HIP(launch_cg_pupdate(B->p[0], B->rs, mode == 1 ? B->rs : p_src, c, B->ppart, vh, fmt.spinor,
-                                       fmt.compute, g0, st));
+        Sums ru;
+        HISQ_TRY(enq_sums<4>(B->partial, blas_blocks(vh), SUMS_RU, g0, &ru));
+        HISQ_TRY_HIP(launch_ru_pupdate(B->p[0], B->rs, mode == 1 ? B->rs : p_src, c, ru, mode,
+                                       ru_est ? B->ppart : nullptr, vh, fmt.spinor, fmt.compute, g0, st));
         const double bs = spinor_site_bytes(fmt.spinor);
         alg_bytes += vh * (48.0 + 5 * bs) + vh * 3 * bs;
         return HISQ_OK;
@@ -789,6 +674,7 @@ extern "C" hisq_status hisq_cg_solve(double *x, const double *b, const hisq_gaug
     R.chunk = chunk_of(q);
     R.graph = q.use_graph != 0;
     R.multishift = false;
+    R.ru_est = q.ru_estimate != 0;
     R.nshift = 1;
     R.B = &B;
     R.st = E.ds->stream;
@@ -887,6 +773,7 @@ extern "C" hisq_status hisq_multishift_cg_solve(double *const *x, const double *
         R.chunk = chunk_of(q);
         R.graph = q.use_graph != 0;
         R.multishift = nshift > 1;
+        R.ru_est = q.ru_estimate != 0;
         R.nshift = nshift;
         R.B = &B;
         R.st = s_;
@@ -966,6 +853,7 @@ extern "C" hisq_status hisq_multishift_cg_solve(double *const *x, const double *
         R.chunk = chunk_of(q);
         R.graph = q.use_graph != 0;
         R.multishift = false;
+        R.ru_est = q.ru_estimate != 0;
         R.nshift = 1;
         Bi = B;
         if (i > 0) Bi.x64 = B.xs[i];
