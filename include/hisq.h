@@ -259,9 +259,9 @@ typedef struct {
                             default 8 */
     int pr_beta;         /* 1: Polak-Ribiere beta (Sec. 3.1 item 3); 0: Fletcher-Reeves */
     int reproject;       /* 1: re-project the gradient vector at each reliable update (Sec. 3.1 item 2) */
-    int poll_every;      /* iterations enqueued between host polls of the device state (rounded up to a
-                            multiple of grad_buffer); 0 = default */
-    int use_graph;       /* 1: replay each block of iterations as a captured hipGraph */
+    int poll_every;      /* iterations the host may have enqueued beyond the last state it has read (rounded up
+                            to a multiple of grad_buffer); 0 = default */
+    int use_graph;       /* 1: replay each unit of iterations as a captured hipGraph */
     double shift_floor;  /* multi-shift: a shifted system stops updating once its iterated residual is below
                             max(tol_i, shift_floor) (Sec. 3.2: the shifts stop at the sloppy precision's
                             limit); <= 0 selects that limit: none (tol_i alone) for triplets with FP64

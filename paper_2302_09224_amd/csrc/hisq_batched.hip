@@ -262,8 +262,13 @@ struct BRun {
     int nrhs;
     hisq_fmt fmt;
     const hisq_gauge *g64, *gs;
-    int nb, chunk;
+    int nb;
+    int unit;                 // iterations enqueued (and captured) as a whole, a multiple of nb
+    int depth;                // units kept in flight at most
     bool graph;
+    SolverHost *h = nullptr;
+    Status last{};
+    int inflight = 0;
     BBuf *B;
     hipStream_t st;
     size_t fs, fs64;
@@ -338,13 +343,11 @@ struct BRun {
 
     // the sloppy launches cover the systems still iterating; a change of that set
     // re-plans them and drops the captured block of iterations
-    hisq_status remap_sloppy(const SolverCtrl *h) {
-        unsigned mask = 0;
-        for (int j = 0; j < nrhs; j++)
-            if (h->bactive[j]) mask |= 1u << j;
+    hisq_status remap_sloppy() {
+        const unsigned mask = last.act;
         if (mask == 0 || mask == ms_.mask) return HISQ_OK;
         ms_ = map_columns(fmt, gs, B->ts, B->rs, mask);
-        if (exec) {
+        if (exec) {   // idle: the status read before this call came after every unit
             HISQ_TRY_HIP(hipGraphExecDestroy(exec));
             exec = nullptr;
         }
@@ -352,7 +355,10 @@ struct BRun {
     }
 
     ~BRun() {
-        if (exec) (void)hipGraphExecDestroy(exec);
+        if (exec) {
+            (void)hipStreamSynchronize(st);
+            (void)hipGraphExecDestroy(exec);
+        }
     }
 
     DslashArgs dargs(const hisq_gauge *gg, const hisq_fmt &f, char *out, const char *in, int parity) const {
@@ -449,23 +455,34 @@ struct BRun {
         return HISQ_OK;
     }
 
-    hisq_status read_ctrl(SolverCtrl *h) {
-        HISQ_TRY_HIP(hipMemcpyAsync(h, B->ctrl, sizeof(SolverCtrl), hipMemcpyDeviceToHost, st));
+    hisq_status read_ctrl() {
+        HISQ_TRY_HIP(hipMemcpyAsync(&h->ctrl, B->ctrl, sizeof(SolverCtrl), hipMemcpyDeviceToHost, st));
         HISQ_TRY_HIP(hipStreamSynchronize(st));
         return HISQ_OK;
     }
 
-    hisq_status enq_chunk() {
+    // the control block's state now, after everything enqueued
+    hisq_status read_status() {
+        HISQ_TRY_HIP(launch_status(B->ctrl, h, nrhs, st));
+        h->launched++;
+        inflight = 0;
+        return wait_status(h, h->launched, st, &last);
+    }
+
+    // a unit of iterations and its status record
+    hisq_status enq_unit() {
         if (graph) {
             if (!exec) {
                 hipGraph_t gr = nullptr;
                 HISQ_TRY_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
                 hisq_status s = HISQ_OK;
-                for (int j = 0; j < chunk && s == HISQ_OK; j++) s = enq_iteration(j);
+                for (int j = 0; j < unit && s == HISQ_OK; j++) s = enq_iteration(j);
+                hipError_t es = launch_status(B->ctrl, h, nrhs, st);
                 hipError_t e = hipStreamEndCapture(st, &gr);
-                if (s != HISQ_OK) {
+                if (e == hipSuccess) e = es;
+                if (s != HISQ_OK || e != hipSuccess) {
                     if (gr) (void)hipGraphDestroy(gr);
-                    return s;
+                    if (s != HISQ_OK) return s;
                 }
                 HISQ_TRY_HIP(e);
                 e = hipGraphInstantiate(&exec, gr, nullptr, nullptr, 0);
@@ -473,9 +490,12 @@ struct BRun {
                 HISQ_TRY_HIP(e);
             }
             HISQ_TRY_HIP(hipGraphLaunch(exec, st));
-            return HISQ_OK;
+        } else {
+            for (int j = 0; j < unit; j++) HISQ_TRY(enq_iteration(j));
+            HISQ_TRY_HIP(launch_status(B->ctrl, h, nrhs, st));
         }
-        for (int j = 0; j < chunk; j++) HISQ_TRY(enq_iteration(j));
+        h->launched++;
+        inflight++;
         return HISQ_OK;
     }
 };
@@ -483,7 +503,7 @@ struct BRun {
 struct BDev {
     hipStream_t stream = nullptr;
     hipEvent_t ev = nullptr;
-    SolverCtrl *host = nullptr;
+    SolverHost *host = nullptr;
     std::mutex mu;
 };
 BDev g_bdev[64];
@@ -517,7 +537,8 @@ hisq_status batched_run(BatchedJob &J) {
     R.g64 = J.g64;
     R.gs = J.gs;
     R.nb = q.grad_buffer;
-    R.chunk = ((q.poll_every + q.grad_buffer - 1) / q.grad_buffer) * q.grad_buffer;
+    solver_unit(q, &R.unit, &R.depth);
+    R.h = J.h;
     R.graph = q.use_graph != 0;
     R.B = &B;
     R.st = s_;
@@ -528,8 +549,9 @@ hisq_status batched_run(BatchedJob &J) {
         HISQ_TRY_HIP(launch_spinor_pack(B.x64 + j * R.fs64, J.x[j], g.vh, SF_F64, s_));
         HISQ_TRY_HIP(launch_spinor_pack(B.b64 + j * R.fs64, J.b[j], g.vh, SF_F64, s_));
     }
-    SolverCtrl *h = J.h;
+    SolverCtrl *h = &J.h->ctrl;
     memset(h, 0, sizeof(*h));
+    h->seq = J.h->launched;
     h->stop = STOP_NEVER;
     h->pr = q.pr_beta;
     h->reproject = q.reproject;
@@ -586,61 +608,69 @@ hisq_status batched_run(BatchedJob &J) {
     hisq_status status = HISQ_OK;
     if (m0) {
         status = R.enq_reliable(1, 0, J.p_warm ? B.p[0] : nullptr, m0);
-        if (status == HISQ_OK) status = R.read_ctrl(h);
+        if (status == HISQ_OK) status = R.read_ctrl();   // the initial residuals
+        if (status == HISQ_OK) status = R.read_status();
     } else {
-        h->done = 1;
+        R.last.done = 1;
     }
     for (int j = 0; j < nrhs; j++) J.resid0_j[j] = h->bb2[j] > 0 ? std::sqrt(h->br2_true[j] / h->bb2[j]) : 0.0;
-    if (status == HISQ_OK && !h->done) status = R.remap_sloppy(h);
+    if (status == HISQ_OK && !R.last.done) status = R.remap_sloppy();
     long k0 = 0;
-    while (status == HISQ_OK && !h->done) {
-        if (h->breakdown) {
+    Pace pace;
+    while (status == HISQ_OK && !R.last.done) {
+        if (R.last.breakdown) {
             status = set_error(HISQ_EBREAKDOWN, "batched CG breakdown");
             break;
         }
-        status = R.enq_chunk();
+        // the next unit is enqueued before the running one is read, unless the
+        // block is about to stop in what is enqueued already
+        while (status == HISQ_OK && R.inflight < R.depth &&
+               (R.inflight == 0 || pace.left > (double)R.inflight * R.unit))
+            status = R.enq_unit();
         if (status != HISQ_OK) break;
-        status = R.read_ctrl(h);
+        status = wait_status(R.h, R.h->launched - (unsigned long long)R.inflight + 1, s_, &R.last);
         if (status != HISQ_OK) break;
-        const long dk = h->k - k0;
-        k0 = h->k;
+        R.inflight--;
+        const Status &now = R.last;
+        const long dk = now.k - k0;
+        k0 = now.k;
         R.iters += dk;
         R.dsl += 2 * dk;
         {
             // links once per Dslash; spinor traffic of the systems still iterating
-            int na = 0;
-            for (int j = 0; j < nrhs; j++) na += h->bactive[j] ? 1 : 0;
+            const int na = __builtin_popcount(now.act);
             const double bs = spinor_site_bytes(J.fmt.spinor), bl = dslash_link_bytes(J.gs);
             R.alg += dk * (double)g.vh * (2.0 * (bl + na * 2.0 * bs) + na * (7.0 * bs + (R.nb * bs + 96.0) / R.nb));
         }
-        if (h->stop == STOP_NEVER) continue;
-        if (h->breakdown) {
-            status = set_error(HISQ_EBREAKDOWN, "batched CG breakdown after %d iterations", h->k);
+        pace.update(now);
+        if (now.stop == STOP_NEVER) continue;
+        if (now.breakdown) {
+            status = set_error(HISQ_EBREAKDOWN, "batched CG breakdown after %d iterations", now.k);
             break;
         }
-        if (h->stop < 0 || h->stop >= R.chunk) {
-            status = set_error(HISQ_EBREAKDOWN, "inconsistent batched solver state (stop %d)", h->stop);
+        if (now.stop < 0 || now.stop >= R.unit) {
+            status = set_error(HISQ_EBREAKDOWN, "inconsistent batched solver state (stop %d)", now.stop);
             break;
         }
-        const int jb = h->stop % R.nb;
-        const int reason = h->reason;
-        unsigned rum = 0, act = 0;
-        for (int j = 0; j < nrhs; j++) {
-            if (h->bru[j] && h->bactive[j]) rum |= 1u << j;
-            if (h->bactive[j]) act |= 1u << j;
-        }
-        status = R.enq_reliable(0, jb + 1, B.p[jb], rum ? rum : act);
+        const int jb = now.stop % R.nb;
+        const int reason = now.reason;
+        status = R.enq_reliable(0, jb + 1, B.p[jb], now.ru ? now.ru : now.act);
         if (status != HISQ_OK) break;
         R.rus++;
-        status = R.read_ctrl(h);
+        pace.reset();
+        status = R.read_status();   // which systems are left decides the next units
         if (status != HISQ_OK) break;
-        if (h->done) break;
-        status = R.remap_sloppy(h);
+        if (R.last.done) break;
+        status = R.remap_sloppy();
         if (status != HISQ_OK) break;
-        if (reason == STOP_MAXITER || h->k >= q.maxiter) {
-            status = set_error(HISQ_ENOCONV, "batched CG: no convergence in %d iterations", h->k);
+        if (reason == STOP_MAXITER || R.last.k >= q.maxiter) {
+            status = set_error(HISQ_ENOCONV, "batched CG: no convergence in %d iterations", R.last.k);
             break;
         }
+    }
+    {
+        const hisq_status sr = R.read_ctrl();   // every system's residual and iterations
+        if (status == HISQ_OK) status = sr;
     }
     for (int j = 0; j < nrhs; j++) {
         hipError_t e = launch_spinor_unpack(J.x[j], B.x64 + j * R.fs64, g.vh, SF_F64, s_);
@@ -713,7 +743,7 @@ extern "C" hisq_status hisq_cg_solve_batched(double *x, const double *b, int nrh
     if (!dv.stream) {
         HISQ_TRY_HIP(hipStreamCreateWithFlags(&dv.stream, hipStreamNonBlocking));
         HISQ_TRY_HIP(hipEventCreateWithFlags(&dv.ev, hipEventDisableTiming));
-        HISQ_TRY_HIP(hipHostMalloc((void **)&dv.host, sizeof(SolverCtrl), hipHostMallocDefault));
+        HISQ_TRY(solver_host_alloc(&dv.host));
     }
     HISQ_TRY_HIP(hipEventRecord(dv.ev, (hipStream_t)stream));
     HISQ_TRY_HIP(hipStreamWaitEvent(dv.stream, dv.ev, 0));

@@ -8,8 +8,11 @@
 // and are taken on the values as stored (after packing), which is what the
 // next iteration will read.
 #include <algorithm>
+#include <chrono>
+#include <cstring>
 #include <map>
 #include <mutex>
+#include <thread>
 #include <utility>
 
 #include "hisq_internal.h"
@@ -1028,6 +1031,47 @@ __global__ void k_bru_convert(char *rs, const char *r64, size_t fs64, const char
     }
 }
 
+// one wave; see Status
+__global__ void k_status(SolverCtrl *c, SolverHost *h, int nrhs) {
+    const int lane = threadIdx.x;
+    double lead = 1e300;
+    unsigned act = 0, ru = 0;
+    if (nrhs) {
+        const bool on = lane < nrhs && c->bactive[lane & 15];
+        if (on) {
+            const double t = fmax(c->delta2 * c->brmax2[lane], c->btol2[lane] * c->bb2[lane]);
+            if (t > 0.0) lead = c->brho[lane] / t;
+        }
+        act = (unsigned)__ballot(on);
+        ru = (unsigned)__ballot(on && c->bru[lane & 15]);
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) lead = fmin(lead, __shfl_xor(lead, o, 64));
+    } else {
+        const double t = fmax(c->delta2 * c->rmax2, c->tol2 * c->b2);
+        if (t > 0.0) lead = c->rho / t;
+    }
+    if (lane) return;
+    const unsigned long long seq = c->seq + 1;
+    c->seq = seq;
+    Status *s = &h->ring[seq % STATUS_RING];
+    const int stop = c->stop;
+    s->stop = stop;
+    s->reason = c->reason;
+    s->k = c->k;
+    s->done = c->done;
+    s->breakdown = c->breakdown;
+    s->e_mask = c->e_mask;
+    s->act = act;
+    s->ru = ru;
+    s->b2 = c->b2;
+    s->r2_true = c->r2_true;
+    s->pi = c->pi;
+    s->rho_new = c->rho_new;
+    s->lead = lead;
+    if (stop != STOP_NEVER) c->stop = -1;
+    __hip_atomic_store(&s->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // dispatch on the sloppy triplet's spinor format and compute precision
 #define HISQ_DISPATCH_SC(sf, compute, CALL)                                           \
     do {                                                                              \
@@ -1057,6 +1101,38 @@ __global__ void k_bru_convert(char *rs, const char *r64, size_t fs64, const char
     } while (0)
 
 }  // namespace
+
+hisq_status solver_host_alloc(SolverHost **h) {
+    HISQ_TRY_HIP(hipHostMalloc((void **)h, sizeof(SolverHost), hipHostMallocCoherent));
+    memset(*h, 0, sizeof(SolverHost));
+    return HISQ_OK;
+}
+
+hipError_t launch_status(SolverCtrl *c, SolverHost *h, int nrhs, hipStream_t st) {
+    hipLaunchKernelGGL(k_status, dim3(1), dim3(64), 0, st, c, h, nrhs);
+    return hipGetLastError();
+}
+
+hisq_status wait_status(SolverHost *h, unsigned long long seq, hipStream_t st, Status *out) {
+    const Status *s = &h->ring[seq % STATUS_RING];
+    const auto t0 = std::chrono::steady_clock::now();
+    for (long n = 1; __atomic_load_n(&s->seq, __ATOMIC_ACQUIRE) != seq; n++) {
+        if (n % 256) {
+            __builtin_ia32_pause();
+            continue;
+        }
+        // a unit takes 0.1 ms (small lattices) to tens of ms; the stream's own state tells of an error
+        if (std::chrono::steady_clock::now() - t0 < std::chrono::milliseconds(1)) continue;
+        const hipError_t e = hipStreamQuery(st);
+        if (e == hipSuccess && __atomic_load_n(&s->seq, __ATOMIC_ACQUIRE) != seq)
+            return set_error(HISQ_EHIP, "solver status record %llu missing after its stream drained", seq);
+        if (e != hipSuccess && e != hipErrorNotReady)
+            return set_error(HISQ_EHIP, "solver stream: %s", hipGetErrorString(e));
+        std::this_thread::sleep_for(std::chrono::microseconds(20));
+    }
+    *out = *s;
+    return HISQ_OK;
+}
 
 hipError_t launch_spinor_pack(char *dst, const double *src, size_t n, int sf, hipStream_t st) {
     if (n == 0) return hipSuccess;

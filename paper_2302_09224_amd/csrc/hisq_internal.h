@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -233,6 +234,7 @@ struct SolverCtrl {
     int o_k, o_active_mask;
     double o_rho, o_rmax2, o_dev, o_rnorm_prev, o_anorm, o_alpha_prev, o_beta_prev;
     double o_zeta[HISQ_MAX_SHIFTS], o_zeta_prev[HISQ_MAX_SHIFTS];
+    unsigned long long seq;   // status records published so far (StatusBoard)
     double red[8];   // sums of block partials too many for every consumer block to add up (SUMS_* offsets)
     int shift_stop_k[HISQ_MAX_SHIFTS];
     // batched CG: per right-hand side scalars
@@ -253,6 +255,60 @@ constexpr int STOP_NEVER = 0x3fffffff;
 
 struct SpinorList {
     char *p[HISQ_MAX_SHIFTS];
+};
+
+// What the host reads after a unit of iterations, written by the unit's last
+// kernel straight into pinned host memory (record seq % STATUS_RING, seq last):
+// the host polls a word instead of waiting for a copy of the control block, and
+// may have enqueued the next unit before it looks.
+struct Status {
+    unsigned long long seq;
+    int stop, reason, k, done, breakdown, e_mask;
+    unsigned act, ru;      // batched: systems iterating, systems that asked for a reliable update
+    double b2, r2_true, pi, rho_new;
+    double lead;           // smallest |r|^2 / (|r|^2 that stops the block) of the systems iterating
+};
+constexpr int STATUS_RING = 8;
+// pinned host side of one control block
+struct SolverHost {
+    SolverCtrl ctrl;                 // copy source and target of the control block
+    Status ring[STATUS_RING];
+    unsigned long long launched;     // status records enqueued so far (the device's counter continues from here)
+};
+hisq_status solver_host_alloc(SolverHost **h);
+// publish the control block's state (nrhs 0: a single system, else the batched fields); a
+// block that has stopped is closed: the iterations of a unit already enqueued behind it do nothing
+hipError_t launch_status(SolverCtrl *c, SolverHost *h, int nrhs, hipStream_t st);
+// wait for record `seq`; HISQ_EHIP when the stream fails first
+hisq_status wait_status(SolverHost *h, unsigned long long seq, hipStream_t st, Status *out);
+
+// iterations per unit (a multiple of grad_buffer, at least 8 so that the status
+// record's launch is a few per cent of a small lattice's unit) and the units in
+// flight: two when poll_every covers them, so that the host's turn between units
+// costs the device nothing
+inline void solver_unit(const hisq_solver_params &p, int *unit, int *depth) {
+    const int nb = p.grad_buffer;
+    const int chunk = ((p.poll_every + nb - 1) / nb) * nb;
+    const int u = ((8 + nb - 1) / nb) * nb;
+    *unit = u < chunk ? u : chunk;
+    *depth = chunk >= 2 * *unit ? 2 : 1;
+}
+
+// The pace of a solve, from which the host decides how many units to keep
+// enqueued: iterations left before the block stops, at the rate of the last unit.
+struct Pace {
+    double lead = 0.0, left = 1e30;
+    long k = -1;
+    void update(const Status &s) {
+        left = 1e30;
+        if (k >= 0 && s.k > k && s.lead > 0.0 && s.lead < lead) left = log(s.lead) / (log(lead / s.lead) / (double)(s.k - k));
+        lead = s.lead;
+        k = s.k;
+    }
+    void reset() {
+        k = -1;
+        left = 1e30;
+    }
 };
 
 // Block partials of NV sums each that the next kernel's blocks add up
@@ -332,7 +388,7 @@ struct BatchedJob {
     void *ws;
     size_t ws_bytes;
     hipStream_t st;
-    SolverCtrl *h;          // pinned host copy of the control block
+    SolverHost *h;          // pinned host side of the control block
     // optional: called once every launch shape the block can use has been
     // planned (tuned on first use) and before the first iteration, so that
     // work the caller starts there on another stream never overlaps a timing

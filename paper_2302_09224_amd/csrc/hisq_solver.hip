@@ -3,9 +3,9 @@
 // Design (MI355X): every scalar of the recurrences lives on the device in a
 // SolverCtrl block and is formed by the vector kernel that needs it first, from
 // the per-block partials of the preceding kernel summed in a fixed order.  No
-// iteration needs the host: the host enqueues blocks of `chunk` iterations
-// (optionally as one captured hipGraph replayed per block) and polls the
-// control block once per block.  A kernel that decides to leave the
+// iteration needs the host: the host enqueues units of iterations (optionally as
+// one captured hipGraph replayed per unit), the next one before the running one
+// has ended, and reads a status record that each unit leaves in host memory.  A kernel that decides to leave the
 // loop (reliable update due, convergence candidate, multi-shift phase done,
 // breakdown, iteration cap) lowers ctrl->stop, and every later kernel of the
 // block sees its guard fail and returns at once.  The host then performs the
@@ -113,18 +113,18 @@ __global__ void k_fin_ru_check(SolverCtrl *c, const double *partial, int n) {
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 // ---------------------------------------------------------------------------
-// library-owned stream (default priority) and pinned mirror of the control block
+// library-owned stream (default priority) and pinned host side of the control block
 // ---------------------------------------------------------------------------
 
 struct DevState {
     hipStream_t stream = nullptr;
     hipEvent_t ev = nullptr;
-    SolverCtrl *host_ctrl = nullptr;
+    SolverHost *host = nullptr;
     // the second stream of the multi-shift refinement (shifted systems batched
     // while the base system is refined on `stream`)
     hipStream_t stream2 = nullptr;
     hipEvent_t ev2 = nullptr;
-    SolverCtrl *host_ctrl2 = nullptr;
+    SolverHost *host2 = nullptr;
     std::mutex mu;
 };
 
@@ -138,10 +138,10 @@ hisq_status dev_state(DevState **out) {
     if (!s.stream) {
         HISQ_TRY_HIP(hipStreamCreateWithFlags(&s.stream, hipStreamNonBlocking));
         HISQ_TRY_HIP(hipEventCreateWithFlags(&s.ev, hipEventDisableTiming));
-        HISQ_TRY_HIP(hipHostMalloc((void **)&s.host_ctrl, sizeof(SolverCtrl), hipHostMallocDefault));
+        HISQ_TRY(solver_host_alloc(&s.host));
         HISQ_TRY_HIP(hipStreamCreateWithFlags(&s.stream2, hipStreamNonBlocking));
         HISQ_TRY_HIP(hipEventCreateWithFlags(&s.ev2, hipEventDisableTiming));
-        HISQ_TRY_HIP(hipHostMalloc((void **)&s.host_ctrl2, sizeof(SolverCtrl), hipHostMallocDefault));
+        HISQ_TRY(solver_host_alloc(&s.host2));
     }
     *out = &s;
     return HISQ_OK;
@@ -237,17 +237,22 @@ struct Run {
     hisq_fmt fmt;              // sloppy triplet
     const hisq_gauge *g64, *gs;
     double c;                  // 4m^2 + shift of the system being iterated
-    int nb, chunk;
+    int nb;
+    int unit;                  // iterations enqueued (and captured) as a whole, a multiple of nb
+    int depth;                 // units kept in flight at most
     bool graph;
     bool multishift;
     bool ru_est;
     int nshift;
     CgBuffers *B;
     hipStream_t st;
-    DevState *ds;
+    SolverHost *h = nullptr;   // pinned host side of the control block
+    Status last{};             // the last status record read
+    int inflight = 0;          // units enqueued whose records have not been read
     // counters
     long dslash_sloppy = 0, dslash_f64 = 0, rus = 0, iters = 0;
     double alg_bytes = 0.0;
+    int maxiter = 0;
     int last_slot = 0;         // slot of the current gradient vector when the run ended
     hipGraphExec_t exec = nullptr;
     DslashPlan plan_s{}, plan_64{};
@@ -398,23 +403,35 @@ struct Run {
         return HISQ_OK;
     }
 
-    hisq_status read_ctrl(SolverCtrl *h) {
-        HISQ_TRY_HIP(hipMemcpyAsync(h, B->ctrl, sizeof(SolverCtrl), hipMemcpyDeviceToHost, st));
+    hisq_status read_ctrl() {
+        HISQ_TRY_HIP(hipMemcpyAsync(&h->ctrl, B->ctrl, sizeof(SolverCtrl), hipMemcpyDeviceToHost, st));
         HISQ_TRY_HIP(hipStreamSynchronize(st));
+        inflight = 0;
         return HISQ_OK;
     }
 
-    hisq_status enq_chunk() {
+    // the control block's state now (every record still outstanding is skipped)
+    hisq_status read_status() {
+        HISQ_TRY_HIP(launch_status(B->ctrl, h, 0, st));
+        h->launched++;
+        inflight = 0;
+        return wait_status(h, h->launched, st, &last);
+    }
+
+    // a unit of iterations and its status record
+    hisq_status enq_unit() {
         if (graph) {
             if (!exec) {
                 hipGraph_t gr = nullptr;
                 HISQ_TRY_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
                 hisq_status s = HISQ_OK;
-                for (int j = 0; j < chunk && s == HISQ_OK; j++) s = enq_iteration(j);
+                for (int j = 0; j < unit && s == HISQ_OK; j++) s = enq_iteration(j);
+                hipError_t es = launch_status(B->ctrl, h, 0, st);
                 hipError_t e = hipStreamEndCapture(st, &gr);
-                if (s != HISQ_OK) {
+                if (e == hipSuccess) e = es;
+                if (s != HISQ_OK || e != hipSuccess) {
                     if (gr) (void)hipGraphDestroy(gr);
-                    return s;
+                    if (s != HISQ_OK) return s;
                 }
                 HISQ_TRY_HIP(e);
                 e = hipGraphInstantiate(&exec, gr, nullptr, nullptr, 0);
@@ -422,9 +439,12 @@ struct Run {
                 HISQ_TRY_HIP(e);
             }
             HISQ_TRY_HIP(hipGraphLaunch(exec, st));
-            return HISQ_OK;
+        } else {
+            for (int j = 0; j < unit; j++) HISQ_TRY(enq_iteration(j));
+            HISQ_TRY_HIP(launch_status(B->ctrl, h, 0, st));
         }
-        for (int j = 0; j < chunk; j++) HISQ_TRY(enq_iteration(j));
+        h->launched++;
+        inflight++;
         return HISQ_OK;
     }
 
@@ -438,15 +458,23 @@ struct Run {
     }
 
     // Iterate until the true residual meets tol (returns OK), or the
-    // multi-shift phase ends (OK, *ms_done = 1), or an error.
-    hisq_status iterate(SolverCtrl *h, int *ms_done) {
+    // multi-shift phase ends (OK, *ms_done = 1), or an error.  The next unit is
+    // enqueued before the running one is read, unless the pace says that the
+    // block stops in what is enqueued already: units behind a stop only return
+    // from their guards (1.6 us a launch).  After a reliable update the next
+    // unit follows at once; its record tells whether the update met tol.
+    hisq_status iterate(int *ms_done) {
         if (ms_done) *ms_done = 0;
-        long k0 = h->k;
+        long k0 = last.k;
+        Pace pace;
         for (;;) {
-            HISQ_TRY(enq_chunk());
-            HISQ_TRY(read_ctrl(h));
-            const long dk = h->k - k0;
-            k0 = h->k;
+            while (inflight < depth && (inflight == 0 || pace.left > (double)inflight * unit)) HISQ_TRY(enq_unit());
+            const unsigned long long seq = h->launched - (unsigned long long)inflight + 1;
+            HISQ_TRY(wait_status(h, seq, st, &last));
+            inflight--;
+            if (last.done) return HISQ_OK;
+            const long dk = last.k - k0;
+            k0 = last.k;
             iters += dk;
             dslash_sloppy += 2 * dk;
             alg_bytes += dk * iter_bytes();
@@ -455,19 +483,21 @@ struct Run {
                 // updated shift, once per block of N_b iterations: its gradient vector read
                 // and written and its FP64 solution read and written
                 const double bs = spinor_site_bytes(fmt.spinor);
-                const int ne = __builtin_popcount((unsigned)h->e_mask);
+                const int ne = __builtin_popcount((unsigned)last.e_mask);
                 alg_bytes += dk * (double)vh * (2.0 * bs + ne * (2.0 * bs + 96.0) / nb);
             }
-            if (h->stop == STOP_NEVER) continue;
-            if (h->breakdown)
+            if (last.breakdown)
                 return set_error(HISQ_EBREAKDOWN, "solver breakdown after %d iterations (pAp = %g, |r|^2 = %g)",
-                                 h->k, h->pi, h->rho_new);
-            if (h->stop < 0 || h->stop >= chunk)
-                return set_error(HISQ_EBREAKDOWN, "inconsistent solver state (stop %d, reason %d)", h->stop, h->reason);
-            const int js = h->stop, jb = js % nb;
+                                 last.k, last.pi, last.rho_new);
+            pace.update(last);
+            if (last.stop == STOP_NEVER) continue;
+            if (last.stop < 0 || last.stop >= unit)
+                return set_error(HISQ_EBREAKDOWN, "inconsistent solver state (stop %d, reason %d)", last.stop, last.reason);
+            inflight = 0;   // the units behind the stop do nothing; their records are skipped
+            const int js = last.stop, jb = js % nb;
             last_slot = jb;
             HISQ_TRY(realign_shifts(jb));
-            if (h->reason == STOP_MSDONE) {
+            if (last.reason == STOP_MSDONE) {
                 SpinorList pl;
                 for (int i = 0; i < HISQ_MAX_SHIFTS; i++) pl.p[i] = i < nb ? B->p[i] : nullptr;
                 HISQ_TRY_HIP(launch_flush_x(B->x64, pl, jb + 1, B->ctrl->alpha_buf, vh, fmt.spinor, fmt.compute,
@@ -475,26 +505,34 @@ struct Run {
                 if (ms_done) *ms_done = 1;
                 return HISQ_OK;
             }
-            const int reason = h->reason;
+            const int reason = last.reason;
             HISQ_TRY(enq_reliable(0, jb + 1, B->p[jb]));
             rus++;
-            HISQ_TRY(read_ctrl(h));
             last_slot = 0;
-            if (h->breakdown) return set_error(HISQ_EBREAKDOWN, "non-finite true residual");
-            if (h->done) return HISQ_OK;
-            if (reason == STOP_MAXITER || h->k >= h->maxiter)
-                return set_error(HISQ_ENOCONV, "no convergence in %d iterations (true residual %g)", h->k,
-                                 std::sqrt(h->r2_true / h->b2));
+            pace.reset();
+            if (reason == STOP_RU && last.k < maxiter) continue;
+            HISQ_TRY(read_status());
+            if (last.breakdown) return set_error(HISQ_EBREAKDOWN, "non-finite true residual");
+            if (last.done) return HISQ_OK;
+            if (reason == STOP_MAXITER || last.k >= maxiter)
+                return set_error(HISQ_ENOCONV, "no convergence in %d iterations (true residual %g)", last.k,
+                                 std::sqrt(last.r2_true / last.b2));
         }
     }
 
     ~Run() {
-        if (exec) (void)hipGraphExecDestroy(exec);
+        // a unit behind the last stop may still be running
+        if (exec) {
+            (void)hipStreamSynchronize(st);
+            (void)hipGraphExecDestroy(exec);
+        }
     }
 };
 
-void init_ctrl(SolverCtrl *h, const hisq_solver_params &p, double tol, double b2, int sloppy_spinor) {
+void init_ctrl(SolverHost *host, const hisq_solver_params &p, double tol, double b2, int sloppy_spinor) {
+    SolverCtrl *h = &host->ctrl;
     memset(h, 0, sizeof(*h));
+    h->seq = host->launched;
     h->ru_est = p.ru_estimate;
     h->eps_s = std::ldexp(1.0, -sloppy_floor_bits(sloppy_spinor));
     h->stop = STOP_NEVER;
@@ -541,11 +579,6 @@ MsLayout ms_layout(const Geom &g, int nshift, const hisq_fmt &ms_fmt, const hisq
     return L;
 }
 
-int chunk_of(const hisq_solver_params &p) {
-    const int nb = p.grad_buffer;
-    return ((p.poll_every + nb - 1) / nb) * nb;
-}
-
 hisq_status check_gauge(const hisq_gauge *gg, const int dims[4], const hisq_fmt &f, const char *what) {
     if (!gg || !gg->fat || !gg->lng) return set_error(HISQ_EINVAL, "%s: null gauge field", what);
     for (int k = 0; k < 4; k++)
@@ -569,18 +602,18 @@ hisq_status enq_b2(Run &R) {
 // Full CG on prepared buffers (x64, b64 filled).  mode 1: fresh start; mode 2:
 // continue the gradient vector p_init (refinement format) with rho_prev.
 hisq_status cg_core(Run &R, const hisq_solver_params &p, double tol, int mode, const char *p_init, double rho_prev,
-                    SolverCtrl *h, double *resid0) {
-    init_ctrl(h, p, tol, 0.0, R.fmt.spinor);
-    h->rho_prev = rho_prev;
-    HISQ_TRY_HIP(hipMemcpyAsync(R.B->ctrl, h, sizeof(SolverCtrl), hipMemcpyHostToDevice, R.st));
+                    double *resid0) {
+    init_ctrl(R.h, p, tol, 0.0, R.fmt.spinor);
+    R.h->ctrl.rho_prev = rho_prev;
+    HISQ_TRY_HIP(hipMemcpyAsync(R.B->ctrl, &R.h->ctrl, sizeof(SolverCtrl), hipMemcpyHostToDevice, R.st));
     R.setup_plans();
     HISQ_TRY(enq_b2(R));
     HISQ_TRY(R.enq_reliable(mode, 0, mode == 2 ? p_init : nullptr));
-    HISQ_TRY(R.read_ctrl(h));
-    if (resid0) *resid0 = h->b2 > 0 ? std::sqrt(h->r2_true / h->b2) : 0.0;
-    if (h->breakdown) return set_error(HISQ_EBREAKDOWN, "non-finite initial residual");
-    if (h->b2 == 0.0 || h->done) return HISQ_OK;
-    return R.iterate(h, nullptr);
+    HISQ_TRY(R.read_status());
+    if (resid0) *resid0 = R.last.b2 > 0 ? std::sqrt(R.last.r2_true / R.last.b2) : 0.0;
+    if (R.last.breakdown) return set_error(HISQ_EBREAKDOWN, "non-finite initial residual");
+    if (R.last.b2 == 0.0 || R.last.done) return HISQ_OK;
+    return R.iterate(nullptr);
 }
 
 void fill_common_stats(hisq_solver_stats *s, const Run &R) {
@@ -671,18 +704,18 @@ extern "C" hisq_status hisq_cg_solve(double *x, const double *b, const hisq_gaug
     R.gs = gs;
     R.c_ = 4.0 * mass * mass + shift;
     R.nb = q.grad_buffer;
-    R.chunk = chunk_of(q);
+    solver_unit(q, &R.unit, &R.depth);
+    R.maxiter = q.maxiter;
     R.graph = q.use_graph != 0;
     R.multishift = false;
     R.ru_est = q.ru_estimate != 0;
     R.nshift = 1;
     R.B = &B;
     R.st = E.ds->stream;
-    R.ds = E.ds;
+    R.h = E.ds->host;
     HISQ_TRY_HIP(launch_spinor_pack(B.x64, x, g.vh, SF_F64, R.st));
     HISQ_TRY_HIP(launch_spinor_pack(B.b64, b, g.vh, SF_F64, R.st));
-    SolverCtrl *h = E.ds->host_ctrl;
-    hisq_status s = cg_core(R, q, tol, 1, nullptr, 0.0, h, nullptr);
+    hisq_status s = cg_core(R, q, tol, 1, nullptr, 0.0, nullptr);
     if (s == HISQ_OK || s == HISQ_ENOCONV || s == HISQ_EBREAKDOWN) {
         hipError_t e = launch_spinor_unpack(x, B.x64, g.vh, SF_F64, R.st);
         if (e != hipSuccess && s == HISQ_OK) s = set_error(HISQ_EHIP, "unpack: %s", hipGetErrorString(e));
@@ -690,7 +723,7 @@ extern "C" hisq_status hisq_cg_solve(double *x, const double *b, const hisq_gaug
     hisq_status s2 = E.end();
     if (s == HISQ_OK) s = s2;
     fill_common_stats(st, R);
-    st->true_resid = h->b2 > 0 ? std::sqrt(h->r2_true / h->b2) : 0.0;
+    st->true_resid = R.last.b2 > 0 ? std::sqrt(R.last.r2_true / R.last.b2) : 0.0;
     st->nshift = 1;
     st->shift_resid[0] = st->true_resid;
     st->status = s;
@@ -750,7 +783,7 @@ extern "C" hisq_status hisq_multishift_cg_solve(double *const *x, const double *
     Entry E;
     HISQ_TRY(E.begin(stream));
     hipStream_t s_ = E.ds->stream;
-    SolverCtrl *h = E.ds->host_ctrl;
+    SolverCtrl *h = &E.ds->host->ctrl;
     st->nshift = nshift;
     hisq_status status = HISQ_OK;
     const double m2 = 4.0 * mass * mass;
@@ -770,15 +803,16 @@ extern "C" hisq_status hisq_multishift_cg_solve(double *const *x, const double *
         R.gs = g_ms;
         R.c_ = m2 + shifts[0];
         R.nb = q.grad_buffer;
-        R.chunk = chunk_of(q);
+        solver_unit(q, &R.unit, &R.depth);
+        R.maxiter = q.maxiter;
         R.graph = q.use_graph != 0;
         R.multishift = nshift > 1;
         R.ru_est = q.ru_estimate != 0;
         R.nshift = nshift;
         R.B = &B;
         R.st = s_;
-        R.ds = E.ds;
-        init_ctrl(h, q, tol[0], 0.0, ms_fmt.spinor);
+        R.h = E.ds->host;
+        init_ctrl(R.h, q, tol[0], 0.0, ms_fmt.spinor);
         h->nshift = nshift;
         // where a shifted system's iterated residual stops tracking its true
         // residual: with FP32 arithmetic near the storage format's epsilon;
@@ -802,19 +836,21 @@ extern "C" hisq_status hisq_multishift_cg_solve(double *const *x, const double *
         // every shifted gradient vector starts as p_i = b (stored in the sloppy format)
         for (int i = 1; i < nshift; i++)
             HISQ_TRY_HIP(launch_spinor_convert(B.ps[i], ms_fmt.spinor, B.rs, ms_fmt.spinor, g.vh, s_));
-        HISQ_TRY(R.read_ctrl(h));
-        if (h->b2 == 0.0) {
+        HISQ_TRY(R.read_status());
+        if (R.last.b2 == 0.0) {
             for (int i = 0; i < nshift; i++) HISQ_TRY_HIP(hipMemsetAsync(x[i], 0, 48 * (size_t)g.vh, s_));
             HISQ_TRY(E.end());
             st->status = HISQ_OK;
             return HISQ_OK;
         }
         int ms_done = 0;
-        if (!h->done) {
+        if (!R.last.done) {
             // one shift: plain CG with reliable updates in the multi-shift triplet
-            status = R.iterate(h, &ms_done);
+            status = R.iterate(&ms_done);
             if (status == HISQ_ENOCONV) status = HISQ_OK;  // the refinement continues from here
         }
+        const hisq_status sr = R.read_ctrl();   // the shifts' stop iterations and the base's |r|^2
+        if (status == HISQ_OK) status = sr;
         fill_common_stats(st, R);
         for (int i = 1; i < nshift; i++) st->shift_iters[i] = h->shift_stop_k[i] ? h->shift_stop_k[i] : h->k;
         st->shift_iters[0] = h->k;
@@ -842,7 +878,7 @@ extern "C" hisq_status hisq_multishift_cg_solve(double *const *x, const double *
         Run R;
     };
     // refinement run of system i on stream sr with host control block hc
-    auto setup_run = [&](Run &R, CgBuffers &Bi, int i, hipStream_t sr) {
+    auto setup_run = [&](Run &R, CgBuffers &Bi, int i, hipStream_t sr, SolverHost *hc) {
         R.g = g;
         R.vh = g.vh;
         R.fmt = refine_fmt;
@@ -850,7 +886,8 @@ extern "C" hisq_status hisq_multishift_cg_solve(double *const *x, const double *
         R.gs = g_ref;
         R.c_ = m2 + shifts[i];
         R.nb = q.grad_buffer;
-        R.chunk = chunk_of(q);
+        solver_unit(q, &R.unit, &R.depth);
+        R.maxiter = q.maxiter;
         R.graph = q.use_graph != 0;
         R.multishift = false;
         R.ru_est = q.ru_estimate != 0;
@@ -859,17 +896,17 @@ extern "C" hisq_status hisq_multishift_cg_solve(double *const *x, const double *
         if (i > 0) Bi.x64 = B.xs[i];
         R.B = &Bi;
         R.st = sr;
-        R.ds = E.ds;
+        R.h = hc;
     };
-    auto refine_one = [&](int i, Refined &out, SolverCtrl *hc) {
+    auto refine_one = [&](int i, Refined &out, SolverHost *hc) {
         auto ts = std::chrono::steady_clock::now();
         CgBuffers Bi;
-        setup_run(out.R, Bi, i, s_);
+        setup_run(out.R, Bi, i, s_, hc);
         if (i == 0 && nshift > 1)
-            out.status = cg_core(out.R, q, tol[0], 2, B.pconv, rho_ms, hc, &out.r0);
+            out.status = cg_core(out.R, q, tol[0], 2, B.pconv, rho_ms, &out.r0);
         else
-            out.status = cg_core(out.R, q, tol[i], 1, nullptr, 0.0, hc, &out.r0);
-        out.r1 = hc->b2 > 0 ? std::sqrt(hc->r2_true / hc->b2) : 0.0;
+            out.status = cg_core(out.R, q, tol[i], 1, nullptr, 0.0, &out.r0);
+        out.r1 = out.R.last.b2 > 0 ? std::sqrt(out.R.last.r2_true / out.R.last.b2) : 0.0;
         hipError_t e = launch_spinor_unpack(x[i], Bi.x64, g.vh, SF_F64, s_);
         if (e == hipSuccess) e = hipStreamSynchronize(s_);
         if (e != hipSuccess && out.status == HISQ_OK)
@@ -891,7 +928,7 @@ extern "C" hisq_status hisq_multishift_cg_solve(double *const *x, const double *
     const bool overlap = L.batch && nshift > 1 && q.batch_refine == 2;
     const bool joint = L.batch && nshift > 1 && q.batch_refine == 3;
     // one batched block of the systems [i0, i0 + n): the base (i0 == 0) continues its gradient vector
-    auto run_block = [&](int i0, int n, hipStream_t sr, SolverCtrl *hc, BatchedJob &J) {
+    auto run_block = [&](int i0, int n, hipStream_t sr, SolverHost *hc, BatchedJob &J) {
         memset(&J, 0, sizeof(J));
         J.nrhs = n;
         for (int j = 0; j < n; j++) {
@@ -932,7 +969,7 @@ extern "C" hisq_status hisq_multishift_cg_solve(double *const *x, const double *
             HISQ_TRY_HIP(launch_spinor_unpack(x[i], B.xs[i], g.vh, SF_F64, s_));
         for (int i0 = 0; i0 < nshift && status == HISQ_OK; i0 += 16) {
             BatchedJob J;
-            run_block(i0, std::min(16, nshift - i0), s_, h, J);
+            run_block(i0, std::min(16, nshift - i0), s_, E.ds->host, J);
             status = batched_run(J);
             account_block(i0, J);
         }
@@ -941,7 +978,7 @@ extern "C" hisq_status hisq_multishift_cg_solve(double *const *x, const double *
         // the base, then the shifts: one after another, or together as a batch
         for (int i = 0; i < (L.batch ? 1 : nshift) && status == HISQ_OK; i++) {
             Refined o;
-            refine_one(i, o, h);
+            refine_one(i, o, E.ds->host);
             status = o.status;
             account(i, o);
             if (i == 0) {
@@ -953,7 +990,7 @@ extern "C" hisq_status hisq_multishift_cg_solve(double *const *x, const double *
             for (int i = 1; i < nshift; i++) HISQ_TRY_HIP(launch_spinor_unpack(x[i], B.xs[i], g.vh, SF_F64, s_));
             for (int i0 = 1; i0 < nshift && status == HISQ_OK; i0 += 16) {
                 BatchedJob J;
-                run_block(i0, std::min(16, nshift - i0), s_, h, J);
+                run_block(i0, std::min(16, nshift - i0), s_, E.ds->host, J);
                 status = batched_run(J);
                 account_block(i0, J);
             }
@@ -965,7 +1002,7 @@ extern "C" hisq_status hisq_multishift_cg_solve(double *const *x, const double *
         {
             Run Rp;
             CgBuffers Bp;
-            setup_run(Rp, Bp, 0, s_);
+            setup_run(Rp, Bp, 0, s_, E.ds->host);
             Rp.setup_plans();
         }
         HISQ_TRY_HIP(hipEventRecord(E.ds->ev2, s_));
@@ -976,10 +1013,10 @@ extern "C" hisq_status hisq_multishift_cg_solve(double *const *x, const double *
         struct Start {
             std::thread *w;
             std::function<void()> fn;
-        } start{&worker, [&] { refine_one(0, base, h); }};
+        } start{&worker, [&] { refine_one(0, base, E.ds->host); }};
         for (int i0 = 1; i0 < nshift && status == HISQ_OK; i0 += 16) {
             BatchedJob J;
-            run_block(i0, std::min(16, nshift - i0), s2, E.ds->host_ctrl2, J);
+            run_block(i0, std::min(16, nshift - i0), s2, E.ds->host2, J);
             if (!worker.joinable()) {
                 // the base starts once the block's launch shapes are planned
                 J.after_setup = [](void *c) {
@@ -998,7 +1035,7 @@ extern "C" hisq_status hisq_multishift_cg_solve(double *const *x, const double *
         if (worker.joinable()) {
             worker.join();
         } else {
-            refine_one(0, base, h);   // the batched block stopped before it started the base
+            refine_one(0, base, E.ds->host);   // the batched block stopped before it started the base
         }
         account(0, base);
         st->phase_seconds[1] = base.seconds;

@@ -52,3 +52,40 @@ def test_partials_on_both_sides_of_the_line(dims, nshift):
 @pytest.mark.parametrize("nshift", [0, 12])
 def test_rings_and_triggers(opts, nshift):
     solve_and_check((6, 10, 12, 12), "int30", nshift, **opts)
+
+
+def small_problem():
+    hisq = need_gpu()
+    dims = (6, 8, 10, 12)
+    fat, lng = inputs.make_links(dims, "near_unit", device="cuda")
+    b = inputs.gaussian_spinor(dims[0] * dims[1] * dims[2] * dims[3] // 2, inputs.RHS_SEED, device="cuda", nrhs=3)
+    return hisq, b, hisq.pack_gauge(fat, lng, dims, hisq.GAUGE_F64), hisq.pack_gauge(fat, lng, dims, hisq.GAUGE_FIX16)
+
+
+@pytest.mark.parametrize("batched", [False, True])
+def test_units_do_not_change_the_solve(batched):
+    """units in flight or not, replayed or enqueued directly: the same bits"""
+    hisq, b, g64, gs = small_problem()
+    ref = None
+    for opts in (dict(), dict(poll_every=8), dict(poll_every=100), dict(poll_every=32, use_graph=0),
+                 dict(poll_every=8, use_graph=0)):
+        if batched:
+            x, st = hisq.cg_solve_batched(b, g64, gs, 0.05, tol=TOL, sloppy="int20", **opts)
+        else:
+            x, st = hisq.cg_solve(b[0], g64, gs, 0.05, tol=TOL, sloppy="int20", **opts)
+        got = (x, st["iters"], st["reliable_updates"], st["true_resid"])
+        if ref is None:
+            ref = got
+        assert torch.equal(x, ref[0]) and got[1:] == ref[1:], (opts, got[1:], ref[1:])
+
+
+@pytest.mark.parametrize("maxiter", [1, 7, 8, 9, 16, 33])
+@pytest.mark.parametrize("batched", [False, True])
+def test_iteration_cap_at_the_edges_of_a_unit(batched, maxiter):
+    hisq, b, g64, gs = small_problem()
+    if batched:
+        x, st = hisq.cg_solve_batched(b, g64, gs, 0.01, tol=1e-12, sloppy="int20", maxiter=maxiter)
+    else:
+        x, st = hisq.cg_solve(b[0], g64, gs, 0.01, tol=1e-12, sloppy="int20", maxiter=maxiter)
+    assert st["status"] == "HISQ_ENOCONV" and st["iters"] == maxiter
+    assert st["true_resid"] > 1e-12 and bool(torch.isfinite(torch.view_as_real(x)).all())
