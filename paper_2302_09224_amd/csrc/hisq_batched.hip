@@ -27,133 +27,80 @@ namespace hisq {
 
 namespace {
 
-// finalize kernels: 16 waves per block; each thread loads its strided share
-// of the block partials four entries at a time (all four in flight) and adds
-// them in index order
+// scalar kernels: one block of 16 waves per system; each thread loads its
+// strided share of the system's block partials four entries at a time (all four
+// in flight) and adds them in index order
 constexpr int FIN_THREADS = 1024;
 
-// sum over blocks b of partial[(b*nrhs + j)*NV + k], k < NV; valid in thread 0
-template <int NV>
-__device__ __forceinline__ void bsum(const double *partial, int nb, int nrhs, int j, double (&v)[NV], double *lds) {
-#pragma unroll
-    for (int k = 0; k < NV; k++) v[k] = 0.0;
-    const int step = blockDim.x;
-    int b = threadIdx.x;
-    for (; b + 3 * step < nb; b += 4 * step) {
-        double q[4][NV];
-#pragma unroll
-        for (int u = 0; u < 4; u++)
-#pragma unroll
-            for (int k = 0; k < NV; k++) q[u][k] = partial[((size_t)(b + u * step) * nrhs + j) * NV + k];
-#pragma unroll
-        for (int u = 0; u < 4; u++)
-#pragma unroll
-            for (int k = 0; k < NV; k++) v[k] += q[u][k];
-    }
-    for (; b < nb; b += step) {
-#pragma unroll
-        for (int k = 0; k < NV; k++) v[k] += partial[((size_t)b * nrhs + j) * NV + k];
-    }
-    block_sum<NV>(v, lds);
-    __syncthreads();
+// the last block of a scalar kernel to arrive combines what the others decided
+// (each wrote its own system's fields and passes here once; nobody waits)
+__device__ __forceinline__ bool last_block(SolverCtrl *c, int nblocks) {
+    const unsigned t = __hip_atomic_fetch_add(&c->ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    if (t != (unsigned)nblocks - 1u) return false;
+    c->ticket = 0;
+    return true;
 }
 
-// Dslash partials: right-hand side j owns column partial[j*pstride + b], b < nb[j]
-struct NbList {
-    int nb[16];
-    size_t pstride;
-};
-
-__device__ __forceinline__ void csum(const double *col, int nb, double (&v)[1], double *lds) {
-    v[0] = 0.0;
-    const int step = blockDim.x;
-    int b = threadIdx.x;
-    for (; b + 3 * step < nb; b += 4 * step) {
-        const double q0 = col[b], q1 = col[b + step], q2 = col[b + 2 * step], q3 = col[b + 3 * step];
-        v[0] += q0;
-        v[0] += q1;
-        v[0] += q2;
-        v[0] += q3;
-    }
-    for (; b < nb; b += step) v[0] += col[b];
-    block_sum<1>(v, lds);
-    __syncthreads();
-}
-
-// one block per right-hand side j (launched with nrhs blocks): the columns are
-// independent, and a Dslash over rg lanes per site leaves rg times more partials
-// per column than sites per block; each column is summed in a fixed order
-__global__ void k_bfin_alpha(SolverCtrl *c, const double *partial, NbList nl, int nrhs, int jb, Guard gd) {
-    __shared__ double lds[FIN_THREADS / 64];
-    const int j = blockIdx.x;
-    if (j >= nrhs || !gd.pass()) return;
-    double v[1];
-    csum(partial + (size_t)j * nl.pstride, nl.nb[j], v, lds);
+// sums of block partials too many for every block of the consumer to add up
+template <int NV> __global__ void k_bfin_sum(SolverCtrl *c, BSums in, BCols cols, Guard gd) {
+    __shared__ double lds[NV * (FIN_THREADS / 64)];
+    if (!gd.pass()) return;
+    const int j = (int)((cols.map >> (4 * blockIdx.x)) & 15ull);
+    double v[NV];
+    all_sums<NV>(in.p + j * in.stride, in.n, v, lds);
     if (threadIdx.x) return;
-    const double pi = v[0];
-    c->bpi[j] = pi;
-    if (!c->bactive[j]) {
-        c->balpha[j] = 0.0;
-        c->balpha_buf[jb][j] = 0.0;
-        return;
-    }
-    if (!(pi > 0.0) || !__builtin_isfinite(pi)) {
-        // every block that finds a breakdown writes the same stop record
-        c->stop = gd.j - 1;
-        c->reason = STOP_BREAKDOWN;
-        c->breakdown = 1;
-        c->balpha[j] = 0.0;
-        c->balpha_buf[jb][j] = 0.0;
-        return;
-    }
-    const double a = c->brho[j] / pi;
-    c->balpha[j] = a;
-    c->balpha_buf[jb][j] = a;
+#pragma unroll
+    for (int k = 0; k < NV; k++) c->bred[j][k] = v[k];
 }
 
-__global__ void k_bfin_beta(SolverCtrl *c, const double *partial, int nb, int nrhs, Guard gd) {
+// beta and the decisions of one iteration: block b for its system, then the
+// block that arrives last for all of them
+enum { BF_RU = 1, BF_CONV = 2, BF_BAD = 4 };
+__global__ void k_bfin_beta(SolverCtrl *c, BSums rr, int nrhs, BCols cols, Guard gd) {
     __shared__ double lds[2 * (FIN_THREADS / 64)];
     if (!gd.pass()) return;
-    int reason = STOP_NONE;
-    for (int j = 0; j < nrhs; j++) {
-        double v[2];
-        bsum<2>(partial, nb, nrhs, j, v, lds);
-        if (threadIdx.x || !c->bactive[j]) continue;
-        const double rn = v[0], g = v[1];
-        c->bk[j] += 1;
-        if (!__builtin_isfinite(rn) || !__builtin_isfinite(g)) {
-            reason = STOP_BREAKDOWN;
-            c->breakdown = 1;
-            continue;
-        }
-        const double rho = c->brho[j];
-        const double beta = c->pr ? (rn - g) / rho : rn / rho;
-        c->bbeta[j] = beta;
-        c->bpa_re[j] = 1.0;
-        c->bpa_im[j] = 0.0;
-        c->bpb[j] = beta;
-        c->brmax2[j] = fmax(c->brmax2[j], rn);
-        const bool ru = c->delta2 > 0.0 && rn < c->delta2 * c->brmax2[j];
-        const bool conv = rn <= c->btol2[j] * c->bb2[j];
-        if (ru) reason = reason ? reason : STOP_RU;
-        if (conv) reason = reason ? reason : STOP_CONV;
-        if (ru || conv) c->bru[j] = 1;
-        c->brho_prev[j] = rho;
-        c->brho[j] = rn;
-    }
+    const int j = (int)((cols.map >> (4 * blockIdx.x)) & 15ull);
+    double v[2] = {0.0, 0.0};
+    if (c->bactive[j]) all_sums<2>(rr.p + j * rr.stride, rr.n, v, lds);
     if (threadIdx.x) return;
+    int flag = 0;
+    if (c->bactive[j]) {
+        const double rn = v[0], g = v[1], pi = c->bpi[j];
+        c->bk[j] += 1;
+        if (!(pi > 0.0) || !__builtin_isfinite(pi) || !__builtin_isfinite(rn) || !__builtin_isfinite(g)) {
+            flag = BF_BAD;
+        } else {
+            const double rho = c->brho[j];
+            const double beta = c->pr ? (rn - g) / rho : rn / rho;
+            const double rmax2 = fmax(c->brmax2[j], rn);
+            c->bbeta[j] = beta;
+            c->bpb[j] = beta;
+            c->brmax2[j] = rmax2;
+            if (c->delta2 > 0.0 && rn < c->delta2 * rmax2) flag |= BF_RU;
+            if (rn <= c->btol2[j] * c->bb2[j]) flag |= BF_CONV;
+            if (flag) c->bru[j] = 1;
+            c->brho_prev[j] = rho;
+            c->brho[j] = rn;
+        }
+    }
+    c->bflag[j] = flag;
+    if (!last_block(c, gridDim.x)) return;
+    int all = 0;
+    for (int i = 0; i < cols.n; i++) all |= c->bflag[(int)((cols.map >> (4 * i)) & 15ull)];
+    int reason = (all & BF_BAD) ? STOP_BREAKDOWN : (all & BF_RU) ? STOP_RU : (all & BF_CONV) ? STOP_CONV : STOP_NONE;
+    if (reason == STOP_BREAKDOWN) c->breakdown = 1;
     const int k = c->k + 1;
     c->k = k;
     if (reason == STOP_NONE && k >= c->maxiter) {
         reason = STOP_MAXITER;
-        for (int j = 0; j < nrhs; j++) c->bru[j] = c->bactive[j];   // report every true residual
+        for (int i = 0; i < nrhs; i++) c->bru[i] = c->bactive[i];   // report every true residual
     }
     if (reason == STOP_RU || reason == STOP_CONV) {
         // systems whose residual norm is within a factor of about 3 (10 in its square) of
         // their own trigger join this reliable update
         // (one FP64 application serves them all instead of one each shortly after)
-        for (int j = 0; j < nrhs; j++)
-            if (c->bactive[j] && c->delta2 > 0.0 && c->brho[j] < 10.0 * c->delta2 * c->brmax2[j]) c->bru[j] = 1;
+        for (int i = 0; i < nrhs; i++)
+            if (c->bactive[i] && c->delta2 > 0.0 && c->brho[i] < 10.0 * c->delta2 * c->brmax2[i]) c->bru[i] = 1;
     }
     if (reason != STOP_NONE) {
         c->reason = reason;
@@ -161,61 +108,42 @@ __global__ void k_bfin_beta(SolverCtrl *c, const double *partial, int nb, int nr
     }
 }
 
-__global__ void k_bfin_ru_check(SolverCtrl *c, const double *partial, NbList nl, int nrhs) {
+// |b_j - A_j x_j|^2 of the systems taking part: block j for its system, the
+// last one for the batch
+__global__ void k_bfin_ru_check(SolverCtrl *c, BSums in, int nrhs) {
     __shared__ double lds[FIN_THREADS / 64];
-    int all = 1;
-    for (int j = 0; j < nrhs; j++) {
-        double v[1];
-        csum(partial + (size_t)j * nl.pstride, nl.nb[j], v, lds);
-        if (threadIdx.x) continue;
-        if (c->bru[j] && c->bactive[j]) {
-            const double r2 = v[0];
-            c->br2_true[j] = r2;
-            if (!__builtin_isfinite(r2)) c->breakdown = 1;
-            if (r2 <= c->btol2[j] * c->bb2[j]) {
-                c->bactive[j] = 0;
-                c->bdone[j] = 1;
-            }
-        }
-        all &= !c->bactive[j];
-    }
+    const int j = blockIdx.x;
+    const bool part = c->bru[j] && c->bactive[j];
+    double v[1] = {0.0};
+    if (part) all_sums<1>(in.p + j * in.stride, in.n, v, lds);
     if (threadIdx.x) return;
+    int flag = 0;
+    if (part) {
+        const double r2 = v[0];
+        c->br2_true[j] = r2;
+        if (!__builtin_isfinite(r2)) flag = BF_BAD;
+        if (r2 <= c->btol2[j] * c->bb2[j]) {
+            c->bactive[j] = 0;
+            c->bdone[j] = 1;
+        }
+    }
+    c->bflag[j] = flag;
+    if (!last_block(c, gridDim.x)) return;
+    int all = 1, bad = 0;
+    for (int i = 0; i < nrhs; i++) {
+        all &= !c->bactive[i];
+        bad |= c->bflag[i];
+    }
+    if (bad) c->breakdown = 1;
     c->done = all;
     c->stop = (all || c->breakdown) ? -1 : STOP_NEVER;
 }
 
-__global__ void k_bfin_ru_finish(SolverCtrl *c, const double *partial, int nb, int nrhs, int mode, Guard gd) {
-    __shared__ double lds[4 * (FIN_THREADS / 64)];
-    if (!gd.pass()) return;
-    for (int j = 0; j < nrhs; j++) {
-        double v[4];
-        bsum<4>(partial, nb, nrhs, j, v, lds);
-        if (threadIdx.x || !c->bactive[j] || !c->bru[j]) continue;   // the others keep their CG step
-        const double rho = v[0];
-        double beta = 0.0, cr = 0.0, ci = 0.0;
-        // the first reliable update restarts every system, except one that
-        // continues a given gradient vector (re-projected, Fletcher-Reeves beta:
-        // there is no previous iterated residual to form Polak-Ribiere's)
-        if (mode != 1 || c->bwarm[j]) {
-            if (c->reproject && rho > 0.0) {
-                cr = v[1] / rho;
-                ci = v[2] / rho;
-            }
-            beta = c->pr ? (rho - v[3]) / c->brho_prev[j] : rho / c->brho_prev[j];
-        }
-        c->bpa_re[j] = 1.0 - beta * cr;
-        c->bpa_im[j] = -beta * ci;
-        c->bpb[j] = beta;
-        c->bbeta[j] = beta;
-        c->brho[j] = rho;
-        c->brmax2[j] = rho;
-        c->bwarm[j] = 0;
-    }
-    if (threadIdx.x) return;
-    for (int j = 0; j < nrhs; j++) c->bru[j] = 0;
-    c->reason = STOP_NONE;
-    c->stop = STOP_NEVER;
-}
+// a Dslash's partials: column j at j * pstride, nb entries
+struct NbList {
+    int nb;
+    size_t pstride;
+};
 
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
@@ -287,6 +215,7 @@ struct BRun {
         unsigned cvalid = 0, cvalid_red = 0;
         unsigned long long cmap = 0, cmap_red = 0;
         NbList nl{};
+        BCols cols{};                 // the same columns, dense
     };
     Mapped ms_{}, m64_{};
 
@@ -313,8 +242,11 @@ struct BRun {
             m.cmap_red |= (unsigned long long)cols[i] << (4 * kr);
             m.cvalid_red |= 1u << kr;
         }
-        m.nl.pstride = dslash_max_blocks(g);
-        for (int j = 0; j < 16; j++) m.nl.nb[j] = dslash_tile_blocks(g, tr);
+        m.nl.nb = dslash_tile_blocks(g, tr);
+        // few partials: dense columns, beside which the residual update's fit (rpart)
+        m.nl.pstride = m.nl.nb <= SUMS_DIRECT ? (size_t)SUMS_DIRECT : dslash_max_blocks(g);
+        m.cols.n = n;
+        for (int i = 0; i < n; i++) m.cols.map |= (unsigned long long)cols[i] << (4 * i);
         return m;
     }
 
@@ -398,18 +330,38 @@ struct BRun {
         Bk.pstride = ms_.nl.pstride;
         Bk.guard = gns;
         HISQ_TRY_HIP(launch_dslash(Bk, fmt, ms_.plan, st, nullptr));
-        hipLaunchKernelGGL(k_bfin_alpha, dim3(nrhs), dim3(FIN_THREADS), 0, st, c, B->partial, ms_.nl, nrhs, jb, gns);
+        BSums pap, rr;
+        HISQ_TRY(enq_sums<1>(BSums{B->partial, ms_.nl.nb, ms_.nl.pstride}, ms_.cols, gns, &pap));
+        HISQ_TRY_HIP(launch_bcg_axpy(B->rs, B->aps, c, pap, vh, fs, ms_.cols, fmt.spinor, fmt.compute, rpart(), jb, gns, st));
+        const int nbv = bcg_blocks(vh, ms_.cols.n);
+        rr = BSums{rpart(), nbv, (size_t)2 * nbv};
+        hipLaunchKernelGGL(k_bfin_beta, dim3(ms_.cols.n), dim3(FIN_THREADS), 0, st, c, rr, nrhs, ms_.cols, gns);
         HISQ_TRY_HIP(hipGetLastError());
-        HISQ_TRY_HIP(launch_bcg_axpy(B->rs, B->aps, c, vh, fs, nrhs, fmt.spinor, fmt.compute, B->partial, gns, st));
-        hipLaunchKernelGGL(k_bfin_beta, dim3(1), dim3(FIN_THREADS), 0, st, c, B->partial, blas_blocks(vh), nrhs, gns);
-        HISQ_TRY_HIP(hipGetLastError());
-        if (jb == nb - 1) {
-            SpinorList pl;
-            for (int i = 0; i < HISQ_MAX_SHIFTS; i++) pl.p[i] = i < nb ? B->p[i] : nullptr;
-            HISQ_TRY_HIP(launch_bflush_x(B->x64, fs64, pl, nb, c, vh, fs, nrhs, fmt.spinor, fmt.compute, gsn, st));
-        }
-        HISQ_TRY_HIP(launch_bcg_pupdate(B->p[jn], B->rs, B->p[jb], c, vh, fs, nrhs, fmt.spinor, fmt.compute, gsn, st));
+        SpinorList pl;
+        for (int i = 0; i < HISQ_MAX_SHIFTS; i++) pl.p[i] = i < nb ? B->p[i] : nullptr;
+        HISQ_TRY_HIP(launch_bcg_pupdate(B->p[jn], B->rs, B->p[jb], c, B->x64, fs64, pl, jb == nb - 1 ? nb : 0, vh, fs,
+                                        ms_.cols, fmt.spinor, fmt.compute, gsn, st));
         return HISQ_OK;
+    }
+    // partials of the residual update, apart from the dense Dslash columns that its blocks read
+    double *rpart() const { return B->partial + (size_t)SUMS_DIRECT * nrhs; }
+
+    // block partials for the next kernel: as they are when few, else added up in a launch
+    template <int NV>
+    hisq_status enq_sums(const BSums &in, const BCols &cols, Guard gd, BSums *out) {
+        *out = in;
+        if (in.n * NV <= SUMS_DIRECT) return HISQ_OK;
+        hipLaunchKernelGGL((k_bfin_sum<NV>), dim3(cols.n), dim3(FIN_THREADS), 0, st, B->ctrl, in, cols, gd);
+        HISQ_TRY_HIP(hipGetLastError());
+        *out = BSums{&B->ctrl->bred[0][0], 1, 4};
+        return HISQ_OK;
+    }
+
+    // every system (those that have stopped return at once)
+    BCols all_cols() const {
+        BCols k{0, nrhs};
+        for (int j = 0; j < nrhs; j++) k.map |= (unsigned long long)j << (4 * j);
+        return k;
     }
 
     // ru_mask: the systems taking part (the FP64 launches cover those only)
@@ -417,11 +369,12 @@ struct BRun {
         SolverCtrl *c = B->ctrl;
         const hisq_fmt f64 = {HISQ_GAUGE_F64, HISQ_SPINOR_F64, 64};
         const int nru = __builtin_popcount(ru_mask);
+        const BCols cols = ms_.cols.n ? ms_.cols : all_cols();   // before the first unit: every system
         if (ru_mask != m64_.mask) m64_ = map_columns(f64, g64, B->t64, B->x64, ru_mask);
         if (count > 0) {
             SpinorList pl;
             for (int i = 0; i < HISQ_MAX_SHIFTS; i++) pl.p[i] = i < nb ? B->p[i] : nullptr;
-            HISQ_TRY_HIP(launch_bflush_x(B->x64, fs64, pl, count, c, vh, fs, nrhs, fmt.spinor, fmt.compute,
+            HISQ_TRY_HIP(launch_bflush_x(B->x64, fs64, pl, count, c, vh, fs, cols, fmt.spinor, fmt.compute,
                                          Guard{nullptr, 0, 0}, st));
         }
         // true residuals of the systems taking part (c->bru) only
@@ -440,17 +393,18 @@ struct BRun {
         Bk.partial = B->partial;
         Bk.pstride = m64_.nl.pstride;
         HISQ_TRY_HIP(launch_dslash(Bk, f64, m64_.plan, st, nullptr));
-        hipLaunchKernelGGL(k_bfin_ru_check, dim3(1), dim3(FIN_THREADS), 0, st, c, B->partial, m64_.nl, nrhs);
+        hipLaunchKernelGGL(k_bfin_ru_check, dim3(nrhs), dim3(FIN_THREADS), 0, st, c,
+                           BSums{B->partial, m64_.nl.nb, m64_.nl.pstride}, nrhs);
         HISQ_TRY_HIP(hipGetLastError());
         d64 += 2;
         alg += 2.0 * vh * (dslash_link_bytes(g64) + nru * 2.0 * 48) + 2.0 * vh * nru * 48;
         const Guard g0{&c->stop, 0, 0};
-        HISQ_TRY_HIP(launch_bru_convert(B->rs, B->r64, fs64, p_src, mode == 0 ? B->aps : nullptr,
-                                        c, vh, fs, nrhs, fmt.spinor, fmt.compute, B->partial, g0, st));
-        hipLaunchKernelGGL(k_bfin_ru_finish, dim3(1), dim3(FIN_THREADS), 0, st, c, B->partial, blas_blocks(vh), nrhs,
-                           mode, g0);
-        HISQ_TRY_HIP(hipGetLastError());
-        HISQ_TRY_HIP(launch_bcg_pupdate(B->p[0], B->rs, p_src ? p_src : B->rs, c, vh, fs, nrhs, fmt.spinor,
+        HISQ_TRY_HIP(launch_bru_convert(B->rs, B->r64, fs64, p_src, mode == 0 ? B->aps : nullptr, c, vh, fs, cols,
+                                        fmt.spinor, fmt.compute, B->partial, g0, st));
+        const int nbv = bcg_blocks(vh, cols.n);
+        BSums ru;
+        HISQ_TRY(enq_sums<4>(BSums{B->partial, nbv, (size_t)4 * nbv}, cols, g0, &ru));
+        HISQ_TRY_HIP(launch_bru_pupdate(B->p[0], B->rs, p_src ? p_src : B->rs, c, ru, mode, vh, fs, cols, fmt.spinor,
                                         fmt.compute, g0, st));
         return HISQ_OK;
     }

@@ -894,140 +894,228 @@ __global__ void __launch_bounds__(BLAS_BLOCK) k_shift_replay(SpinorList x64, Spi
 constexpr int REPLAY_GROUP = 4;
 
 // ---------------------------------------------------------------------------
-// batched (nrhs independent systems) vector updates
+// batched (independent systems) vector updates: block row blockIdx.y works on
+// one system
 // ---------------------------------------------------------------------------
 
+__device__ __forceinline__ int bcol(const BCols &cols) { return (int)((cols.map >> (4 * blockIdx.y)) & 15ull); }
+
+// r_j -= alpha_j A p_j with alpha_j = rho_j / <p_j,Ap_j>, as k_cg_axpy
 template <int SF, class R>
-__global__ void k_bcg_axpy(char *r, const char *ap, const SolverCtrl *ctrl, size_t n, size_t fs, int nrhs,
-                           double *partial, Guard gd) {
-    __shared__ double lds[32];
+__global__ void __launch_bounds__(BLAS_BLOCK) k_bcg_axpy(char *r, const char *ap, SolverCtrl *ctl, BSums pap, size_t n,
+                                                         size_t fs, BCols cols, double *partial, int jb, Guard gd) {
+    __shared__ double lds[2 * (BLAS_BLOCK / 64)];
     if (!gd.pass()) return;
-    for (int j = 0; j < nrhs; j++) {
-        double acc[2] = {0.0, 0.0};
-        if (ctrl->bactive[j]) {
-            const R a = (R)ctrl->balpha[j];
-            char *rj = r + j * fs;
-            const char *aj = ap + j * fs;
-            for (size_t s = gtid(); s < n; s += gstride()) {
-                CVec<R> ro = SpinorIO<SF, R>::load(rj, n, s);
-                CVec<R> av = SpinorIO<SF, R>::load(aj, n, s);
-                CVec<R> rn;
+    const int j = bcol(cols);
+    if (!ctl->bactive[j]) return;
+    double pv[1];
+    all_sums<1>(pap.p + j * pap.stride, pap.n, pv, lds);
+    const double pi = pv[0];
+    const bool bad = !(pi > 0.0) || !__builtin_isfinite(pi);
+    const double alpha = bad ? 0.0 : ctl->brho[j] / pi;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        ctl->bpi[j] = pi;
+        ctl->balpha[j] = alpha;
+        ctl->balpha_buf[jb][j] = alpha;
+        ctl->bru[j] = ctl->bwarm[j] = 0;   // the last reliable update is over
+    }
+    const R a = (R)alpha;
+    r += j * fs;
+    ap += j * fs;
+    double acc[2] = {0.0, 0.0};
+    for (size_t s = gtid(); s < n; s += gstride()) {
+        CVec<R> ro = SpinorIO<SF, R>::load(r, n, s);
+        CVec<R> av = SpinorIO<SF, R>::load(ap, n, s);
+        CVec<R> rn;
 #pragma unroll
-                for (int c = 0; c < 3; c++) {
-                    rn.re[c] = fma(-a, av.re[c], ro.re[c]);
-                    rn.im[c] = fma(-a, av.im[c], ro.im[c]);
-                }
-                CVec<R> o = SpinorIO<SF, R>::store(rj, n, s, rn);
+        for (int c = 0; c < 3; c++) {
+            rn.re[c] = fma(-a, av.re[c], ro.re[c]);
+            rn.im[c] = fma(-a, av.im[c], ro.im[c]);
+        }
+        CVec<R> o = SpinorIO<SF, R>::store(r, n, s, rn);
 #pragma unroll
-                for (int c = 0; c < 3; c++) {
-                    acc[0] += (double)o.re[c] * (double)o.re[c] + (double)o.im[c] * (double)o.im[c];
-                    acc[1] += (double)o.re[c] * (double)ro.re[c] + (double)o.im[c] * (double)ro.im[c];
-                }
-            }
+        for (int c = 0; c < 3; c++) {
+            acc[0] += (double)o.re[c] * (double)o.re[c] + (double)o.im[c] * (double)o.im[c];
+            acc[1] += (double)o.re[c] * (double)ro.re[c] + (double)o.im[c] * (double)ro.im[c];
         }
-        block_sum<2>(acc, lds);
-        if (threadIdx.x == 0) {
-            partial[((size_t)blockIdx.x * nrhs + j) * 2] = acc[0];
-            partial[((size_t)blockIdx.x * nrhs + j) * 2 + 1] = acc[1];
-        }
-        __syncthreads();
+    }
+    block_sum<2>(acc, lds);
+    if (threadIdx.x == 0) {
+        double *p = partial + 2 * ((size_t)j * gridDim.x + blockIdx.x);
+        p[0] = acc[0];
+        p[1] = acc[1];
     }
 }
 
+// x += sum_i a_i ring_i over the ring's first `count` vectors; returns the last
+// of them (loads grouped as in k_flush_x; a zero coefficient leaves x as it is)
 template <int SF, class R>
-__global__ void k_bcg_pupdate(char *pd, const char *r, const char *ps, const SolverCtrl *ctrl, size_t n, size_t fs,
-                              int nrhs, Guard gd) {
-    if (!gd.pass()) return;
-    for (int j = 0; j < nrhs; j++) {
-        if (!ctrl->bactive[j]) continue;
-        const R ar = (R)ctrl->bpa_re[j], ai = (R)ctrl->bpa_im[j], b = (R)ctrl->bpb[j];
-        for (size_t s = gtid(); s < n; s += gstride()) {
-            CVec<R> rv = SpinorIO<SF, R>::load(r + j * fs, n, s);
-            CVec<R> pv = SpinorIO<SF, R>::load(ps + j * fs, n, s);
-            CVec<R> o;
+__device__ __forceinline__ CVec<R> bflush_site(CVec<double> &x, const SpinorList &ring, size_t off, int count,
+                                               const SolverCtrl *ctl, int j, size_t n, size_t s) {
+    constexpr int LOAD_GROUP = load_group<SF>();
+    CVec<R> last;
+    for (int i0 = 0; i0 < count; i0 += LOAD_GROUP) {
+        CVec<R> gv[LOAD_GROUP];
+        double a[LOAD_GROUP];
+#pragma unroll
+        for (int k = 0; k < LOAD_GROUP; k++) {
+            const int i = min(i0 + k, count - 1);
+            gv[k] = SpinorIO<SF, R>::load(ring.p[i] + off, n, s);
+            a[k] = i0 + k < count ? ctl->balpha_buf[i][j] : 0.0;
+        }
+#pragma unroll
+        for (int k = 0; k < LOAD_GROUP; k++) {
 #pragma unroll
             for (int c = 0; c < 3; c++) {
-                o.re[c] = fma(ar, rv.re[c], fma(-ai, rv.im[c], b * pv.re[c]));
-                o.im[c] = fma(ar, rv.im[c], fma(ai, rv.re[c], b * pv.im[c]));
+                x.re[c] = fma(a[k], (double)gv[k].re[c], x.re[c]);
+                x.im[c] = fma(a[k], (double)gv[k].im[c], x.im[c]);
             }
-            SpinorIO<SF, R>::store(pd + j * fs, n, s, o);
         }
+        last = gv[LOAD_GROUP - 1];
     }
+    return last;
 }
 
-template <int SF, class R>
-__global__ void k_bflush_x(char *x64, size_t fs64, SpinorList p, int count, const SolverCtrl *ctrl, size_t n, size_t fs,
-                           int nrhs, Guard gd) {
-    if (!gd.pass()) return;
-    for (int j = 0; j < nrhs; j++) {
-        // a stopped system's buffered gradients were flushed before it stopped
-        if (!ctrl->bactive[j]) continue;
-        char *xj = x64 + j * fs64;
-        for (size_t s = gtid(); s < n; s += gstride()) {
-            CVec<double> x = SpinorIO<SF_F64, double>::load(xj, n, s);
-            for (int i = 0; i < count; i++) {
-                const double a = ctrl->balpha_buf[i][j];
-                if (a == 0.0) continue;
-                CVec<R> pv = SpinorIO<SF, R>::load(p.p[i] + j * fs, n, s);
+// pa and pb of the update p = pa r + pb p
+template <class R> struct PCoef {
+    R ar, ai, b;
+};
+template <class R>
+__device__ __forceinline__ CVec<R> pstep(const PCoef<R> &k, const CVec<R> &rv, const CVec<R> &pv) {
+    CVec<R> o;
 #pragma unroll
-                for (int c = 0; c < 3; c++) {
-                    x.re[c] = fma(a, (double)pv.re[c], x.re[c]);
-                    x.im[c] = fma(a, (double)pv.im[c], x.im[c]);
-                }
-            }
-            SpinorIO<SF_F64, double>::store(xj, n, s, x);
+    for (int c = 0; c < 3; c++) {
+        o.re[c] = fma(k.ar, rv.re[c], fma(-k.ai, rv.im[c], k.b * pv.re[c]));
+        o.im[c] = fma(k.ar, rv.im[c], fma(k.ai, rv.re[c], k.b * pv.im[c]));
+    }
+    return o;
+}
+
+template <int SF, class R, bool FLUSH>
+__global__ void __launch_bounds__(BLAS_BLOCK) k_bcg_pupdate(char *pd, const char *r, const char *ps,
+                                                            const SolverCtrl *ctl, char *x64, size_t fs64,
+                                                            SpinorList ring, int count, size_t n, size_t fs, BCols cols,
+                                                            Guard gd) {
+    if (!gd.pass()) return;
+    const int j = bcol(cols);
+    if (!ctl->bactive[j]) return;
+    const PCoef<R> k{R(1), R(0), (R)ctl->bpb[j]};
+    const size_t off = j * fs;
+    for (size_t s = gtid(); s < n; s += gstride()) {
+        const CVec<R> rv = SpinorIO<SF, R>::load(r + off, n, s);
+        CVec<R> pv;
+        if constexpr (FLUSH) {
+            CVec<double> x = SpinorIO<SF_F64, double>::load(x64 + j * fs64, n, s);
+            pv = bflush_site<SF, R>(x, ring, off, count, ctl, j, n, s);
+            SpinorIO<SF_F64, double>::store(x64 + j * fs64, n, s, x);
+        } else {
+            pv = SpinorIO<SF, R>::load(ps + off, n, s);
         }
+        (void)SpinorIO<SF, R>::store(pd + off, n, s, pstep<R>(k, rv, pv));
+    }
+}
+
+// the gradient update of a reliable update, the scalars formed from the sums of
+// k_bru_convert in every block.  mode 1 (the first one) restarts every system
+// but one that continues a given gradient vector (re-projected, Fletcher-Reeves
+// beta: there is no previous iterated residual to form Polak-Ribiere's).
+template <int SF, class R>
+__global__ void __launch_bounds__(BLAS_BLOCK) k_bru_pupdate(char *pd, const char *r, const char *ps, SolverCtrl *ctl,
+                                                            BSums ru, int mode, size_t n, size_t fs, BCols cols,
+                                                            Guard gd) {
+    __shared__ double lds[4 * (BLAS_BLOCK / 64)];
+    if (!gd.pass()) return;
+    const int j = bcol(cols);
+    if (!ctl->bactive[j]) return;
+    PCoef<R> k{R(1), R(0), (R)ctl->bpb[j]};   // the ordinary step
+    if (ctl->bru[j]) {
+        double v[4];
+        all_sums<4>(ru.p + j * ru.stride, ru.n, v, lds);
+        const double rho = v[0], rho_prev = ctl->brho_prev[j];
+        double beta = 0.0, cr = 0.0, ci = 0.0;
+        if (mode != 1 || ctl->bwarm[j]) {
+            if (ctl->reproject && rho > 0.0) {
+                cr = v[1] / rho;
+                ci = v[2] / rho;
+            }
+            beta = ctl->pr ? (rho - v[3]) / rho_prev : rho / rho_prev;
+        }
+        k = PCoef<R>{(R)(1.0 - beta * cr), (R)(-beta * ci), (R)beta};
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            ctl->bbeta[j] = beta;
+            ctl->brho[j] = rho;
+            ctl->brmax2[j] = rho;
+        }
+    }
+    for (size_t s = gtid(); s < n; s += gstride()) {
+        const CVec<R> rv = SpinorIO<SF, R>::load(r + j * fs, n, s), pv = SpinorIO<SF, R>::load(ps + j * fs, n, s);
+        (void)SpinorIO<SF, R>::store(pd + j * fs, n, s, pstep<R>(k, rv, pv));
     }
 }
 
 template <int SF, class R>
-__global__ void k_bru_convert(char *rs, const char *r64, size_t fs64, const char *p, const char *ap,
-                              const SolverCtrl *ctrl, size_t n, size_t fs, int nrhs, double *partial, Guard gd) {
-    __shared__ double lds[64];
+__global__ void __launch_bounds__(BLAS_BLOCK) k_bflush_x(char *x64, size_t fs64, SpinorList ring, int count,
+                                                         const SolverCtrl *ctl, size_t n, size_t fs, BCols cols,
+                                                         Guard gd) {
     if (!gd.pass()) return;
-    for (int j = 0; j < nrhs; j++) {
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        const R a = (R)ctrl->balpha[j];
-        char *rsj = rs + j * fs;
-        // only the systems taking part in the reliable update replace their residual
-        const bool part = ctrl->bru[j] && ctrl->bactive[j];
-        for (size_t s = gtid(); part && s < n; s += gstride()) {
-            CVec<double> rt = SpinorIO<SF_F64, double>::load(r64 + j * fs64, n, s);
-            CVec<R> rold;
-            if (ap) rold = SpinorIO<SF, R>::load(rsj, n, s);
-            CVec<R> rn;
+    const int j = bcol(cols);
+    // a stopped system's buffered gradients were flushed before it stopped
+    if (!ctl->bactive[j]) return;
+    char *xj = x64 + j * fs64;
+    for (size_t s = gtid(); s < n; s += gstride()) {
+        CVec<double> x = SpinorIO<SF_F64, double>::load(xj, n, s);
+        (void)bflush_site<SF, R>(x, ring, j * fs, count, ctl, j, n, s);
+        SpinorIO<SF_F64, double>::store(xj, n, s, x);
+    }
+}
+
+template <int SF, class R>
+__global__ void __launch_bounds__(BLAS_BLOCK) k_bru_convert(char *rs, const char *r64, size_t fs64, const char *p,
+                                                            const char *ap, const SolverCtrl *ctrl, size_t n, size_t fs,
+                                                            BCols cols, double *partial, Guard gd) {
+    __shared__ double lds[4 * (BLAS_BLOCK / 64)];
+    if (!gd.pass()) return;
+    const int j = bcol(cols);
+    // only the systems taking part in the reliable update replace their residual
+    if (!ctrl->bru[j] || !ctrl->bactive[j]) return;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    const R a = (R)ctrl->balpha[j];
+    char *rsj = rs + j * fs;
+    for (size_t s = gtid(); s < n; s += gstride()) {
+        CVec<double> rt = SpinorIO<SF_F64, double>::load(r64 + j * fs64, n, s);
+        CVec<R> rold;
+        if (ap) rold = SpinorIO<SF, R>::load(rsj, n, s);
+        CVec<R> rn;
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            rn.re[c] = (R)rt.re[c];
+            rn.im[c] = (R)rt.im[c];
+        }
+        CVec<R> o = SpinorIO<SF, R>::store(rsj, n, s, rn);
+#pragma unroll
+        for (int c = 0; c < 3; c++) acc[0] += (double)o.re[c] * (double)o.re[c] + (double)o.im[c] * (double)o.im[c];
+        if (p) {
+            CVec<R> pv = SpinorIO<SF, R>::load(p + j * fs, n, s);
 #pragma unroll
             for (int c = 0; c < 3; c++) {
-                rn.re[c] = (R)rt.re[c];
-                rn.im[c] = (R)rt.im[c];
-            }
-            CVec<R> o = SpinorIO<SF, R>::store(rsj, n, s, rn);
-#pragma unroll
-            for (int c = 0; c < 3; c++) acc[0] += (double)o.re[c] * (double)o.re[c] + (double)o.im[c] * (double)o.im[c];
-            if (p) {
-                CVec<R> pv = SpinorIO<SF, R>::load(p + j * fs, n, s);
-#pragma unroll
-                for (int c = 0; c < 3; c++) {
-                    acc[1] += (double)o.re[c] * (double)pv.re[c] + (double)o.im[c] * (double)pv.im[c];
-                    acc[2] += (double)o.re[c] * (double)pv.im[c] - (double)o.im[c] * (double)pv.re[c];
-                }
-            }
-            if (ap) {
-                CVec<R> av = SpinorIO<SF, R>::load(ap + j * fs, n, s);
-#pragma unroll
-                for (int c = 0; c < 3; c++) {
-                    const double pr = (double)rold.re[c] + (double)a * (double)av.re[c];
-                    const double pi = (double)rold.im[c] + (double)a * (double)av.im[c];
-                    acc[3] += (double)o.re[c] * pr + (double)o.im[c] * pi;
-                }
+                acc[1] += (double)o.re[c] * (double)pv.re[c] + (double)o.im[c] * (double)pv.im[c];
+                acc[2] += (double)o.re[c] * (double)pv.im[c] - (double)o.im[c] * (double)pv.re[c];
             }
         }
-        block_sum<4>(acc, lds);
-        if (threadIdx.x == 0) {
+        if (ap) {
+            CVec<R> av = SpinorIO<SF, R>::load(ap + j * fs, n, s);
 #pragma unroll
-            for (int k = 0; k < 4; k++) partial[((size_t)blockIdx.x * nrhs + j) * 4 + k] = acc[k];
+            for (int c = 0; c < 3; c++) {
+                const double pr = (double)rold.re[c] + (double)a * (double)av.re[c];
+                const double pi = (double)rold.im[c] + (double)a * (double)av.im[c];
+                acc[3] += (double)o.re[c] * pr + (double)o.im[c] * pi;
+            }
         }
-        __syncthreads();
+    }
+    block_sum<4>(acc, lds);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int k = 0; k < 4; k++) partial[((size_t)j * gridDim.x + blockIdx.x) * 4 + k] = acc[k];
     }
 }
 
@@ -1333,29 +1421,52 @@ hipError_t launch_shift_replay(const SpinorList &x64, const SpinorList &p, const
     return hipGetLastError();
 }
 
-hipError_t launch_bcg_axpy(char *r, const char *ap, const SolverCtrl *ctrl, size_t n, size_t stride, int nrhs, int sf,
-                           int compute, double *partial, Guard gd, hipStream_t st) {
-    HISQ_DISPATCH_SC(sf, compute, hipLaunchKernelGGL((k_bcg_axpy<SFc, Rc>), dim3(blas_blocks(n)), dim3(BLAS_BLOCK), 0, st, r, ap, ctrl, n, stride, nrhs, partial, gd));
+int bcg_blocks(size_t n, int na) {
+    // 2048 resident blocks shared by the systems; at least 32 each, so that a row's
+    // partials and scalars are few against its sites
+    const int row = std::max(32, BLAS_MAX_BLOCKS / std::max(1, na));
+    return std::min(blas_blocks(n), row);
+}
+
+hipError_t launch_bcg_axpy(char *r, const char *ap, SolverCtrl *ctrl, const BSums &pap, size_t n, size_t stride,
+                           const BCols &cols, int sf, int compute, double *partial, int jb, Guard gd, hipStream_t st) {
+    const dim3 grid(bcg_blocks(n, cols.n), cols.n);
+    HISQ_DISPATCH_SC(sf, compute, hipLaunchKernelGGL((k_bcg_axpy<SFc, Rc>), grid, dim3(BLAS_BLOCK), 0, st, r, ap, ctrl, pap, n, stride, cols, partial, jb, gd));
     return hipGetLastError();
 }
 
-hipError_t launch_bcg_pupdate(char *p_dst, const char *r, const char *p_src, const SolverCtrl *ctrl, size_t n,
-                              size_t stride, int nrhs, int sf, int compute, Guard gd, hipStream_t st) {
-    HISQ_DISPATCH_SC(sf, compute, hipLaunchKernelGGL((k_bcg_pupdate<SFc, Rc>), dim3(blas_blocks(n)), dim3(BLAS_BLOCK), 0, st, p_dst, r, p_src, ctrl, n, stride, nrhs, gd));
+hipError_t launch_bcg_pupdate(char *p_dst, const char *r, const char *p_src, const SolverCtrl *ctrl, char *x64,
+                              size_t stride64, const SpinorList &ring, int count, size_t n, size_t stride,
+                              const BCols &cols, int sf, int compute, Guard gd, hipStream_t st) {
+    const dim3 grid(bcg_blocks(n, cols.n), cols.n);
+    if (count > 0)
+        HISQ_DISPATCH_SC(sf, compute, hipLaunchKernelGGL((k_bcg_pupdate<SFc, Rc, true>), grid, dim3(BLAS_BLOCK), 0, st, p_dst, r, p_src, ctrl, x64, stride64, ring, count, n, stride, cols, gd));
+    else
+        HISQ_DISPATCH_SC(sf, compute, hipLaunchKernelGGL((k_bcg_pupdate<SFc, Rc, false>), grid, dim3(BLAS_BLOCK), 0, st, p_dst, r, p_src, ctrl, x64, stride64, ring, 0, n, stride, cols, gd));
+    return hipGetLastError();
+}
+
+hipError_t launch_bru_pupdate(char *p_dst, const char *r, const char *p_src, SolverCtrl *ctrl, const BSums &ru,
+                              int mode, size_t n, size_t stride, const BCols &cols, int sf, int compute, Guard gd,
+                              hipStream_t st) {
+    const dim3 grid(bcg_blocks(n, cols.n), cols.n);
+    HISQ_DISPATCH_SC(sf, compute, hipLaunchKernelGGL((k_bru_pupdate<SFc, Rc>), grid, dim3(BLAS_BLOCK), 0, st, p_dst, r, p_src, ctrl, ru, mode, n, stride, cols, gd));
     return hipGetLastError();
 }
 
 hipError_t launch_bflush_x(char *x64, size_t stride64, const SpinorList &p, int count, const SolverCtrl *ctrl,
-                           size_t n, size_t stride, int nrhs, int sf, int compute, Guard gd, hipStream_t st) {
+                           size_t n, size_t stride, const BCols &cols, int sf, int compute, Guard gd, hipStream_t st) {
     if (count <= 0) return hipSuccess;
-    HISQ_DISPATCH_SC(sf, compute, hipLaunchKernelGGL((k_bflush_x<SFc, Rc>), dim3(blas_blocks(n)), dim3(BLAS_BLOCK), 0, st, x64, stride64, p, count, ctrl, n, stride, nrhs, gd));
+    const dim3 grid(bcg_blocks(n, cols.n), cols.n);
+    HISQ_DISPATCH_SC(sf, compute, hipLaunchKernelGGL((k_bflush_x<SFc, Rc>), grid, dim3(BLAS_BLOCK), 0, st, x64, stride64, p, count, ctrl, n, stride, cols, gd));
     return hipGetLastError();
 }
 
 hipError_t launch_bru_convert(char *r_s, const char *r64, size_t stride64, const char *p, const char *ap,
-                              const SolverCtrl *ctrl, size_t n, size_t stride, int nrhs, int sf, int compute,
+                              const SolverCtrl *ctrl, size_t n, size_t stride, const BCols &cols, int sf, int compute,
                               double *partial, Guard gd, hipStream_t st) {
-    HISQ_DISPATCH_SC(sf, compute, hipLaunchKernelGGL((k_bru_convert<SFc, Rc>), dim3(blas_blocks(n)), dim3(BLAS_BLOCK), 0, st, r_s, r64, stride64, p, ap, ctrl, n, stride, nrhs, partial, gd));
+    const dim3 grid(bcg_blocks(n, cols.n), cols.n);
+    HISQ_DISPATCH_SC(sf, compute, hipLaunchKernelGGL((k_bru_convert<SFc, Rc>), grid, dim3(BLAS_BLOCK), 0, st, r_s, r64, stride64, p, ap, ctrl, n, stride, cols, partial, gd));
     return hipGetLastError();
 }
 

@@ -248,6 +248,9 @@ struct SolverCtrl {
     int bdone[16];
     int bk[16];
     int bwarm[16];     // 1: system j continues a given gradient vector at its first reliable update
+    int bflag[16];     // what this iteration (or true residual) decided for system j, for the last block to combine
+    unsigned ticket;   // blocks of the running scalar kernel that have written theirs
+    double bred[16][4];   // sums of block partials too many for every consumer block to add up
 };
 
 enum { STOP_NONE = 0, STOP_RU = 1, STOP_CONV = 2, STOP_BREAKDOWN = 3, STOP_MAXITER = 4, STOP_MSDONE = 5 };
@@ -362,15 +365,36 @@ hipError_t launch_shift_replay(const SpinorList &x64, const SpinorList &p, const
 int shift_replay_grid(size_t n, int sf, int compute);
 int flush_x_grid(size_t n, int sf, int compute);
 
-// batched versions (nrhs consecutive fields of `stride` bytes)
-hipError_t launch_bcg_axpy(char *r, const char *ap, const SolverCtrl *ctrl, size_t n, size_t stride, int nrhs,
-                           int sf, int compute, double *partial, Guard gd, hipStream_t st);
-hipError_t launch_bcg_pupdate(char *p_dst, const char *r, const char *p_src, const SolverCtrl *ctrl, size_t n,
-                              size_t stride, int nrhs, int sf, int compute, Guard gd, hipStream_t st);
+// Batched versions: nrhs consecutive fields of `stride` bytes; the launch has a
+// row of bcg_blocks(n, na) blocks for each of the na systems of `cols` (four bits
+// each), so that a small lattice's systems run side by side.  Partials of system
+// j: partial[(j * blocks + b) * NV + k].
+struct BCols {
+    unsigned long long map;
+    int n;
+};
+// one block's partials of system j start at p + j * stride, n tuples
+struct BSums {
+    const double *p;
+    int n;
+    size_t stride;
+};
+int bcg_blocks(size_t n, int na);
+hipError_t launch_bcg_axpy(char *r, const char *ap, SolverCtrl *ctrl, const BSums &pap, size_t n, size_t stride,
+                           const BCols &cols, int sf, int compute, double *partial, int jb, Guard gd, hipStream_t st);
+// p_dst = r + beta p_src; count > 0: also the buffered solutions, as launch_cg_pupdate
+hipError_t launch_bcg_pupdate(char *p_dst, const char *r, const char *p_src, const SolverCtrl *ctrl, char *x64,
+                              size_t stride64, const SpinorList &ring, int count, size_t n, size_t stride,
+                              const BCols &cols, int sf, int compute, Guard gd, hipStream_t st);
+// after a reliable update: the systems that took part take their scalars from
+// the sums of launch_bru_convert, the others their ordinary CG step
+hipError_t launch_bru_pupdate(char *p_dst, const char *r, const char *p_src, SolverCtrl *ctrl, const BSums &ru,
+                              int mode, size_t n, size_t stride, const BCols &cols, int sf, int compute, Guard gd,
+                              hipStream_t st);
 hipError_t launch_bflush_x(char *x64, size_t stride64, const SpinorList &p, int count, const SolverCtrl *ctrl,
-                           size_t n, size_t stride, int nrhs, int sf, int compute, Guard gd, hipStream_t st);
+                           size_t n, size_t stride, const BCols &cols, int sf, int compute, Guard gd, hipStream_t st);
 hipError_t launch_bru_convert(char *r_s, const char *r64, size_t stride64, const char *p, const char *ap,
-                              const SolverCtrl *ctrl, size_t n, size_t stride, int nrhs, int sf, int compute,
+                              const SolverCtrl *ctrl, size_t n, size_t stride, const BCols &cols, int sf, int compute,
                               double *partial, Guard gd, hipStream_t st);
 
 // A block of independent CG solves (A + c_j) x_j = b_j sharing every Dslash

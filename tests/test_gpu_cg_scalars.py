@@ -89,3 +89,29 @@ def test_iteration_cap_at_the_edges_of_a_unit(batched, maxiter):
         x, st = hisq.cg_solve(b[0], g64, gs, 0.01, tol=1e-12, sloppy="int20", maxiter=maxiter)
     assert st["status"] == "HISQ_ENOCONV" and st["iters"] == maxiter
     assert st["true_resid"] > 1e-12 and bool(torch.isfinite(torch.view_as_real(x)).all())
+
+
+# 128 sites per parity (one block a row); a ragged last block; above the line where a row's partials are
+# added up in a launch of their own (one system: its row has over 512 blocks)
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (6, 10, 12, 12), (24, 24, 24, 24)])
+@pytest.mark.parametrize("sloppy,nrhs", [("int20", 1), ("half", 2), ("single", 5), ("int20", 11), ("int24", 16)])
+def test_batched_rows(dims, sloppy, nrhs):
+    hisq = need_gpu()
+    fat, lng = inputs.make_links(dims, "near_unit", device="cuda")
+    ev = oracle.parity_sites(dims, 0)
+    b = inputs.gaussian_spinor(ev.size, inputs.RHS_SEED, device="cuda", nrhs=nrhs)
+    if nrhs > 2:
+        b[1] = 0.0    # a system that never iterates
+    g64 = hisq.pack_gauge(fat, lng, dims, hisq.GAUGE_F64, long_recon=12)
+    gs = hisq.pack_gauge(fat, lng, dims, hisq.fmt(sloppy).gauge, long_recon=12)
+    x, st = hisq.cg_solve_batched(b, g64, gs, MASS, tol=TOL, sloppy=sloppy)
+    assert st["status"] == "HISQ_OK", st
+    fat, lng = fat.cpu().numpy(), lng.cpu().numpy()
+    full = lambda v: torch.zeros((oracle.volume(dims), 3), dtype=torch.complex128).index_copy_(  # noqa: E731
+        0, torch.from_numpy(ev), v.cpu()).numpy()
+    for j in range(nrhs):
+        if nrhs > 2 and j == 1:
+            assert not bool(x[j].abs().any())
+            continue
+        res = oracle.true_residual(fat, lng, full(x[j]), full(b[j]), dims, MASS)
+        assert res <= TOL * (1 + 1e-6), (j, res, st)
