@@ -1010,7 +1010,7 @@ __device__ __forceinline__ void dslash_site_mfma(const DslashArgs &A, int s, boo
 // standalone applications use the unguarded instantiation.
 // LR: 18 = long links stored in full, 12 = two rows + reconstruction
 template <int GF, int SF, class R, int NR, int STAGE, bool RED, bool GUARD, int LR>
-__global__ void __launch_bounds__(256) k_dslash(DslashArgs A, int rhs0, int rg, FastDiv drg, int sweep) {
+__global__ void __launch_bounds__(256) k_dslash(DslashArgs A, int rhs0, int rg, int sweep) {
     __shared__ double lds[64];
     if (GUARD && !A.guard.pass()) return;
     const Geom g = A.g;
@@ -1024,7 +1024,20 @@ __global__ void __launch_bounds__(256) k_dslash(DslashArgs A, int rhs0, int rg, 
     // the wave then skips.  Those at or beyond ncol (a block padded to a power
     // of two) and those marked inactive are neither read nor written.
     const int ncol = A.nrhs > 1 ? A.nrhs : 1;
-    const int grp0 = (int)(threadIdx.x & (unsigned)(rg - 1));
+    // Lanes and sites: the wave's 64 / rg sites are consecutive lanes, group after
+    // group, so that each quad of lanes reads one 64-byte piece of one column.
+    // With the groups of a site on adjacent lanes a quad's 16-byte loads fell on
+    // two (rg 2) or four columns and took as many passes of the address unit:
+    // COALESCE_FIGURES
+    // The matrix-core path needs a site's four lanes side by side.
+    constexpr bool ADJ = STAGE == MFMA_STAGE;
+    const int lrg = __builtin_ctz((unsigned)rg), lane = threadIdx.x & 63, lw = 6 - lrg;
+    const int grp0 = ADJ ? lane & (rg - 1) : lane >> lw;
+    // site of this lane among the 64 / rg per wave of a run of lanes that starts at lane index l0
+    auto site_of = [&](int l0) {
+        const int l = l0 + (int)threadIdx.x;
+        return ADJ ? l >> lrg : ((l >> 6) << lw) + (lane & ((1 << lw) - 1));
+    };
     auto cofs = [&](int lg, int j) { return j * rg + lg; };
     unsigned live = 0;
 #pragma unroll
@@ -1068,41 +1081,38 @@ __global__ void __launch_bounds__(256) k_dslash(DslashArgs A, int rhs0, int rg, 
         tstep = gridDim.x >> 3;
     }
     for (int tile = tile0; tile < tend; tile += tstep) {
-    int s, grp;
+    int s;
     bool inside;
     if (sweep == 2) {
         const int t = tile / tps;
-        const int off = (tile - t * tps) * (int)blockDim.x + (int)threadIdx.x;
-        const int sl = rg == 1 ? off : fdiv(off, drg);
+        const int sl = site_of((tile - t * tps) * (int)blockDim.x);
         inside = sl < slab;
         s = (t * g.Z + zs0) * g.Y * g.X2 + sl;
-        grp = off - sl * rg;
     } else {
-        const int tid = tile * blockDim.x + threadIdx.x;
-        s = rg == 1 ? tid : fdiv(tid, drg);
-        grp = tid - s * rg;
+        s = site_of(tile * (int)blockDim.x);
         inside = s < g.vh;
     }
     if constexpr (STAGE == MFMA_STAGE) {
         // every lane takes part in the matrix instructions of its site's block
-        dslash_site_mfma<GF, SF, NR, RED, LR>(A, s, inside, rhs0, grp, live, acoef, red);
+        dslash_site_mfma<GF, SF, NR, RED, LR>(A, s, inside, rhs0, grp0, live, acoef, red);
     } else {
-        if (inside && live) dslash_site<GF, SF, R, NR, STAGE, RED, LR>(A, s, rhs0 + grp, rg, live, acoef, red);
+        if (inside && live) dslash_site<GF, SF, R, NR, STAGE, RED, LR>(A, s, rhs0 + grp0, rg, live, acoef, red);
     }
     }
     if (RED) {
-        // per right-hand side: sum over the lanes of the same group (lanes l with
-        // l % rg == grp; rg is a power of two dividing 64), then over the waves
-        const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+        // per right-hand side: sum over the lanes of the same group (rg is a power
+        // of two dividing 64), then over the waves
+        const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+        const int o0 = ADJ ? 32 : 32 >> lrg, o1 = ADJ ? rg : 1;
 #pragma unroll
         for (int j = 0; j < NR; j++) {
             double v = red[j];
-            for (int o = 32; o >= rg; o >>= 1) v += __shfl_xor(v, o, 64);
+            for (int o = o0; o >= o1; o >>= 1) v += __shfl_xor(v, o, 64);
             red[j] = v;
         }
-        if (lane < rg) {
+        if (ADJ ? lane < rg : (lane & ((1 << lw) - 1)) == 0) {
 #pragma unroll
-            for (int j = 0; j < NR; j++) lds[w * rg * NR + cofs(lane, j)] = red[j];
+            for (int j = 0; j < NR; j++) lds[w * rg * NR + cofs(grp0, j)] = red[j];
         }
         __syncthreads();
         const int k = threadIdx.x;
@@ -1149,35 +1159,34 @@ hipError_t launch_cfg(const DslashArgs &a, int rhs0, int rg, int block, int grid
                       int *nblocks) {
     const int nb = dslash_tile_blocks(a.g, DslashTile{NR, rg, STAGE, block, grid, sweep});
     if (nblocks) *nblocks = nb;
-    const FastDiv drg = make_fastdiv((unsigned)rg);
     if (a.long_recon == 8) {
         if constexpr (NR == 1 && std::is_same<R, double>::value && (GF == GF_F64 || GF == GF_FIX32) &&
                       STAGE != MFMA_STAGE) {
             if (rg != 1) return hipErrorInvalidValue;
             if (a.red != RED_NONE)
-                hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, true, true, 8>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, drg, sweep);
+                hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, true, true, 8>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, sweep);
             else if (a.guard.stop)
-                hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, true, 8>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, drg, sweep);
+                hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, true, 8>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, sweep);
             else
-                hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, false, 8>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, drg, sweep);
+                hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, false, 8>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, sweep);
             return hipGetLastError();
         }
         return hipErrorInvalidValue;
     }
     if (a.long_recon == 12) {
         if (a.red != RED_NONE)
-            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, true, true, 12>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, drg, sweep);
+            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, true, true, 12>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, sweep);
         else if (a.guard.stop)
-            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, true, 12>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, drg, sweep);
+            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, true, 12>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, sweep);
         else
-            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, false, 12>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, drg, sweep);
+            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, false, 12>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, sweep);
     } else {
         if (a.red != RED_NONE)
-            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, true, true, 18>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, drg, sweep);
+            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, true, true, 18>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, sweep);
         else if (a.guard.stop)
-            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, true, 18>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, drg, sweep);
+            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, true, 18>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, sweep);
         else
-            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, false, 18>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, drg, sweep);
+            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, false, 18>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, sweep);
     }
     return hipGetLastError();
 }
