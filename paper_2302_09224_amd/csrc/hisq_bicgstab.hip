@@ -7,11 +7,21 @@
 // iterated |r_0| drops by delta below its maximum since the last update (or
 // meets the target), r = b - M x is computed with the FP64 operator and
 // replaces r_0.  Every scalar (rho, alpha, beta, tau, sigma, gamma, omega) is
-// formed on the device by one-thread kernels from fixed-order reductions, and
-// every vector kernel reads its coefficients from device memory, so a whole
-// cycle (l BiCG steps and the minimal-residual step) is enqueued without the
-// host, replayed as a captured hipGraph, and followed by one synchronisation,
-// where the host reads |r_0|^2 and decides on a reliable update.
+// formed on the device, by every block of the kernel that needs it first, from
+// the block partials of the kernel before (fixed order, so all blocks agree);
+// the first block records it.  A whole cycle (l BiCG steps and the
+// minimal-residual step) is enqueued without the host and replayed as a captured
+// hipGraph: 5 l + 2 launches,
+//   per step j:  u_i = r_i - beta u_i (all i <= j); u_{j+1} = M u_j with <r~, u_{j+1}>;
+//                r_i -= alpha u_{i+1} (all i <= j), x += alpha u_0; r_{j+1} = M r_j with
+//                <r~, r_{j+1}>
+//   l passes of the modified Gram-Schmidt (row i: r_j -= tau_{i-1,j} r_{i-1} for j >= i, and
+//   the dot products with r_i in the same pass), the closing updates, the cycle's record.
+// (As a launch per operation a cycle of l = 4 took 108 launches; 16^4 with 20-bit
+// spinors, m = 0.05 to 1e-12: 39 -> 15.7 ms.)
+// A cycle whose |r_0|^2 asks for a reliable update, or that breaks down, lowers
+// the guard of the cycles behind it; the host reads each cycle's record from
+// pinned memory, with the next cycle already enqueued.
 //
 // A whole-lattice field is two single-parity fields back to back: the even
 // sites, then the odd sites, each in the usual packed layout of Vh sites.
@@ -35,144 +45,45 @@ constexpr int BL_BLOCK = 256;
 
 constexpr int BL_MAXL = HISQ_MAX_BICGSTAB_L;
 
+constexpr int BL_WAVES = BL_BLOCK / 64;
+
 struct VecList {
-    const char *p[BL_MAXK];
+    char *p[BL_MAXL + 1];
 };
 
-// device scalars of one solve (complex values as re, im)
+// device scalars of one solve (complex values as re, im).  A kernel reads no
+// field that its own first block writes.
 struct BlCtl {
-    int stop;     // guard of every kernel of a cycle: 0 while running, -1 after a breakdown
+    int stop;     // guard of every kernel of a cycle: 0 while running, below after a breakdown (-1) or when a
+                  // reliable update is due (-2)
     int broke;    // 1: a BiCG or minimal-residual denominator vanished, 2: non-finite residual
-    double one[2];
-    double rho0[2], alpha[2], omega[2];
-    double beta_neg[2], alpha_neg[2], tau_neg[2];
+    int due;      // the last cycle asked for a reliable update
+    int cycles;   // completed
+    unsigned long long seq;   // records published
+    double rho_c[2], alpha_c[2];                            // entering the cycle
+    double rho[BL_MAXL][2], alpha[BL_MAXL][2];              // of the cycle's steps
     double tau[BL_MAXL + 1][BL_MAXL + 1][2];
     double sigma[BL_MAXL + 1];
-    double gp[BL_MAXL + 1][2], gm[BL_MAXL + 1][2];
-    double cx[BL_MAXK][2], cu[BL_MAXK][2], cr[BL_MAXK][2];   // coefficients of the closing updates
-    double rs2;
+    double gp[BL_MAXL + 1][2];
+    double rs2, rmax2, delta2, tol2;
+    double red[2 * BL_MAXL + 2];   // sums of block partials too many for every consumer block to add up
 };
-// what the host reads after a cycle
-struct BlSummary {
-    int stop, broke;
-    double rs2;
+// what the host reads after a cycle or a true residual
+struct BlRecord {
+    unsigned long long seq;
+    int stop, broke, cycles;
+    double rs2;       // |r_0|^2 (a cycle) or |b - M x|^2 (a true residual)
+    double lead;      // |r_0|^2 over the value that asks for a reliable update
+};
+constexpr int BL_RING = 8;
+struct BlHost {
+    BlRecord ring[BL_RING];
+    unsigned long long launched;
 };
 
 __device__ __forceinline__ size_t bl_tid() { return (size_t)blockIdx.x * blockDim.x + threadIdx.x; }
 __device__ __forceinline__ size_t bl_stride() { return (size_t)gridDim.x * blockDim.x; }
-
-// y = a*y + sum_k c_k x_k on the 2*vh sites of whole-lattice fields (half h at
-// byte offset h*fb); a and c (K complex values) in device memory;
-// partial[block] = |y_new|^2 (stored values) if partial
-template <int SF, class R>
-__global__ void k_bl_combine(char *y, const double *a, int read_y, VecList xs, const double *c, int K, size_t vh,
-                             size_t fb, double *partial, const int *stop) {
-    __shared__ double lds[8];
-    if (*stop < 0) return;
-    const double are = a[0], aim = a[1];
-    double acc[1] = {0.0};
-    for (size_t i = bl_tid(); i < 2 * vh; i += bl_stride()) {
-        const size_t h = i >= vh ? 1 : 0, s = i - h * vh;
-        CVec<R> o;
-        if (read_y) {
-            const CVec<R> v = SpinorIO<SF, R>::load(y + h * fb, vh, s);
-#pragma unroll
-            for (int q = 0; q < 3; q++) {
-                o.re[q] = (R)are * v.re[q] - (R)aim * v.im[q];
-                o.im[q] = (R)are * v.im[q] + (R)aim * v.re[q];
-            }
-        } else {
-            cvec_zero(o);
-        }
-        for (int k = 0; k < K; k++) {
-            const CVec<R> v = SpinorIO<SF, R>::load(xs.p[k] + h * fb, vh, s);
-            const R cr = (R)c[2 * k], ci = (R)c[2 * k + 1];
-#pragma unroll
-            for (int q = 0; q < 3; q++) {
-                o.re[q] = fma(cr, v.re[q], fma(-ci, v.im[q], o.re[q]));
-                o.im[q] = fma(cr, v.im[q], fma(ci, v.re[q], o.im[q]));
-            }
-        }
-        const CVec<R> st = SpinorIO<SF, R>::store(y + h * fb, vh, s, o);
-        if (partial) {
-#pragma unroll
-            for (int q = 0; q < 3; q++) acc[0] += (double)st.re[q] * st.re[q] + (double)st.im[q] * st.im[q];
-        }
-    }
-    if (partial) {
-        block_sum<1>(acc, lds);
-        if (threadIdx.x == 0) partial[blockIdx.x] = acc[0];
-    }
-}
-
-// <x_k, y> for k < K (re, im) and |y|^2: partial[(block)*(2K+1) + v]
-template <int SF, class R>
-__global__ void k_bl_dots(VecList xs, int K, const char *y, size_t vh, size_t fb, double *partial, const int *stop) {
-    __shared__ double lds[4 * (2 * BL_MAXK + 1)];
-    if (*stop < 0) return;
-    double acc[2 * BL_MAXK + 1];
-#pragma unroll
-    for (int v = 0; v < 2 * BL_MAXK + 1; v++) acc[v] = 0.0;
-    for (size_t i = bl_tid(); i < 2 * vh; i += bl_stride()) {
-        const size_t h = i >= vh ? 1 : 0, s = i - h * vh;
-        const CVec<R> w = SpinorIO<SF, R>::load(y + h * fb, vh, s);
-#pragma unroll
-        for (int q = 0; q < 3; q++) acc[2 * BL_MAXK] += (double)w.re[q] * w.re[q] + (double)w.im[q] * w.im[q];
-#pragma unroll
-        for (int k = 0; k < BL_MAXK; k++) {
-            if (k >= K) break;
-            const CVec<R> v = SpinorIO<SF, R>::load(xs.p[k] + h * fb, vh, s);
-#pragma unroll
-            for (int q = 0; q < 3; q++) {
-                acc[2 * k] += (double)v.re[q] * w.re[q] + (double)v.im[q] * w.im[q];
-                acc[2 * k + 1] += (double)v.re[q] * w.im[q] - (double)v.im[q] * w.re[q];
-            }
-        }
-    }
-    block_sum<2 * BL_MAXK + 1>(acc, lds);
-    if (threadIdx.x == 0) {
-        for (int k = 0; k < K; k++) {
-            partial[(size_t)blockIdx.x * (2 * K + 1) + 2 * k] = acc[2 * k];
-            partial[(size_t)blockIdx.x * (2 * K + 1) + 2 * k + 1] = acc[2 * k + 1];
-        }
-        partial[(size_t)blockIdx.x * (2 * K + 1) + 2 * K] = acc[2 * BL_MAXK];
-    }
-}
-
-// out[v] = sum over nb blocks of partial[b*nv + v], v < nv (one block, fixed order)
-__global__ void k_bl_fin(const double *partial, int nb, int nv, double *out) {
-    __shared__ double lds[4];
-    for (int v = 0; v < nv; v++) {
-        double acc[1] = {0.0};
-        for (int b = threadIdx.x; b < nb; b += blockDim.x) acc[0] += partial[(size_t)b * nv + v];
-        block_sum<1>(acc, lds);
-        if (threadIdx.x == 0) out[v] = acc[0];
-        __syncthreads();
-    }
-}
-
-// x64 += sum_k c_k v_k (FP64 solution, sloppy vectors; c in device memory)
-template <int SF, class R>
-__global__ void k_bl_xupdate(char *x64, VecList vs, const double *c, int K, size_t vh, size_t fb, size_t fb64,
-                             const int *stop) {
-    if (*stop < 0) return;
-    for (size_t i = bl_tid(); i < 2 * vh; i += bl_stride()) {
-        const size_t h = i >= vh ? 1 : 0, s = i - h * vh;
-        CVec<double> x = SpinorIO<SF_F64, double>::load(x64 + h * fb64, vh, s);
-        for (int k = 0; k < K; k++) {
-            const CVec<R> v = SpinorIO<SF, R>::load(vs.p[k] + h * fb, vh, s);
-#pragma unroll
-            for (int q = 0; q < 3; q++) {
-                x.re[q] += c[2 * k] * (double)v.re[q] - c[2 * k + 1] * (double)v.im[q];
-                x.im[q] += c[2 * k] * (double)v.im[q] + c[2 * k + 1] * (double)v.re[q];
-            }
-        }
-        SpinorIO<SF_F64, double>::store(x64 + h * fb64, vh, s, x);
-    }
-}
-
-// ---- the scalars of the method, one thread ----
-enum BlOp { BL_START, BL_RHO, BL_GAM, BL_TAU, BL_SIGMA, BL_MR, BL_RS2 };
+__device__ __forceinline__ bool bl_first() { return blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0; }
 
 __device__ __forceinline__ void bl_mul(const double *a, const double *b, double *o) {
     const double re = a[0] * b[0] - a[1] * b[1], im = a[0] * b[1] + a[1] * b[0];
@@ -197,121 +108,385 @@ __device__ __forceinline__ void bl_div(const double *a, const double *b, double 
 __device__ __forceinline__ bool bl_zero(const double *a) { return a[0] == 0.0 && a[1] == 0.0; }
 __device__ __forceinline__ bool bl_finite(const double *a) { return __builtin_isfinite(a[0]) && __builtin_isfinite(a[1]); }
 
-// res: the finished reduction of the step's dot products (<x, y> as re, im, then |y|^2)
-__global__ void k_bl_step(BlCtl *c, const double *res, int op, int i, int j, int l) {
-    if (threadIdx.x || c->stop < 0) return;
-    auto fail = [&](int code) {
-        c->broke = code;
-        c->stop = -1;
-    };
-    switch (op) {
-    case BL_START: {   // rho0 = -omega rho0
-        double t[2];
-        bl_mul(c->omega, c->rho0, t);
-        c->rho0[0] = -t[0];
-        c->rho0[1] = -t[1];
-        break;
+// v += c x, c complex
+template <class R> __device__ __forceinline__ void bl_axpy(CVec<R> &v, const double *c, const CVec<R> &x) {
+    const R cr = (R)c[0], ci = (R)c[1];
+#pragma unroll
+    for (int q = 0; q < 3; q++) {
+        v.re[q] = fma(cr, x.re[q], fma(-ci, x.im[q], v.re[q]));
+        v.im[q] = fma(cr, x.im[q], fma(ci, x.re[q], v.im[q]));
     }
-    case BL_RHO: {     // rho1 = <r~, r_j>; beta = alpha rho1 / rho0; rho0 = rho1
-        const double rho1[2] = {res[0], res[1]};
-        if (bl_zero(c->rho0) || !bl_finite(rho1)) {
-            fail(1);
-            break;
-        }
-        double t[2], beta[2];
-        bl_mul(c->alpha, rho1, t);
-        bl_div(t, c->rho0, beta);
-        c->rho0[0] = rho1[0];
-        c->rho0[1] = rho1[1];
-        c->beta_neg[0] = -beta[0];
-        c->beta_neg[1] = -beta[1];
-        break;
+}
+template <class R> __device__ __forceinline__ void bl_xaxpy(CVec<double> &x, const double *c, const CVec<R> &v) {
+#pragma unroll
+    for (int q = 0; q < 3; q++) {
+        x.re[q] += c[0] * (double)v.re[q] - c[1] * (double)v.im[q];
+        x.im[q] += c[0] * (double)v.im[q] + c[1] * (double)v.re[q];
     }
-    case BL_GAM: {     // gamma = <r~, u_{j+1}>; alpha = rho0 / gamma
-        const double gam[2] = {res[0], res[1]};
-        if (bl_zero(gam) || !bl_finite(gam)) {
-            fail(1);
-            break;
-        }
-        bl_div(c->rho0, gam, c->alpha);
-        c->alpha_neg[0] = -c->alpha[0];
-        c->alpha_neg[1] = -c->alpha[1];
-        break;
+}
+// acc += conj(v) w (re, im)
+template <class R> __device__ __forceinline__ void bl_cdot(double *acc, const CVec<R> &v, const CVec<R> &w) {
+#pragma unroll
+    for (int q = 0; q < 3; q++) {
+        acc[0] += (double)v.re[q] * w.re[q] + (double)v.im[q] * w.im[q];
+        acc[1] += (double)v.re[q] * w.im[q] - (double)v.im[q] * w.re[q];
     }
-    case BL_TAU: {     // tau_ij = <r_i, r_j> / sigma_i
-        c->tau[i][j][0] = res[0] / c->sigma[i];
-        c->tau[i][j][1] = res[1] / c->sigma[i];
-        c->tau_neg[0] = -c->tau[i][j][0];
-        c->tau_neg[1] = -c->tau[i][j][1];
-        break;
-    }
-    case BL_SIGMA: {   // sigma_j = |r_j|^2; gamma'_j = <r_j, r_0> / sigma_j
-        const double s2 = res[2];
-        c->sigma[j] = s2;
-        if (!(s2 > 0.0) || !__builtin_isfinite(s2)) {
-            fail(1);
-            break;
-        }
-        c->gp[j][0] = res[0] / s2;
-        c->gp[j][1] = -res[1] / s2;
-        break;
-    }
-    case BL_MR: {      // gamma_l, gamma_j (back substitution), gamma''_j; the closing coefficients
-        double gpp[BL_MAXL + 1][2];
-        c->gm[l][0] = c->gp[l][0];
-        c->gm[l][1] = c->gp[l][1];
-        c->omega[0] = c->gm[l][0];
-        c->omega[1] = c->gm[l][1];
-        for (int jj = l - 1; jj >= 1; jj--) {
-            double sr = c->gp[jj][0], si = c->gp[jj][1];
-            for (int ii = jj + 1; ii <= l; ii++) {
-                double t[2];
-                bl_mul(c->tau[jj][ii], c->gm[ii], t);
-                sr -= t[0];
-                si -= t[1];
-            }
-            c->gm[jj][0] = sr;
-            c->gm[jj][1] = si;
-        }
-        for (int jj = 1; jj < l; jj++) {
-            double sr = c->gm[jj + 1][0], si = c->gm[jj + 1][1];
-            for (int ii = jj + 1; ii < l; ii++) {
-                double t[2];
-                bl_mul(c->tau[jj][ii], c->gm[ii + 1], t);
-                sr += t[0];
-                si += t[1];
-            }
-            gpp[jj][0] = sr;
-            gpp[jj][1] = si;
-        }
-        // x += gamma_1 r_0 + sum_{j<l} gamma''_j r_j; u_0 -= sum gamma_j u_j; r_0 -= sum gamma'_j r_j
-        c->cx[0][0] = c->gm[1][0];
-        c->cx[0][1] = c->gm[1][1];
-        for (int jj = 1; jj < l; jj++) {
-            c->cx[jj][0] = gpp[jj][0];
-            c->cx[jj][1] = gpp[jj][1];
-        }
-        for (int jj = 1; jj <= l; jj++) {
-            c->cu[jj - 1][0] = -c->gm[jj][0];
-            c->cu[jj - 1][1] = -c->gm[jj][1];
-            c->cr[jj - 1][0] = -c->gp[jj][0];
-            c->cr[jj - 1][1] = -c->gp[jj][1];
-        }
-        break;
-    }
-    case BL_RS2:       // |r_0|^2 after the cycle
-        c->rs2 = res[0];
-        if (!__builtin_isfinite(res[0])) fail(2);
-        break;
-    default: break;
+}
+template <class R> __device__ __forceinline__ double bl_norm(const CVec<R> &w) {
+    double a = 0.0;
+#pragma unroll
+    for (int q = 0; q < 3; q++) a += (double)w.re[q] * w.re[q] + (double)w.im[q] * w.im[q];
+    return a;
+}
+
+// sums of block partials too many for every block of the consumer (one block, fixed order)
+template <int NV> __global__ void k_bl_sum(const double *partial, int n, double *out, const int *stop) {
+    __shared__ double lds[16 * NV];
+    if (stop && *stop < 0) return;
+    double v[NV];
+    all_sums<NV>(partial, n, v, lds);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int k = 0; k < NV; k++) out[k] = v[k];
     }
 }
 
-__global__ void k_bl_summary(const BlCtl *c, BlSummary *o) {
+// Step j, first half: rho1 = <r~, r_j> (in: Re, Im first of each partial's nv),
+// beta = alpha rho1 / rho0, u_i = r_i - beta u_i; block row i <= j.
+template <int SF, class R>
+__global__ void __launch_bounds__(BL_BLOCK) k_bl_dir(VecList u, VecList r, BlCtl *c, Sums in, int nv, int j, size_t vh,
+                                                     size_t fb) {
+    __shared__ double lds[3 * BL_WAVES];
+    if (c->stop < 0) return;
+    double v[3];
+    if (nv == 3) {
+        all_sums<3>(in.p, in.n, v, lds);
+    } else {
+        double w[2];
+        all_sums<2>(in.p, in.n, w, lds);
+        v[0] = w[0];
+        v[1] = w[1];
+    }
+    const double rho1[2] = {v[0], v[1]};
+    const double *rho0 = j ? c->rho[j - 1] : c->rho_c, *alpha = j ? c->alpha[j - 1] : c->alpha_c;
+    const bool bad = bl_zero(rho0) || !bl_finite(rho1);
+    if (bl_first()) {
+        c->rho[j][0] = rho1[0];
+        c->rho[j][1] = rho1[1];
+        if (bad) {
+            c->broke = 1;
+            c->stop = -1;
+        }
+    }
+    if (bad) return;
+    double t[2], beta[2];
+    bl_mul(alpha, rho1, t);
+    bl_div(t, rho0, beta);
+    const R br = (R)-beta[0], bi = (R)-beta[1];
+    char *ui = u.p[blockIdx.y];
+    const char *ri = r.p[blockIdx.y];
+    for (size_t i = bl_tid(); i < 2 * vh; i += bl_stride()) {
+        const size_t h = i >= vh ? 1 : 0, s = i - h * vh;
+        const CVec<R> y = SpinorIO<SF, R>::load(ui + h * fb, vh, s), x = SpinorIO<SF, R>::load(ri + h * fb, vh, s);
+        CVec<R> o;
+#pragma unroll
+        for (int q = 0; q < 3; q++) {
+            o.re[q] = br * y.re[q] - bi * y.im[q] + x.re[q];
+            o.im[q] = br * y.im[q] + bi * y.re[q] + x.im[q];
+        }
+        (void)SpinorIO<SF, R>::store(ui + h * fb, vh, s, o);
+    }
+}
+
+// Step j, second half: gamma = <r~, u_{j+1}>, alpha = rho / gamma,
+// r_i -= alpha u_{i+1} (block row i <= j) and x += alpha u_0 (row j + 1).
+template <int SF, class R>
+__global__ void __launch_bounds__(BL_BLOCK) k_bl_res(VecList u, VecList r, char *x64, BlCtl *c, Sums in, int j,
+                                                     size_t vh, size_t fb, size_t fb64) {
+    __shared__ double lds[2 * BL_WAVES];
+    if (c->stop < 0) return;
+    double gam[2], alpha[2];
+    all_sums<2>(in.p, in.n, gam, lds);
+    const bool bad = bl_zero(gam) || !bl_finite(gam);
+    if (!bad) bl_div(c->rho[j], gam, alpha);
+    if (bl_first()) {
+        if (bad) {
+            c->broke = 1;
+            c->stop = -1;
+        } else {
+            c->alpha[j][0] = alpha[0];
+            c->alpha[j][1] = alpha[1];
+        }
+    }
+    if (bad) return;
+    const int k = blockIdx.y;
+    const double an[2] = {-alpha[0], -alpha[1]};
+    for (size_t i = bl_tid(); i < 2 * vh; i += bl_stride()) {
+        const size_t h = i >= vh ? 1 : 0, s = i - h * vh;
+        if (k <= j) {
+            CVec<R> o = SpinorIO<SF, R>::load(r.p[k] + h * fb, vh, s);
+            bl_axpy<R>(o, an, SpinorIO<SF, R>::load(u.p[k + 1] + h * fb, vh, s));
+            (void)SpinorIO<SF, R>::store(r.p[k] + h * fb, vh, s, o);
+        } else {
+            CVec<double> x = SpinorIO<SF_F64, double>::load(x64 + h * fb64, vh, s);
+            bl_xaxpy<R>(x, alpha, SpinorIO<SF, R>::load(u.p[0] + h * fb, vh, s));
+            SpinorIO<SF_F64, double>::store(x64 + h * fb64, vh, s, x);
+        }
+    }
+}
+
+// the scalars of a finished row i: sigma_i = |r_i|^2, gamma'_i = <r_i, r_0> / sigma_i, tau_ij =
+// <r_i, r_j> / sigma_i; v: <r_0, r_i>, |r_i|^2, <r_i, r_{i+1}>, ...  Returns false when sigma_i vanishes.
+__device__ __forceinline__ bool bl_row(BlCtl *c, const double *v, int i, int l) {
+    const double s2 = v[2];
+    const bool bad = !(s2 > 0.0) || !__builtin_isfinite(s2);
+    if (bl_first()) {
+        c->sigma[i] = s2;
+        if (bad) {
+            c->broke = 1;
+            c->stop = -1;
+        } else {
+            c->gp[i][0] = v[0] / s2;
+            c->gp[i][1] = -v[1] / s2;
+            for (int j = i + 1; j <= l; j++) {
+                c->tau[i][j][0] = v[3 + 2 * (j - i - 1)] / s2;
+                c->tau[i][j][1] = v[4 + 2 * (j - i - 1)] / s2;
+            }
+        }
+    }
+    return !bad;
+}
+
+// Row i of the modified Gram-Schmidt: r_j -= tau_{i-1,j} r_{i-1} for j = i..l
+// (i > 1; tau from the partials `in` of row i-1), then the dot products of row i
+// on the vectors in registers.  m = l - i + 1 vectors, at most M (the registers).
+// partial[block * (2 m + 1) + k]: <r_0, r_i>, |r_i|^2, <r_i, r_{i+1}>, ...
+template <int SF, class R, int M>
+__global__ void __launch_bounds__(BL_BLOCK) k_bl_mgs(VecList r, BlCtl *c, Sums in, int i, int l, size_t vh, size_t fb,
+                                                     double *partial) {
+    constexpr int NV = 2 * M + 1, NP = 2 * (M + 1) + 1;
+    __shared__ double lds[NP * BL_WAVES], tl[M][2];
+    if (c->stop < 0) return;
+    const int m = l - i + 1;
+    if (i > 1) {
+        // the previous row's m + 1 vectors left 2 m + 3 sums
+        if (in.n == 1) {
+            if (threadIdx.x < NP) lds[threadIdx.x] = threadIdx.x < 2 * m + 3 ? in.p[threadIdx.x] : 0.0;
+        } else {
+            // wave w sums the values k = w, w + BL_WAVES, ...
+            for (int k = threadIdx.x >> 6; k < 2 * m + 3; k += BL_WAVES) {
+                double t = 0.0;
+                for (int b = threadIdx.x & 63; b < in.n; b += 64) t += in.p[(size_t)b * (2 * m + 3) + k];
+                t = wave_sum(t);
+                if ((threadIdx.x & 63) == 0) lds[k] = t;
+            }
+        }
+        __syncthreads();
+        const bool ok = bl_row(c, lds, i - 1, l);
+        if (!ok) return;
+        if (threadIdx.x < M) {
+            const int k = threadIdx.x;
+            tl[k][0] = k < m ? -lds[3 + 2 * k] / lds[2] : 0.0;
+            tl[k][1] = k < m ? -lds[4 + 2 * k] / lds[2] : 0.0;
+        }
+        __syncthreads();
+    }
+    double acc[NV];
+#pragma unroll
+    for (int k = 0; k < NV; k++) acc[k] = 0.0;
+    for (size_t t = bl_tid(); t < 2 * vh; t += bl_stride()) {
+        const size_t h = t >= vh ? 1 : 0, s = t - h * vh;
+        CVec<R> v[M], prev;
+        const CVec<R> r0 = SpinorIO<SF, R>::load(r.p[0] + h * fb, vh, s);
+        if (i > 1) prev = SpinorIO<SF, R>::load(r.p[i - 1] + h * fb, vh, s);
+#pragma unroll
+        for (int k = 0; k < M; k++) v[k] = SpinorIO<SF, R>::load(r.p[min(i + k, l)] + h * fb, vh, s);
+        if (i > 1) {
+#pragma unroll
+            for (int k = 0; k < M; k++) {
+                if (k >= m) break;
+                bl_axpy<R>(v[k], tl[k], prev);
+                v[k] = SpinorIO<SF, R>::store(r.p[i + k] + h * fb, vh, s, v[k]);
+            }
+        }
+        bl_cdot<R>(acc, r0, v[0]);
+        acc[2] += bl_norm<R>(v[0]);
+#pragma unroll
+        for (int k = 1; k < M; k++) {
+            if (k >= m) break;
+            bl_cdot<R>(acc + 1 + 2 * k, v[0], v[k]);
+        }
+    }
+    __syncthreads();
+    block_sum<NV>(acc, lds);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int k = 0; k < NV; k++)
+            if (k < 2 * m + 1) partial[(size_t)blockIdx.x * (2 * m + 1) + k] = acc[k];
+    }
+}
+
+// The closing updates: gamma_l, gamma_j by back substitution, gamma''_j, then
+// (block row 0) u_0 -= sum gamma_j u_j and (row 1) x += gamma_1 r_0 + sum_{j<l}
+// gamma''_j r_j, r_0 -= sum gamma'_j r_j with <r~, r_0> and |r_0|^2 of the new one.
+template <int SF, class R>
+__global__ void __launch_bounds__(BL_BLOCK) k_bl_close(VecList u, VecList r, const char *rt, char *x64, BlCtl *c,
+                                                       Sums in, int l, size_t vh, size_t fb, size_t fb64,
+                                                       double *partial) {
+    __shared__ double lds[3 * BL_WAVES], gm[BL_MAXL + 1][2], cx[BL_MAXL][2], cu[BL_MAXL][2], cr[BL_MAXL][2];
+    if (c->stop < 0) return;
+    double v[3];
+    all_sums<3>(in.p, in.n, v, lds);   // <r_0, r_l>, |r_l|^2
+    if (!bl_row(c, v, l, l)) return;
+    if (threadIdx.x == 0) {
+        gm[l][0] = v[0] / v[2];
+        gm[l][1] = -v[1] / v[2];
+        cr[l - 1][0] = -gm[l][0];
+        cr[l - 1][1] = -gm[l][1];
+        for (int jj = l - 1; jj >= 1; jj--) {
+            double sr = c->gp[jj][0], si = c->gp[jj][1];
+            cr[jj - 1][0] = -sr;
+            cr[jj - 1][1] = -si;
+            for (int ii = jj + 1; ii <= l; ii++) {
+                double t[2];
+                bl_mul(c->tau[jj][ii], gm[ii], t);
+                sr -= t[0];
+                si -= t[1];
+            }
+            gm[jj][0] = sr;
+            gm[jj][1] = si;
+        }
+        cx[0][0] = gm[1][0];
+        cx[0][1] = gm[1][1];
+        for (int jj = 1; jj < l; jj++) {
+            double sr = gm[jj + 1][0], si = gm[jj + 1][1];
+            for (int ii = jj + 1; ii < l; ii++) {
+                double t[2];
+                bl_mul(c->tau[jj][ii], gm[ii + 1], t);
+                sr += t[0];
+                si += t[1];
+            }
+            cx[jj][0] = sr;
+            cx[jj][1] = si;
+        }
+        for (int jj = 1; jj <= l; jj++) {
+            cu[jj - 1][0] = -gm[jj][0];
+            cu[jj - 1][1] = -gm[jj][1];
+        }
+        if (bl_first()) {   // the next cycle's rho_0 = -omega rho, omega = gamma_l, and its alpha
+            double t[2];
+            bl_mul(gm[l], c->rho[l - 1], t);
+            c->rho_c[0] = -t[0];
+            c->rho_c[1] = -t[1];
+            c->alpha_c[0] = c->alpha[l - 1][0];
+            c->alpha_c[1] = c->alpha[l - 1][1];
+        }
+    }
+    __syncthreads();
+    double acc[3] = {0.0, 0.0, 0.0};
+    for (size_t i = bl_tid(); i < 2 * vh; i += bl_stride()) {
+        const size_t h = i >= vh ? 1 : 0, s = i - h * vh;
+        if (blockIdx.y == 0) {
+            CVec<R> o = SpinorIO<SF, R>::load(u.p[0] + h * fb, vh, s);
+#pragma unroll 4
+            for (int k = 1; k <= l; k++) bl_axpy<R>(o, cu[k - 1], SpinorIO<SF, R>::load(u.p[k] + h * fb, vh, s));
+            (void)SpinorIO<SF, R>::store(u.p[0] + h * fb, vh, s, o);
+            continue;
+        }
+        CVec<R> o = SpinorIO<SF, R>::load(r.p[0] + h * fb, vh, s);
+        const CVec<R> w = SpinorIO<SF, R>::load(rt + h * fb, vh, s);
+        CVec<double> x = SpinorIO<SF_F64, double>::load(x64 + h * fb64, vh, s);
+        bl_xaxpy<R>(x, cx[0], o);
+#pragma unroll 4
+        for (int k = 1; k <= l; k++) {
+            const CVec<R> y = SpinorIO<SF, R>::load(r.p[k] + h * fb, vh, s);
+            if (k < l) bl_xaxpy<R>(x, cx[k], y);
+            bl_axpy<R>(o, cr[k - 1], y);
+        }
+        SpinorIO<SF_F64, double>::store(x64 + h * fb64, vh, s, x);
+        const CVec<R> st = SpinorIO<SF, R>::store(r.p[0] + h * fb, vh, s, o);
+        bl_cdot<R>(acc, w, st);
+        acc[2] += bl_norm<R>(st);
+    }
+    if (blockIdx.y == 0) return;
+    block_sum<3>(acc, lds);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int k = 0; k < 3; k++) partial[3 * (size_t)blockIdx.x + k] = acc[k];
+    }
+}
+
+// r_0 = pack(r64) (and the shadow residual, at the start), with <r~, r_0> and
+// |r_0|^2 as the closing updates leave them
+template <int SF, class R>
+__global__ void __launch_bounds__(BL_BLOCK) k_bl_restart(char *r0, char *rt, int start, const char *r64, size_t vh,
+                                                         size_t fb, size_t fb64, double *partial) {
+    __shared__ double lds[3 * BL_WAVES];
+    double acc[3] = {0.0, 0.0, 0.0};
+    for (size_t i = bl_tid(); i < 2 * vh; i += bl_stride()) {
+        const size_t h = i >= vh ? 1 : 0, s = i - h * vh;
+        const CVec<double> t = SpinorIO<SF_F64, double>::load(r64 + h * fb64, vh, s);
+        const CVec<double> o = SpinorIO<SF, double>::store(r0 + h * fb, vh, s, t);
+        CVec<double> w = o;
+        if (start)
+            (void)SpinorIO<SF, double>::store(rt + h * fb, vh, s, t);
+        else
+            w = SpinorIO<SF, double>::load(rt + h * fb, vh, s);
+        bl_cdot<double>(acc, w, o);
+        acc[2] += bl_norm<double>(o);
+    }
+    block_sum<3>(acc, lds);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int k = 0; k < 3; k++) partial[3 * (size_t)blockIdx.x + k] = acc[k];
+    }
+}
+
+// The record of a cycle (op 0; in: the closing updates' partials), of a true
+// residual (op 1; in: |b - M x|^2 partials) or of |b|^2 (op 2), and what it
+// decides: a cycle that asks for a reliable update closes the cycles behind it,
+// a true residual opens them again.
+__global__ void k_bl_record(BlCtl *c, Sums in, int op, BlHost *host) {
+    __shared__ double lds[16 * 3];
+    const bool ran = op != 0 || c->stop == 0;
+    double v[3] = {0.0, 0.0, 0.0};
+    if (ran) {
+        if (op == 0) {
+            all_sums<3>(in.p, in.n, v, lds);
+        } else {
+            double w[1];
+            all_sums<1>(in.p, in.n, w, lds);
+            v[2] = w[0];
+        }
+    }
     if (threadIdx.x) return;
+    double lead = 0.0;
+    if (ran && op == 0) {
+        c->cycles++;
+        const double rs2 = v[2], rmax2 = fmax(c->rmax2, rs2);
+        c->rs2 = rs2;
+        c->rmax2 = rmax2;
+        const double t = fmax(c->delta2 * rmax2, c->tol2);
+        lead = t > 0.0 ? rs2 / t : 0.0;
+        if (!__builtin_isfinite(rs2)) {
+            c->broke = 2;
+            c->stop = -1;
+        } else if (rs2 < c->delta2 * rmax2 || rs2 <= c->tol2) {
+            c->stop = -2;
+        }
+    } else if (op == 1) {
+        c->rmax2 = v[2];
+        if (!c->broke) c->stop = 0;
+    }
+    const unsigned long long seq = c->seq + 1;
+    c->seq = seq;
+    BlRecord *o = &host->ring[seq % BL_RING];
     o->stop = c->stop;
     o->broke = c->broke;
-    o->rs2 = c->rs2;
+    o->cycles = c->cycles;
+    o->rs2 = v[2];
+    o->lead = lead;
+    __hip_atomic_store(&o->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // canonical lexicographic [V][3] <-> (even field, odd field) in F64 layout
@@ -373,72 +548,45 @@ struct Bl {
     const hisq_gauge *g64, *gs;
     double mass;
     hipStream_t st;
+    int l;
     int nbl;                      // grid of the vector kernels
-    double *partial;              // >= nbl * (2*BL_MAXK+1) and >= 2 * dslash partials
-    double *dres;                 // device results of a reduction (<= 2*BL_MAXK+1)
-    double *hres;                 // pinned host copy
+    double *dpart;                // partials of the operator (both parities, two each)
+    double *vpart[3];             // partials of the vector kernels: closing updates, Gram-Schmidt rows in turn
+    VecList r, u;
+    char *rt;
     DslashPlan plan_s{}, plan_64{};
-    int nb64 = 0;
+    int nb_s = 0, nb64 = 0;
     long matvecs = 0, f64apps = 0;
     double alg = 0.0;
-
     BlCtl *ctl = nullptr;         // device scalars
     const int *stopp = nullptr;   // &ctl->stop
+    BlHost *host = nullptr;
 
-    // y = a*y + sum c_k x_k (a, c: device addresses of complex values); with
-    // norm, |y|^2 is reduced into dres[0]
-    hisq_status combine(char *y, const double *a, bool read_y, const std::vector<const char *> &x, const double *c,
-                        bool norm) {
-        VecList xl;
-        memset(&xl, 0, sizeof(xl));
-        const int K = (int)x.size();
-        if (K > BL_MAXK) return set_error(HISQ_EINVAL, "bicgstab: too many vectors in one update");
-        for (int k = 0; k < K; k++) xl.p[k] = x[k];
-        double *pp = norm ? partial : nullptr;
-        HISQ_BL_DISPATCH(f.spinor, f.compute,
-                         hipLaunchKernelGGL((k_bl_combine<SFc, Rc>), dim3(nbl), dim3(BL_BLOCK), 0, st, y, a,
-                                            read_y ? 1 : 0, xl, c, K, vh, fb, pp, stopp));
+    // block partials for the next kernel: as they are when few, else added up in a launch
+    template <int NV> hisq_status sums(const double *partial, int n, bool guarded, Sums *out) {
+        *out = Sums{partial, n};
+        if (n * NV <= SUMS_DIRECT) return HISQ_OK;
+        hipLaunchKernelGGL((k_bl_sum<NV>), dim3(1), dim3(1024), 0, st, partial, n, ctl->red, guarded ? stopp : nullptr);
         HISQ_TRY_HIP(hipGetLastError());
-        alg += 2.0 * vh * spinor_site_bytes(f.spinor) * (K + (read_y ? 2 : 1));
-        if (norm) {
-            hipLaunchKernelGGL(k_bl_fin, dim3(1), dim3(BL_BLOCK), 0, st, partial, nbl, 1, dres);
-            HISQ_TRY_HIP(hipGetLastError());
+        *out = Sums{ctl->red, 1};
+        return HISQ_OK;
+    }
+    // for the Gram-Schmidt rows, whose blocks add up nv values with a wave each: up to 512
+    // blocks' tuples directly (a launch of its own took 10 us at 16^4)
+    hisq_status sums_n(const double *partial, int nv, Sums *out) {
+        *out = Sums{partial, nbl};
+        if (nbl <= 512 && nv > 3) return HISQ_OK;
+        switch (nv) {
+        case 3: return sums<3>(partial, nbl, true, out);
+        case 5: return sums<5>(partial, nbl, true, out);
+        case 7: return sums<7>(partial, nbl, true, out);
+        case 9: return sums<9>(partial, nbl, true, out);
+        case 11: return sums<11>(partial, nbl, true, out);
+        case 13: return sums<13>(partial, nbl, true, out);
+        case 15: return sums<15>(partial, nbl, true, out);
+        case 17: return sums<17>(partial, nbl, true, out);
+        default: return set_error(HISQ_EINVAL, "bicgstab: l out of range");
         }
-        return HISQ_OK;
-    }
-
-    // dres = (<x, y> re, im, |y|^2)
-    hisq_status dot(const char *x, const char *y) {
-        VecList xl;
-        memset(&xl, 0, sizeof(xl));
-        xl.p[0] = x;
-        HISQ_BL_DISPATCH(f.spinor, f.compute,
-                         hipLaunchKernelGGL((k_bl_dots<SFc, Rc>), dim3(nbl), dim3(BL_BLOCK), 0, st, xl, 1, y, vh, fb,
-                                            partial, stopp));
-        HISQ_TRY_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_bl_fin, dim3(1), dim3(BL_BLOCK), 0, st, partial, nbl, 3, dres);
-        HISQ_TRY_HIP(hipGetLastError());
-        alg += 2.0 * vh * spinor_site_bytes(f.spinor) * 2;
-        return HISQ_OK;
-    }
-
-    hisq_status step(int op, int i = 0, int j = 0, int l = 0) {
-        hipLaunchKernelGGL(k_bl_step, dim3(1), dim3(64), 0, st, ctl, dres, op, i, j, l);
-        HISQ_TRY_HIP(hipGetLastError());
-        return HISQ_OK;
-    }
-
-    hisq_status xupdate(char *x64, const std::vector<const char *> &v, const double *c) {
-        VecList vl;
-        memset(&vl, 0, sizeof(vl));
-        const int K = (int)v.size();
-        for (int k = 0; k < K; k++) vl.p[k] = v[k];
-        HISQ_BL_DISPATCH(f.spinor, f.compute,
-                         hipLaunchKernelGGL((k_bl_xupdate<SFc, Rc>), dim3(nbl), dim3(BL_BLOCK), 0, st, x64, vl, c, K,
-                                            vh, fb, fb64, stopp));
-        HISQ_TRY_HIP(hipGetLastError());
-        alg += 2.0 * vh * (96.0 + K * spinor_site_bytes(f.spinor));
-        return HISQ_OK;
     }
 
     DslashArgs dargs(const hisq_gauge *gg, int sf) const {
@@ -453,56 +601,125 @@ struct Bl {
         return a;
     }
 
-    // out = M in = 2m in + D in (sloppy): per output parity p, out_p = D in_q + 2m in_p
-    // (skipped after a breakdown in the cycle)
-    hisq_status matvec(char *out, const char *in) {
-        for (int p = 0; p < 2; p++) {
-            DslashArgs a = dargs(gs, f.spinor);
-            a.out = out + p * fb;
-            a.in = in + (1 - p) * fb;
-            a.x = in + p * fb;
-            a.a = 2.0 * mass;
-            a.parity = p;
-            a.guard = Guard{stopp, 0, 0};
-            HISQ_TRY_HIP(launch_dslash(a, f, plan_s, st, nullptr));
+    // out = M in = 2m in + D in (sloppy) on both parities, one launch: per output parity
+    // p, out_p = D in_q + 2m in_p (skipped after a breakdown in the cycle); dot: the
+    // partials of <r~, out>
+    hisq_status matvec(char *out, const char *in, bool dot) {
+        DslashArgs a = dargs(gs, f.spinor);
+        a.both = 1;
+        a.half = fb;
+        a.out = out;
+        a.in = in;
+        a.x = in;
+        a.a = 2.0 * mass;
+        a.guard = Guard{stopp, 0, 0};
+        if (dot) {
+            a.red = RED_CDOT;
+            a.z = rt;
+            a.partial = dpart;
         }
-        matvecs++;
-        alg += 2.0 * vh * (dslash_link_bytes(gs) + 3.0 * spinor_site_bytes(f.spinor));
+        HISQ_TRY_HIP(launch_dslash(a, f, plan_s, st, nullptr));
+        alg += 2.0 * vh * (dslash_link_bytes(gs) + (dot ? 4.0 : 3.0) * spinor_site_bytes(f.spinor));
         return HISQ_OK;
     }
 
-    // r64 = b64 - M x64 with the FP64 operator; returns |r64|^2
+    template <int M> hisq_status mgs_row(int i, const Sums &in, double *out) {
+        HISQ_BL_DISPATCH(f.spinor, f.compute,
+                         hipLaunchKernelGGL((k_bl_mgs<SFc, Rc, M>), dim3(nbl), dim3(BL_BLOCK), 0, st, r, ctl, in, i, l,
+                                            vh, fb, out));
+        HISQ_TRY_HIP(hipGetLastError());
+        return HISQ_OK;
+    }
+
+    // one cycle: l BiCG steps, the minimal-residual step by modified Gram-Schmidt, the record
+    hisq_status enq_cycle(char *x64) {
+        const double bs = spinor_site_bytes(f.spinor);
+        Sums in;
+        for (int j = 0; j < l; j++) {
+            const int nv = j ? 2 : 3;
+            if (j)
+                HISQ_TRY(sums<2>(dpart, 2 * nb_s, true, &in));
+            else
+                HISQ_TRY(sums<3>(vpart[0], nbl, true, &in));
+            HISQ_BL_DISPATCH(f.spinor, f.compute,
+                             hipLaunchKernelGGL((k_bl_dir<SFc, Rc>), dim3(nbl, j + 1), dim3(BL_BLOCK), 0, st, u, r, ctl,
+                                                in, nv, j, vh, fb));
+            HISQ_TRY_HIP(hipGetLastError());
+            HISQ_TRY(matvec(u.p[j + 1], u.p[j], true));
+            HISQ_TRY(sums<2>(dpart, 2 * nb_s, true, &in));
+            HISQ_BL_DISPATCH(f.spinor, f.compute,
+                             hipLaunchKernelGGL((k_bl_res<SFc, Rc>), dim3(nbl, j + 2), dim3(BL_BLOCK), 0, st, u, r, x64,
+                                                ctl, in, j, vh, fb, fb64));
+            HISQ_TRY_HIP(hipGetLastError());
+            HISQ_TRY(matvec(r.p[j + 1], r.p[j], j + 1 < l));
+            alg += 2.0 * vh * ((j + 1) * 6.0 * bs + bs + 96.0);
+        }
+        in = Sums{nullptr, 0};
+        for (int i = 1; i <= l; i++) {
+            const int m = l - i + 1;
+            double *out = vpart[1 + (i & 1)];
+            if (m == 1)
+                HISQ_TRY(mgs_row<1>(i, in, out));
+            else if (m == 2)
+                HISQ_TRY(mgs_row<2>(i, in, out));
+            else if (m == 3)
+                HISQ_TRY(mgs_row<3>(i, in, out));
+            else if (m == 4)
+                HISQ_TRY(mgs_row<4>(i, in, out));
+            else
+                HISQ_TRY(mgs_row<BL_MAXL>(i, in, out));
+            HISQ_TRY(sums_n(out, 2 * m + 1, &in));
+            alg += 2.0 * vh * bs * (i > 1 ? 2.0 + 2.0 * m : 1.0 + m);
+        }
+        HISQ_BL_DISPATCH(f.spinor, f.compute,
+                         hipLaunchKernelGGL((k_bl_close<SFc, Rc>), dim3(nbl, 2), dim3(BL_BLOCK), 0, st, u, r, rt, x64,
+                                            ctl, in, l, vh, fb, fb64, vpart[0]));
+        HISQ_TRY_HIP(hipGetLastError());
+        alg += 2.0 * vh * (bs * (2.0 * l + 5.0) + 96.0);
+        HISQ_TRY(record(Sums{vpart[0], nbl}, 0));
+        return HISQ_OK;
+    }
+
+    hisq_status record(const Sums &in, int op) {
+        hipLaunchKernelGGL(k_bl_record, dim3(1), dim3(1024), 0, st, ctl, in, op, host);
+        HISQ_TRY_HIP(hipGetLastError());
+        return HISQ_OK;
+    }
+    hisq_status wait(unsigned long long seq, BlRecord *out) {
+        return wait_record(&host->ring[seq % BL_RING], seq, st, out);
+    }
+
+    // r64 = b64 - M x64 with the FP64 operator (both parities in one launch); *r2 = |r64|^2
     hisq_status residual64(char *r64, const char *x64, const char *b64, double *r2) {
         const hisq_fmt f64 = {HISQ_GAUGE_F64, HISQ_SPINOR_F64, 64};
-        for (int p = 0; p < 2; p++) {
-            DslashArgs a = dargs(g64, SF_F64);
-            a.out = r64 + p * fb64;
-            a.in = x64 + (1 - p) * fb64;
-            a.x = x64 + p * fb64;
-            a.y = b64 + p * fb64;
-            a.b = -1.0;
-            a.a = -2.0 * mass;
-            a.c = 1.0;
-            a.parity = p;
-            a.red = RED_NORM;
-            a.partial = partial + (size_t)p * nb64;
-            a.pstride = 0;
-            HISQ_TRY_HIP(launch_dslash(a, f64, plan_64, st, nullptr));
-        }
+        DslashArgs a = dargs(g64, SF_F64);
+        a.both = 1;
+        a.half = fb64;
+        a.out = r64;
+        a.in = x64;
+        a.x = x64;
+        a.y = b64;
+        a.b = -1.0;
+        a.a = -2.0 * mass;
+        a.c = 1.0;
+        a.red = RED_NORM;
+        a.partial = dpart;
+        HISQ_TRY_HIP(launch_dslash(a, f64, plan_64, st, nullptr));
         f64apps++;
         alg += 2.0 * vh * (dslash_link_bytes(g64) + 4.0 * 48);
-        hipLaunchKernelGGL(k_bl_fin, dim3(1), dim3(BL_BLOCK), 0, st, partial, 2 * nb64, 1, dres);
-        HISQ_TRY_HIP(hipGetLastError());
-        HISQ_TRY_HIP(hipMemcpyAsync(hres, dres, sizeof(double), hipMemcpyDeviceToHost, st));
-        HISQ_TRY_HIP(hipStreamSynchronize(st));
-        *r2 = hres[0];
+        HISQ_TRY(record(Sums{dpart, 2 * nb64}, 1));
+        BlRecord rec;
+        HISQ_TRY(wait(++host->launched, &rec));
+        *r2 = rec.rs2;
         return HISQ_OK;
     }
 
-    hisq_status to_sloppy(char *dst, const char *src64) {
-        for (int p = 0; p < 2; p++)
-            HISQ_TRY_HIP(launch_spinor_convert(dst + p * fb, f.spinor, src64 + p * fb64, SF_F64, vh, st));
-        alg += 2.0 * vh * (48.0 + spinor_site_bytes(f.spinor));
+    hisq_status restart(const char *r64, bool start) {
+        HISQ_BL_DISPATCH(f.spinor, f.compute,
+                         hipLaunchKernelGGL((k_bl_restart<SFc, Rc>), dim3(nbl), dim3(BL_BLOCK), 0, st, r.p[0], rt,
+                                            start ? 1 : 0, r64, vh, fb, fb64, vpart[0]));
+        HISQ_TRY_HIP(hipGetLastError());
+        alg += 2.0 * vh * (48.0 + 2.0 * spinor_site_bytes(f.spinor));
         return HISQ_OK;
     }
 };
@@ -515,13 +732,14 @@ inline size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
 struct BlDev {
     hipStream_t stream = nullptr;
     hipEvent_t ev = nullptr;
+    BlHost *host = nullptr;   // pinned: the records the device leaves
     std::mutex mu;
 };
 BlDev g_bldev[64];
 
 struct BlLayout {
-    size_t fb, fb64, part_doubles, total;
-    size_t off_part, off_dres, off_ctl, off_x64, off_b64, off_r64, off_vec;
+    size_t fb, fb64, dpart, vpart, part_doubles, total;
+    size_t off_part, off_ctl, off_x64, off_b64, off_r64, off_vec;
     int nvec;
 };
 
@@ -530,13 +748,14 @@ BlLayout bl_layout(const Geom &g, int l, const hisq_fmt &f) {
     L.fb = al256(spinor_field_bytes(g.vh, f.spinor));
     L.fb64 = al256(spinor_field_bytes(g.vh, SF_F64));
     const size_t nbl = (size_t)blas_blocks(2 * (size_t)g.vh);
-    L.part_doubles = std::max(nbl * (2 * BL_MAXK + 1), 2 * dslash_max_blocks(g));
+    // the operator's partials: two per block of the largest one-system launch, both parities
+    L.dpart = 4 * (size_t)std::max(dslash_blocks(g.vh, 128), 8 * g.T * slab_tiles(g, 1, 128));
+    L.vpart = nbl * (2 * BL_MAXL + 1);
+    L.part_doubles = L.dpart + 3 * L.vpart;
     L.nvec = 2 * (l + 1) + 1;   // r_0..r_l, u_0..u_l, shadow
     size_t off = 0;
     L.off_part = off;
     off += al256(L.part_doubles * sizeof(double));
-    L.off_dres = off;
-    off += al256(64 * sizeof(double));
     L.off_ctl = off;
     off += al256(sizeof(BlCtl));
     L.off_x64 = off;
@@ -612,33 +831,36 @@ extern "C" hisq_status hisq_bicgstab_solve(double *x, const double *b, const his
         HISQ_TRY_HIP(hipStreamCreateWithFlags(&dv.stream, hipStreamNonBlocking));
         HISQ_TRY_HIP(hipEventCreateWithFlags(&dv.ev, hipEventDisableTiming));
     }
+    if (!dv.host) {
+        HISQ_TRY_HIP(hipHostMalloc((void **)&dv.host, sizeof(BlHost), hipHostMallocCoherent));
+        memset(dv.host, 0, sizeof(BlHost));
+    }
     HISQ_TRY_HIP(hipEventRecord(dv.ev, (hipStream_t)stream));
     HISQ_TRY_HIP(hipStreamWaitEvent(dv.stream, dv.ev, 0));
     B.st = dv.stream;
+    B.host = dv.host;
+    B.l = l;
     B.nbl = blas_blocks(2 * (size_t)g.vh);
-    B.partial = (double *)(w + L.off_part);
-    B.dres = (double *)(w + L.off_dres);
+    B.dpart = (double *)(w + L.off_part);
+    for (int k = 0; k < 3; k++) B.vpart[k] = B.dpart + L.dpart + k * L.vpart;
     B.ctl = (BlCtl *)(w + L.off_ctl);
     B.stopp = &B.ctl->stop;
-    HISQ_TRY_HIP(hipHostMalloc((void **)&B.hres, 64 * sizeof(double), hipHostMallocDefault));
-    struct Free {
-        double *p;
-        ~Free() { (void)hipHostFree(p); }
-    } free_hres{B.hres};
     char *x64 = w + L.off_x64, *b64 = w + L.off_b64, *r64 = w + L.off_r64;
-    std::vector<char *> r(l + 1), u(l + 1);
+    memset(&B.r, 0, sizeof(B.r));
+    memset(&B.u, 0, sizeof(B.u));
     for (int i = 0; i <= l; i++) {
-        r[i] = w + L.off_vec + (size_t)i * 2 * L.fb;
-        u[i] = w + L.off_vec + (size_t)(l + 1 + i) * 2 * L.fb;
+        B.r.p[i] = w + L.off_vec + (size_t)i * 2 * L.fb;
+        B.u.p[i] = w + L.off_vec + (size_t)(l + 1 + i) * 2 * L.fb;
     }
-    char *rt = w + L.off_vec + (size_t)(2 * l + 2) * 2 * L.fb;
+    B.rt = w + L.off_vec + (size_t)(2 * l + 2) * 2 * L.fb;
 
     // launch shapes (autotuned on first use)
     {
         DslashArgs ps = B.dargs(gs, sloppy.spinor);
-        ps.out = r[1];
-        ps.in = r[0] + L.fb;
+        ps.out = B.r.p[1];
+        ps.in = B.r.p[0] + L.fb;
         B.plan_s = dslash_plan(sloppy, g, 1, &ps, B.st);
+        B.nb_s = dslash_tile_blocks(g, B.plan_s.tile[0]);
         const hisq_fmt f64 = {HISQ_GAUGE_F64, HISQ_SPINOR_F64, 64};
         DslashArgs p64 = B.dargs(g64, SF_F64);
         p64.out = r64;
@@ -650,24 +872,31 @@ extern "C" hisq_status hisq_bicgstab_solve(double *x, const double *b, const his
     hipLaunchKernelGGL(k_bl_split, dim3(B.nbl), dim3(BL_BLOCK), 0, B.st, x64, x, g, L.fb64);
     hipLaunchKernelGGL(k_bl_split, dim3(B.nbl), dim3(BL_BLOCK), 0, B.st, b64, b, g, L.fb64);
     HISQ_TRY_HIP(hipGetLastError());
-    // |b|^2 in FP64 (both halves' block partials, then one fixed-order sum)
-    double b2 = 0.0;
-    {
-        int nbe = 0, nbo = 0;
-        HISQ_TRY_HIP(launch_norm2_f64(b64, g.vh, B.partial, &nbe, B.st));
-        HISQ_TRY_HIP(launch_norm2_f64(b64 + L.fb64, g.vh, B.partial + nbe, &nbo, B.st));
-        hipLaunchKernelGGL(k_bl_fin, dim3(1), dim3(BL_BLOCK), 0, B.st, B.partial, nbe + nbo, 1, B.dres);
-        HISQ_TRY_HIP(hipGetLastError());
-        HISQ_TRY_HIP(hipMemcpyAsync(B.hres, B.dres, sizeof(double), hipMemcpyDeviceToHost, B.st));
+    {   // rho0 = 1, alpha = 0, omega = 1 (entering a cycle: -omega rho0); tol2 becomes tol^2 |b|^2 with |b|^2
+        BlCtl c0;
+        memset(&c0, 0, sizeof(c0));
+        c0.rho_c[0] = -1.0;
+        c0.delta2 = q.delta > 0 ? q.delta * q.delta : 0.0;
+        c0.tol2 = tol * tol;
+        c0.seq = B.host->launched;
+        HISQ_TRY_HIP(hipMemcpyAsync(B.ctl, &c0, sizeof(c0), hipMemcpyHostToDevice, B.st));
         HISQ_TRY_HIP(hipStreamSynchronize(B.st));
-        b2 = B.hres[0];
+    }
+    double b2 = 0.0;
+    {   // both halves' block partials, then one fixed-order sum
+        int nbe = 0, nbo = 0;
+        HISQ_TRY_HIP(launch_norm2_f64(b64, g.vh, B.vpart[0], &nbe, B.st));
+        HISQ_TRY_HIP(launch_norm2_f64(b64 + L.fb64, g.vh, B.vpart[0] + nbe, &nbo, B.st));
+        HISQ_TRY(B.record(Sums{B.vpart[0], nbe + nbo}, 2));
+        BlRecord rec;
+        HISQ_TRY(B.wait(++B.host->launched, &rec));
+        b2 = rec.rs2;
     }
     double r2 = 0.0;
     HISQ_TRY(B.residual64(r64, x64, b64, &r2));
     hisq_status status = HISQ_OK;
     long rus = 0;
     const double tol2 = tol * tol * b2;
-    const double delta2 = q.delta > 0 ? q.delta * q.delta : 0.0;
     if (b2 == 0.0) {   // x = 0
         HISQ_TRY_HIP(hipMemsetAsync(x, 0, 2 * (size_t)g.vh * 6 * sizeof(double), B.st));
         HISQ_TRY_HIP(hipStreamSynchronize(B.st));
@@ -675,116 +904,83 @@ extern "C" hisq_status hisq_bicgstab_solve(double *x, const double *b, const his
         return HISQ_OK;
     }
     if (r2 > tol2) {
-        HISQ_TRY(B.to_sloppy(r[0], r64));
-        HISQ_TRY(B.to_sloppy(rt, r64));
-        HISQ_TRY_HIP(hipMemsetAsync(u[0], 0, 2 * L.fb, B.st));
-        {   // rho0 = 1, alpha = 0, omega = 1
-            BlCtl c0;
-            memset(&c0, 0, sizeof(c0));
-            c0.one[0] = c0.rho0[0] = c0.omega[0] = 1.0;
-            HISQ_TRY_HIP(hipMemcpyAsync(B.ctl, &c0, sizeof(c0), hipMemcpyHostToDevice, B.st));
-            HISQ_TRY_HIP(hipStreamSynchronize(B.st));
-        }
-        BlCtl *c = B.ctl;
-        // one cycle: l BiCG steps, then the minimal-residual step by modified Gram-Schmidt
-        auto enq_cycle = [&]() -> hisq_status {
-            HISQ_TRY(B.step(BL_START));
-            for (int j = 0; j < l; j++) {
-                HISQ_TRY(B.dot(rt, r[j]));
-                HISQ_TRY(B.step(BL_RHO));
-                for (int i = 0; i <= j; i++) HISQ_TRY(B.combine(u[i], c->beta_neg, true, {r[i]}, c->one, false));
-                HISQ_TRY(B.matvec(u[j + 1], u[j]));
-                HISQ_TRY(B.dot(rt, u[j + 1]));
-                HISQ_TRY(B.step(BL_GAM));
-                for (int i = 0; i <= j; i++) HISQ_TRY(B.combine(r[i], c->one, true, {u[i + 1]}, c->alpha_neg, false));
-                HISQ_TRY(B.matvec(r[j + 1], r[j]));
-                HISQ_TRY(B.xupdate(x64, {u[0]}, c->alpha));
-            }
-            for (int j = 1; j <= l; j++) {
-                for (int i = 1; i < j; i++) {
-                    HISQ_TRY(B.dot(r[i], r[j]));
-                    HISQ_TRY(B.step(BL_TAU, i, j));
-                    HISQ_TRY(B.combine(r[j], c->one, true, {r[i]}, c->tau_neg, false));
-                }
-                HISQ_TRY(B.dot(r[0], r[j]));                  // <r_0, r_j> and |r_j|^2
-                HISQ_TRY(B.step(BL_SIGMA, 0, j));
-            }
-            HISQ_TRY(B.step(BL_MR, 0, 0, l));
-            std::vector<const char *> vx{r[0]}, vr, vu;
-            for (int j = 1; j < l; j++) vx.push_back(r[j]);
-            for (int j = 1; j <= l; j++) {
-                vr.push_back(r[j]);
-                vu.push_back(u[j]);
-            }
-            HISQ_TRY(B.xupdate(x64, vx, &c->cx[0][0]));
-            HISQ_TRY(B.combine(u[0], c->one, true, vu, &c->cu[0][0], false));
-            HISQ_TRY(B.combine(r[0], c->one, true, vr, &c->cr[0][0], true));
-            HISQ_TRY(B.step(BL_RS2));
-            hipLaunchKernelGGL(k_bl_summary, dim3(1), dim3(64), 0, B.st, c, (BlSummary *)B.dres);
-            HISQ_TRY_HIP(hipGetLastError());
-            return HISQ_OK;
-        };
+        HISQ_TRY(B.restart(r64, true));
+        HISQ_TRY_HIP(hipMemsetAsync(B.u.p[0], 0, 2 * L.fb, B.st));
         hipGraphExec_t exec = nullptr;
         struct ExecFree {
             hipGraphExec_t *e;
+            hipStream_t st;
             ~ExecFree() {
+                (void)hipStreamSynchronize(st);   // a cycle behind the last one may still be returning from its guards
                 if (*e) (void)hipGraphExecDestroy(*e);
             }
-        } exec_free{&exec};
+        } exec_free{&exec, B.st};
         double cyc_alg = 0.0;
-        double rmax2 = r2;
+        int inflight = 0, cycles = 0;
+        Pace pace;
         while (status == HISQ_OK) {
-            if (B.matvecs >= q.maxiter) {
+            // the next cycle is enqueued before the running one is read, unless
+            // that one is about to ask for a reliable update
+            while (inflight < 2 && (inflight == 0 || pace.left > (double)inflight) &&
+                   B.matvecs + 2L * l * inflight < q.maxiter) {
+                const double a0 = B.alg;
+                if (q.use_graph) {
+                    if (!exec) {
+                        hipGraph_t gr = nullptr;
+                        HISQ_TRY_HIP(hipStreamBeginCapture(B.st, hipStreamCaptureModeThreadLocal));
+                        hisq_status cs = B.enq_cycle(x64);
+                        hipError_t e = hipStreamEndCapture(B.st, &gr);
+                        if (cs != HISQ_OK) {
+                            if (gr) (void)hipGraphDestroy(gr);
+                            return cs;
+                        }
+                        HISQ_TRY_HIP(e);
+                        e = hipGraphInstantiate(&exec, gr, nullptr, nullptr, 0);
+                        (void)hipGraphDestroy(gr);
+                        HISQ_TRY_HIP(e);
+                        cyc_alg = B.alg - a0;
+                    }
+                    HISQ_TRY_HIP(hipGraphLaunch(exec, B.st));
+                } else {
+                    HISQ_TRY(B.enq_cycle(x64));
+                    cyc_alg = B.alg - a0;
+                }
+                B.alg = a0;
+                B.host->launched++;
+                inflight++;
+            }
+            if (inflight == 0) {
                 status = set_error(HISQ_ENOCONV, "bicgstab: no convergence in %ld operator applications", B.matvecs);
                 break;
             }
-            if (q.use_graph) {
-                if (!exec) {
-                    const double a0 = B.alg;
-                    hipGraph_t gr = nullptr;
-                    HISQ_TRY_HIP(hipStreamBeginCapture(B.st, hipStreamCaptureModeThreadLocal));
-                    hisq_status cs = enq_cycle();
-                    hipError_t e = hipStreamEndCapture(B.st, &gr);
-                    if (cs != HISQ_OK) {
-                        if (gr) (void)hipGraphDestroy(gr);
-                        return cs;
-                    }
-                    HISQ_TRY_HIP(e);
-                    e = hipGraphInstantiate(&exec, gr, nullptr, nullptr, 0);
-                    (void)hipGraphDestroy(gr);
-                    HISQ_TRY_HIP(e);
-                    cyc_alg = B.alg - a0;
-                    B.alg = a0;
-                    B.matvecs -= 2 * l;
-                }
-                HISQ_TRY_HIP(hipGraphLaunch(exec, B.st));
-                B.alg += cyc_alg;
+            BlRecord rec;
+            HISQ_TRY(B.wait(B.host->launched - (unsigned long long)inflight + 1, &rec));
+            inflight--;
+            if (rec.cycles > cycles) {
+                cycles = rec.cycles;
                 B.matvecs += 2 * l;
-            } else {
-                HISQ_TRY(enq_cycle());
+                B.alg += cyc_alg;
             }
-            HISQ_TRY_HIP(hipMemcpyAsync(B.hres, B.dres, sizeof(BlSummary), hipMemcpyDeviceToHost, B.st));
-            HISQ_TRY_HIP(hipStreamSynchronize(B.st));
-            BlSummary sum;
-            memcpy(&sum, B.hres, sizeof(sum));
-            if (sum.broke == 2) {
+            if (rec.broke == 2) {
                 status = set_error(HISQ_EBREAKDOWN, "bicgstab: non-finite residual");
                 break;
             }
-            if (sum.broke) {
+            if (rec.broke) {
                 status = set_error(HISQ_EBREAKDOWN, "bicgstab: breakdown after %ld operator applications", B.matvecs);
                 break;
             }
-            const double rs2 = sum.rs2;
-            rmax2 = std::max(rmax2, rs2);
+            Status s;
+            s.lead = rec.lead;
+            s.k = cycles;
+            pace.update(s);
+            if (rec.stop == 0) continue;
             // ---- reliable update ----
-            if (rs2 < delta2 * rmax2 || rs2 <= tol2) {
-                HISQ_TRY(B.residual64(r64, x64, b64, &r2));
-                rus++;
-                if (r2 <= tol2) break;
-                HISQ_TRY(B.to_sloppy(r[0], r64));
-                rmax2 = r2;
-            }
+            inflight = 0;   // the cycle behind, if any, does nothing; its record is skipped
+            pace.reset();
+            HISQ_TRY(B.residual64(r64, x64, b64, &r2));
+            rus++;
+            if (r2 <= tol2) break;
+            HISQ_TRY(B.restart(r64, false));
         }
     }
     if (status == HISQ_ENOCONV || status == HISQ_EBREAKDOWN) {

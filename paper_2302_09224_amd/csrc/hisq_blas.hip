@@ -8,11 +8,9 @@
 // and are taken on the values as stored (after packing), which is what the
 // next iteration will read.
 #include <algorithm>
-#include <chrono>
 #include <cstring>
 #include <map>
 #include <mutex>
-#include <thread>
 #include <utility>
 
 #include "hisq_internal.h"
@@ -1199,27 +1197,6 @@ hisq_status solver_host_alloc(SolverHost **h) {
 hipError_t launch_status(SolverCtrl *c, SolverHost *h, int nrhs, hipStream_t st) {
     hipLaunchKernelGGL(k_status, dim3(1), dim3(64), 0, st, c, h, nrhs);
     return hipGetLastError();
-}
-
-hisq_status wait_status(SolverHost *h, unsigned long long seq, hipStream_t st, Status *out) {
-    const Status *s = &h->ring[seq % STATUS_RING];
-    const auto t0 = std::chrono::steady_clock::now();
-    for (long n = 1; __atomic_load_n(&s->seq, __ATOMIC_ACQUIRE) != seq; n++) {
-        if (n % 256) {
-            __builtin_ia32_pause();
-            continue;
-        }
-        // a unit takes 0.1 ms (small lattices) to tens of ms; the stream's own state tells of an error
-        if (std::chrono::steady_clock::now() - t0 < std::chrono::milliseconds(1)) continue;
-        const hipError_t e = hipStreamQuery(st);
-        if (e == hipSuccess && __atomic_load_n(&s->seq, __ATOMIC_ACQUIRE) != seq)
-            return set_error(HISQ_EHIP, "solver status record %llu missing after its stream drained", seq);
-        if (e != hipSuccess && e != hipErrorNotReady)
-            return set_error(HISQ_EHIP, "solver stream: %s", hipGetErrorString(e));
-        std::this_thread::sleep_for(std::chrono::microseconds(20));
-    }
-    *out = *s;
-    return HISQ_OK;
 }
 
 hipError_t launch_spinor_pack(char *dst, const double *src, size_t n, int sf, hipStream_t st) {

@@ -20,7 +20,7 @@
 // against occupancy; the autotuner picks it per triplet and lattice.
 //
 // Right-hand-side blocks (Sec. 1, "Block solvers"): a lane accumulates NR
-// right-hand sides for one site, and rg lanes (adjacent, same wavefront) share
+// right-hand sides for one site, and rg lanes (of the same wavefront) share
 // a site and cover rg*NR right-hand sides, so each link is fetched from memory
 // once per block of right-hand sides while the register footprint per lane
 // stays bounded.  Single right-hand side: NR = rg = 1.
@@ -637,7 +637,8 @@ __device__ __forceinline__ bool colvalid(const DslashArgs &A, int k, int ncol) {
 // the optional reduction.
 template <int SF, class R, int NR, bool RED, class ColF>
 __device__ __forceinline__ void site_epilogue(const DslashArgs &A, int s, ColF col, unsigned live,
-                                              const R (&acoef)[NR], CVec<R> (&acc)[NR], double (&red)[NR]) {
+                                              const R (&acoef)[NR], CVec<R> (&acc)[NR], double (&red)[NR],
+                                              double &redi) {
     const size_t fs = A.field_stride;
     const size_t vh = (size_t)A.g.vh;
     const R b = (R)A.b, cc = (R)A.c;
@@ -675,6 +676,13 @@ __device__ __forceinline__ void site_epilogue(const DslashArgs &A, int s, ColF c
 #pragma unroll
                 for (int c = 0; c < 3; c++)
                     red[j] += (double)xv.re[c] * (double)o.re[c] + (double)xv.im[c] * (double)o.im[c];
+            } else if (NR == 1 && A.red == RED_CDOT) {
+                const CVec<R> zv = SpinorIO<SF, R>::load(A.z + off, vh, s);
+#pragma unroll
+                for (int c = 0; c < 3; c++) {
+                    red[j] += (double)zv.re[c] * (double)o.re[c] + (double)zv.im[c] * (double)o.im[c];
+                    redi += (double)zv.re[c] * (double)o.im[c] - (double)zv.im[c] * (double)o.re[c];
+                }
             } else {
 #pragma unroll
                 for (int c = 0; c < 3; c++)
@@ -689,7 +697,7 @@ __device__ __forceinline__ void site_epilogue(const DslashArgs &A, int s, ColF c
 // store, and the optional reduction into red[].
 template <int GF, int SF, class R, int NR, int STAGE, bool RED, int LR>
 __device__ __forceinline__ void dslash_site(const DslashArgs &A, int s, int c0, int cs, unsigned live,
-                                            const R (&acoef)[NR], double (&red)[NR]) {
+                                            const R (&acoef)[NR], double (&red)[NR], double &redi) {
     const Geom &g = A.g;
     const size_t fs = A.field_stride;
     const size_t vh = (size_t)g.vh;
@@ -820,7 +828,7 @@ __device__ __forceinline__ void dslash_site(const DslashArgs &A, int s, int c0, 
         apply_stage(k * SB, k % NBUF);
         if (PIPE) __builtin_amdgcn_sched_barrier(0);
     }
-    site_epilogue<SF, R, NR, RED>(A, s, [&](int j) { return colmap(A, c0 + j * cs); }, live, acoef, acc, red);
+    site_epilogue<SF, R, NR, RED>(A, s, [&](int j) { return colmap(A, c0 + j * cs); }, live, acoef, acc, red, redi);
 }
 
 // Batched sites on the matrix cores (STAGE == MFMA_STAGE, FP32 compute, four
@@ -1003,7 +1011,9 @@ __device__ __forceinline__ void dslash_site_mfma(const DslashArgs &A, int s, boo
             acc[m].im[c] = acc_im[m][c];
         }
     }
-    site_epilogue<SF, float, NR, RED>(A, s, [&](int m) { return colmap(A, rhs0 + 4 * m + li); }, lv, acoef, acc, red);
+    double unused = 0.0;   // no RED_CDOT here
+    site_epilogue<SF, float, NR, RED>(A, s, [&](int m) { return colmap(A, rhs0 + 4 * m + li); }, lv, acoef, acc, red,
+                                      unused);
 }
 
 // GUARD: launched inside a solver's block of iterations (may return at once);
@@ -1013,7 +1023,19 @@ template <int GF, int SF, class R, int NR, int STAGE, bool RED, bool GUARD, int 
 __global__ void __launch_bounds__(256) k_dslash(DslashArgs A, int rhs0, int rg, int sweep) {
     __shared__ double lds[64];
     if (GUARD && !A.guard.pass()) return;
+    if constexpr (GUARD && NR == 1) {
+        if (A.both) {
+            const int p = blockIdx.y;
+            A.parity = p;
+            A.out += p * A.half;
+            A.in += (1 - p) * A.half;
+            if (A.x) A.x += p * A.half;
+            if (A.y) A.y += p * A.half;
+            if (A.z) A.z += p * A.half;
+        }
+    }
     const Geom g = A.g;
+    double redi = 0.0;
     double red[NR];
 #pragma unroll
     for (int j = 0; j < NR; j++) red[j] = 0.0;
@@ -1028,7 +1050,8 @@ __global__ void __launch_bounds__(256) k_dslash(DslashArgs A, int rhs0, int rg, 
     // group, so that each quad of lanes reads one 64-byte piece of one column.
     // With the groups of a site on adjacent lanes a quad's 16-byte loads fell on
     // two (rg 2) or four columns and took as many passes of the address unit:
-    // COALESCE_FIGURES
+    // at 32^3x64 with 16 INT20 right-hand sides, nr 4, 618 -> 507 us;
+    // at 24^3x32 with 12, 124 -> 90 us (the fastest shape was nr 8, rg 2 at 558 and 97 us).
     // The matrix-core path needs a site's four lanes side by side.
     constexpr bool ADJ = STAGE == MFMA_STAGE;
     const int lrg = __builtin_ctz((unsigned)rg), lane = threadIdx.x & 63, lw = 6 - lrg;
@@ -1096,7 +1119,7 @@ __global__ void __launch_bounds__(256) k_dslash(DslashArgs A, int rhs0, int rg, 
         // every lane takes part in the matrix instructions of its site's block
         dslash_site_mfma<GF, SF, NR, RED, LR>(A, s, inside, rhs0, grp0, live, acoef, red);
     } else {
-        if (inside && live) dslash_site<GF, SF, R, NR, STAGE, RED, LR>(A, s, rhs0 + grp0, rg, live, acoef, red);
+        if (inside && live) dslash_site<GF, SF, R, NR, STAGE, RED, LR>(A, s, rhs0 + grp0, rg, live, acoef, red, redi);
     }
     }
     if (RED) {
@@ -1114,12 +1137,22 @@ __global__ void __launch_bounds__(256) k_dslash(DslashArgs A, int rhs0, int rg, 
 #pragma unroll
             for (int j = 0; j < NR; j++) lds[w * rg * NR + cofs(grp0, j)] = red[j];
         }
+        if (NR == 1 && A.red == RED_CDOT) {
+            const double v = wave_sum(redi);
+            if (lane == 0) lds[32 + w] = v;
+        }
         __syncthreads();
-        const int k = threadIdx.x;
-        if (k < rg * NR && colvalid(A, rhs0 + k, ncol)) {
+        const int k = threadIdx.x, blk = blockIdx.y * gridDim.x + blockIdx.x;
+        if (NR == 1 && A.red == RED_CDOT) {
+            if (k < 2) {
+                double v = 0.0;
+                for (int ww = 0; ww < nw; ww++) v += lds[32 * k + ww];
+                A.partial[2 * (size_t)blk + k] = v;
+            }
+        } else if (k < rg * NR && colvalid(A, rhs0 + k, ncol)) {
             double v = 0.0;
             for (int ww = 0; ww < nw; ww++) v += lds[ww * rg * NR + k];
-            A.partial[(size_t)colmap(A, rhs0 + k) * A.pstride + blockIdx.x] = v;
+            A.partial[(size_t)colmap(A, rhs0 + k) * A.pstride + blk] = v;
         }
     }
 }
@@ -1135,8 +1168,8 @@ __global__ void __launch_bounds__(MULTI_BLOCK) k_dslash_multi(MultiArgs M) {
     const int s = ((int)blockIdx.x - M.boff[l]) * MULTI_BLOCK + (int)threadIdx.x;
     if (s >= A.g.vh) return;
     const R acoef[1] = {(R)A.a};
-    double red[1] = {0.0};
-    dslash_site<GF, SF, R, 1, STAGE, false, LR>(A, s, 0, 1, 1u, acoef, red);
+    double red[1] = {0.0}, redi = 0.0;
+    dslash_site<GF, SF, R, 1, STAGE, false, LR>(A, s, 0, 1, 1u, acoef, red, redi);
 }
 
 // ---------------------------------------------------------------------------
@@ -1159,34 +1192,37 @@ hipError_t launch_cfg(const DslashArgs &a, int rhs0, int rg, int block, int grid
                       int *nblocks) {
     const int nb = dslash_tile_blocks(a.g, DslashTile{NR, rg, STAGE, block, grid, sweep});
     if (nblocks) *nblocks = nb;
+    if (a.both && ((a.red == RED_NONE && !a.guard.stop) || NR != 1 || rg != 1)) return hipErrorInvalidValue;
+    if (a.red == RED_CDOT && (NR != 1 || rg != 1)) return hipErrorInvalidValue;
+    const dim3 grid2(nb, a.both ? 2 : 1);
     if (a.long_recon == 8) {
         if constexpr (NR == 1 && std::is_same<R, double>::value && (GF == GF_F64 || GF == GF_FIX32) &&
                       STAGE != MFMA_STAGE) {
             if (rg != 1) return hipErrorInvalidValue;
             if (a.red != RED_NONE)
-                hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, true, true, 8>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, sweep);
+                hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, true, true, 8>), grid2, dim3(block), 0, st, a, rhs0, rg, sweep);
             else if (a.guard.stop)
-                hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, true, 8>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, sweep);
+                hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, true, 8>), grid2, dim3(block), 0, st, a, rhs0, rg, sweep);
             else
-                hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, false, 8>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, sweep);
+                hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, false, 8>), grid2, dim3(block), 0, st, a, rhs0, rg, sweep);
             return hipGetLastError();
         }
         return hipErrorInvalidValue;
     }
     if (a.long_recon == 12) {
         if (a.red != RED_NONE)
-            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, true, true, 12>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, sweep);
+            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, true, true, 12>), grid2, dim3(block), 0, st, a, rhs0, rg, sweep);
         else if (a.guard.stop)
-            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, true, 12>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, sweep);
+            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, true, 12>), grid2, dim3(block), 0, st, a, rhs0, rg, sweep);
         else
-            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, false, 12>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, sweep);
+            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, false, 12>), grid2, dim3(block), 0, st, a, rhs0, rg, sweep);
     } else {
         if (a.red != RED_NONE)
-            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, true, true, 18>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, sweep);
+            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, true, true, 18>), grid2, dim3(block), 0, st, a, rhs0, rg, sweep);
         else if (a.guard.stop)
-            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, true, 18>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, sweep);
+            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, true, 18>), grid2, dim3(block), 0, st, a, rhs0, rg, sweep);
         else
-            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, false, 18>), dim3(nb), dim3(block), 0, st, a, rhs0, rg, sweep);
+            hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, false, 18>), grid2, dim3(block), 0, st, a, rhs0, rg, sweep);
     }
     return hipGetLastError();
 }

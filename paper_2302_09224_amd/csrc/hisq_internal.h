@@ -7,6 +7,9 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <chrono>
+#include <thread>
+
 #include "hisq.h"
 #include "hisq_device.h"
 
@@ -59,7 +62,8 @@ inline bool recon_ok(const hisq_fmt &f, int long_recon, bool batched) {
 // Dslash
 // ---------------------------------------------------------------------------
 
-enum { RED_NONE = 0, RED_DOT_X = 1, RED_NORM = 2 };
+// RED_CDOT (one right-hand side): Re and Im of <z, out>, two partials per block
+enum { RED_NONE = 0, RED_DOT_X = 1, RED_NORM = 2, RED_CDOT = 3 };
 
 struct DslashArgs {
     char *out;
@@ -68,11 +72,17 @@ struct DslashArgs {
     const char *lng;
     const char *x;   // optional: out += a*x (format and parity of out)
     const char *y;   // optional: out += c*y
+    const char *z;   // RED_CDOT
+    // both != 0 (guarded or reducing launches, one right-hand side): the whole lattice in one
+    // launch, block row blockIdx.y for the sites of parity blockIdx.y; out, in, x, y, z are
+    // whole-lattice fields (the even sites, then the odd ones `half` bytes on)
+    int both;
+    size_t half;
     double a, b, c;  // out = b*D(in) + a*x + c*y
     double gfat, glong;  // fixed-point decode steps (max/Q), unused for IEEE formats
     Geom g;
     int parity;      // parity of the output sites
-    int red;         // RED_*: per-block partial of Re<x,out> or |out|^2 (values as stored)
+    int red;         // RED_*: per-block partial of the values as stored
     double *partial;
     Guard guard;
     size_t field_stride;  // batched: bytes between consecutive right-hand-side fields
@@ -92,7 +102,7 @@ struct DslashArgs {
 };
 
 // Launch shape of one Dslash launch: each lane accumulates `nr` right-hand
-// sides of one site, `rg` adjacent lanes share a site (nr*rg right-hand sides
+// sides of one site, `rg` lanes of a wave share a site (nr*rg right-hand sides
 // per launch), the 16 hops are loaded in stages of `stage` (negative: stages
 // of -stage hops, double-buffered, the next stage's loads issued before this
 // stage's arithmetic; one right-hand side per lane only), `block` threads,
@@ -282,8 +292,29 @@ hisq_status solver_host_alloc(SolverHost **h);
 // publish the control block's state (nrhs 0: a single system, else the batched fields); a
 // block that has stopped is closed: the iterations of a unit already enqueued behind it do nothing
 hipError_t launch_status(SolverCtrl *c, SolverHost *h, int nrhs, hipStream_t st);
-// wait for record `seq`; HISQ_EHIP when the stream fails first
-hisq_status wait_status(SolverHost *h, unsigned long long seq, hipStream_t st, Status *out);
+// wait for record `seq` at *s; HISQ_EHIP when the stream fails first
+template <class Rec> hisq_status wait_record(const Rec *s, unsigned long long seq, hipStream_t st, Rec *out) {
+    const auto t0 = std::chrono::steady_clock::now();
+    for (long n = 1; __atomic_load_n(&s->seq, __ATOMIC_ACQUIRE) != seq; n++) {
+        if (n % 256) {
+            __builtin_ia32_pause();
+            continue;
+        }
+        // a unit takes 0.1 ms (small lattices) to tens of ms; the stream's own state tells of an error
+        if (std::chrono::steady_clock::now() - t0 < std::chrono::milliseconds(1)) continue;
+        const hipError_t e = hipStreamQuery(st);
+        if (e == hipSuccess && __atomic_load_n(&s->seq, __ATOMIC_ACQUIRE) != seq)
+            return set_error(HISQ_EHIP, "solver record %llu missing after its stream drained", seq);
+        if (e != hipSuccess && e != hipErrorNotReady)
+            return set_error(HISQ_EHIP, "solver stream: %s", hipGetErrorString(e));
+        std::this_thread::sleep_for(std::chrono::microseconds(20));
+    }
+    *out = *s;
+    return HISQ_OK;
+}
+inline hisq_status wait_status(SolverHost *h, unsigned long long seq, hipStream_t st, Status *out) {
+    return wait_record(&h->ring[seq % STATUS_RING], seq, st, out);
+}
 
 // iterations per unit (a multiple of grad_buffer, at least 8 so that the status
 // record's launch is a few per cent of a small lattice's unit) and the units in
