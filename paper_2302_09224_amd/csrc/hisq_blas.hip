@@ -73,38 +73,27 @@ template <int SFD, int SFS> __global__ void k_spinor_convert(char *dst, const ch
         SpinorIO<SFD, double>::store(dst, n, s, SpinorIO<SFS, double>::load(src, n, s));
 }
 
+// max |v|, infinite once a value is not finite (fmax drops a NaN)
+__device__ __forceinline__ double max_finite(double m, double v) {
+    return __builtin_isfinite(v) ? fmax(m, fabs(v)) : __builtin_inf();
+}
+// block maximum, valid in thread 0
+__device__ __forceinline__ double block_max(double m, double *lds) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int w = 1; w < (int)(blockDim.x >> 6); w++) m = fmax(m, lds[w]);
+    return m;
+}
+
 __global__ void k_absmax(const double *src, size_t n, double *partial) {
     __shared__ double lds[16];
     double m = 0.0;
-    int bad = 0;
-    for (size_t i = gtid(); i < n; i += gstride()) {
-        double v = src[i];
-        bad |= !__builtin_isfinite(v);
-        m = fmax(m, fabs(v));
-    }
-    if (bad) m = __builtin_inf();
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
-    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < (int)(blockDim.x >> 6); w++) m = fmax(m, lds[w]);
-        partial[blockIdx.x] = m;
-    }
-}
-
-__global__ void k_reduce_max(const double *partial, int n, double *out) {
-    __shared__ double lds[16];
-    double m = 0.0;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) m = fmax(m, partial[i]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
-    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < (int)(blockDim.x >> 6); w++) m = fmax(m, lds[w]);
-        *out = m;
-    }
+    for (size_t i = gtid(); i < n; i += gstride()) m = max_finite(m, src[i]);
+    m = block_max(m, lds);
+    if (threadIdx.x == 0) partial[blockIdx.x] = m;
 }
 
 // row r of a link as a 24-bit shared-exponent record: words 0-3 in 16-byte
@@ -124,12 +113,18 @@ __device__ __forceinline__ void sx24_store_row(char *base, size_t vh, size_t s, 
     st<unsigned>(base + nrow * 16 * vh + r * 4 * vh + 4 * s, w[4]);
 }
 
-// canonical FP64 links [4][V][3][3] -> packed sub-fields (mu, parity)
-template <int GF> __global__ void k_gauge_pack(char *dst, const double *src, Geom g, const double *absmax) {
+// canonical FP64 links [4][V][3][3] -> packed sub-fields (mu, parity).  The
+// fixed-point formats need the field's maximum first; the others (their values
+// do not depend on it) leave its block partials here, in the pass that reads
+// the links anyway.
+template <int GF> constexpr bool pack_needs_max() { return GF == GF_FIX16 || GF == GF_FIX32; }
+template <int GF> __global__ void k_gauge_pack(char *dst, const double *src, Geom g, const double *absmax, double *partial) {
+    __shared__ double lds[16];
+    double top = 0.0;
     const size_t V = 2 * (size_t)g.vh;
     const size_t vh = g.vh;
     const size_t sub = (size_t)gauge_matrix_bytes(GF) * vh;
-    const double m = *absmax;
+    const double m = pack_needs_max<GF>() ? *absmax : 0.0;
     const double c = GF == GF_FIX16 ? (m > 0.0 ? 32767.0 / m : 0.0) : (m > 0.0 ? 2147483647.0 / m : 0.0);
     for (size_t idx = gtid(); idx < 4 * V; idx += gstride()) {
         const int mu = (int)(idx / V);
@@ -143,6 +138,10 @@ template <int GF> __global__ void k_gauge_pack(char *dst, const double *src, Geo
         const size_t s = site >> 1;
         char *base = dst + (size_t)(2 * mu + par) * sub;
         const double *u = src + idx * 18;
+        if (!pack_needs_max<GF>()) {
+#pragma unroll
+            for (int k = 0; k < 18; k++) top = max_finite(top, u[k]);
+        }
         if (GF == GF_F64) {
 #pragma unroll
             for (int k = 0; k < 9; k++) {
@@ -195,6 +194,10 @@ template <int GF> __global__ void k_gauge_pack(char *dst, const double *src, Geo
             st<u32x2>(base + 64 * vh + 8 * s, t2);
         }
     }
+    if (!pack_needs_max<GF>()) {
+        top = block_max(top, lds);
+        if (threadIdx.x == 0) partial[blockIdx.x] = top;
+    }
 }
 
 // staggered phase of a three-hop link starting at (x,y,z,t) along mu: eta_mu(x)
@@ -208,11 +211,16 @@ __device__ __forceinline__ double link_phase3(int mu, int x, int y, int z, int t
 // Long links for two-row storage: every L_mu(x) must be lambda * sigma * phase * U
 // with U in SU(3), lambda > 0 and sigma = +-1 global.  Per block:
 // [min lambda_x, max lambda_x, #sigma_x>0, #sigma_x<0, max unitarity defect,
-//  max |Im det| / |det|, max |component| / lambda_x], lambda_x = |det L|^(1/3).
+//  max |Im det| / |det|, max |component| / lambda_x, max |real component| (infinite when
+//  one is not finite)], lambda_x = |det L|^(1/3).
+constexpr int LC = 8;
+__device__ __forceinline__ double lc_join(int k, double a, double b) {
+    return k == 0 ? fmin(a, b) : (k == 2 || k == 3) ? a + b : fmax(a, b);
+}
 __global__ void k_long_check(const double *src, Geom g, double *partial) {
-    __shared__ double lds[7][8];
+    __shared__ double lds[LC][8];
     const size_t V = 2 * (size_t)g.vh;
-    double mn = 1e300, mx = 0.0, np = 0.0, nn = 0.0, defect = 0.0, imr = 0.0, cmax = 0.0;
+    double mn = 1e300, mx = 0.0, np = 0.0, nn = 0.0, defect = 0.0, imr = 0.0, cmax = 0.0, top = 0.0;
     for (size_t idx = gtid(); idx < 4 * V; idx += gstride()) {
         const int mu = (int)(idx / V);
         size_t r = idx - (size_t)mu * V;
@@ -225,6 +233,7 @@ __global__ void k_long_check(const double *src, Geom g, double *partial) {
         for (int k = 0; k < 9; k++) {
             ar[k] = u[2 * k];
             ai[k] = u[2 * k + 1];
+            top = max_finite(max_finite(top, ar[k]), ai[k]);
         }
         // det by cofactors along row 0
         double dr = 0.0, di = 0.0;
@@ -256,29 +265,58 @@ __global__ void k_long_check(const double *src, Geom g, double *partial) {
             }
         for (int k = 0; k < 9; k++) cmax = fmax(cmax, fmax(fabs(ar[k]), fabs(ai[k])) * inv);
     }
-    double v[7] = {mn, mx, np, nn, defect, imr, cmax};
-    for (int k = 0; k < 7; k++) {
+    double v[LC] = {mn, mx, np, nn, defect, imr, cmax, top};
+    for (int k = 0; k < LC; k++) {
         double w = v[k];
-        for (int o = 32; o > 0; o >>= 1) {
-            const double q = __shfl_xor(w, o, 64);
-            w = (k == 0) ? fmin(w, q) : (k == 2 || k == 3) ? w + q : fmax(w, q);
-        }
+        for (int o = 32; o > 0; o >>= 1) w = lc_join(k, w, __shfl_xor(w, o, 64));
         if ((threadIdx.x & 63) == 0) lds[k][threadIdx.x >> 6] = w;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int k = 0; k < 7; k++) {
-            double w = lds[k][0];
-            for (int j = 1; j < (int)(blockDim.x >> 6); j++)
-                w = (k == 0) ? fmin(w, lds[k][j]) : (k == 2 || k == 3) ? w + lds[k][j] : fmax(w, lds[k][j]);
-            partial[7 * blockIdx.x + k] = w;
-        }
+    if (threadIdx.x < LC) {
+        const int k = threadIdx.x;
+        double w = lds[k][0];
+        for (int j = 1; j < (int)(blockDim.x >> 6); j++) w = lc_join(k, w, lds[k][j]);
+        partial[LC * blockIdx.x + k] = w;
     }
+}
+
+// the field's statistics from the block partials: *max (NULL: none) from nmax
+// maxima, then the long check (check NULL: none) from ncheck tuples.  One block,
+// wave k for value k.
+__global__ void k_link_stats(LinkStats *out, double *max, const double *pmax, int nmax, const double *pcheck, int ncheck) {
+    const int k = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (max && k == LC) {
+        double m = 0.0;
+        for (int i = lane; i < nmax; i += 64) m = fmax(m, pmax[i]);
+        for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+        if (lane == 0) *max = m;
+    }
+    if (!pcheck) return;
+    __shared__ double lds[LC];
+    if (k < LC) {
+        double w = k == 0 ? 1e300 : 0.0;
+        for (int i = lane; i < ncheck; i += 64) w = lc_join(k, w, pcheck[LC * i + k]);
+        for (int o = 32; o > 0; o >>= 1) w = lc_join(k, w, __shfl_xor(w, o, 64));
+        if (lane == 0) lds[k] = w;
+    }
+    __syncthreads();
+    if (threadIdx.x) return;
+    out->lam_min = lds[0];
+    out->lam_max = lds[1];
+    out->npos = lds[2];
+    out->nneg = lds[3];
+    out->defect = lds[4];
+    out->imr = lds[5];
+    out->umax = lds[6];
+    out->long_max = lds[7];
+    const double lam = 0.5 * (lds[0] + lds[1]);
+    out->coeff = lds[2] > 0 ? lam : -lam;
 }
 
 // two rows of U = L / (lambda * sigma * phase) into the 12-real sub-fields;
 // fixed-point formats scale by umax (the global max |component| of U)
-template <int GF> __global__ void k_gauge_pack12(char *dst, const double *src, Geom g, double coef, double umax) {
+template <int GF> __global__ void k_gauge_pack12(char *dst, const double *src, Geom g, const LinkStats *ls) {
+    const double coef = ls->coeff, umax = ls->umax;
     const size_t V = 2 * (size_t)g.vh;
     const size_t vh = g.vh;
     const size_t sub = (size_t)gauge_matrix_bytes12(GF) * vh;
@@ -358,7 +396,8 @@ __device__ __noinline__ double phase_param(double x, double y) {
 // eight parameters of W = L * phase * sign (= |lambda| U): Re/Im of W01, W02,
 // W10, then phase_param of W00 and of W20.  F64: four 16-byte planes; FIX32:
 // two planes, the entries scaled by lmax, the phase parameters by 1.
-template <int GF> __global__ void k_gauge_pack8(char *dst, const double *src, Geom g, double sign, double lmax) {
+template <int GF> __global__ void k_gauge_pack8(char *dst, const double *src, Geom g, const LinkStats *ls) {
+    const double sign = ls->npos > 0 ? 1.0 : -1.0, lmax = ls->long_max;
     const size_t V = 2 * (size_t)g.vh;
     const size_t vh = g.vh;
     const size_t sub = (size_t)gauge_matrix_bytes8(GF) * vh;
@@ -1239,22 +1278,31 @@ hipError_t launch_absmax(const double *src, size_t n, double *partial, int *nblo
     return hipGetLastError();
 }
 
-hipError_t launch_reduce_max(const double *partial, int n, double *out, hipStream_t st) {
-    hipLaunchKernelGGL(k_reduce_max, dim3(1), dim3(1024), 0, st, partial, n, out);
+hipError_t launch_link_stats(LinkStats *out, double *max, const double *pmax, int nmax, const double *pcheck, int ncheck,
+                             hipStream_t st) {
+    hipLaunchKernelGGL(k_link_stats, dim3(1), dim3(64 * (LC + 1)), 0, st, out, max, pmax, nmax, pcheck, ncheck);
     return hipGetLastError();
 }
 
-hipError_t launch_gauge_pack(char *dst, const double *src, const Geom &g, int gf, const double *absmax, hipStream_t st) {
-    const size_t n = 8 * (size_t)g.vh;
-    const int nb = blas_blocks(n);
-    switch (gf) {
-    case GF_F64: hipLaunchKernelGGL((k_gauge_pack<GF_F64>), dim3(nb), dim3(BLAS_BLOCK), 0, st, dst, src, g, absmax); break;
-    case GF_F32: hipLaunchKernelGGL((k_gauge_pack<GF_F32>), dim3(nb), dim3(BLAS_BLOCK), 0, st, dst, src, g, absmax); break;
-    case GF_FIX16: hipLaunchKernelGGL((k_gauge_pack<GF_FIX16>), dim3(nb), dim3(BLAS_BLOCK), 0, st, dst, src, g, absmax); break;
-    case GF_FIX32: hipLaunchKernelGGL((k_gauge_pack<GF_FIX32>), dim3(nb), dim3(BLAS_BLOCK), 0, st, dst, src, g, absmax); break;
-    case GF_SX24: hipLaunchKernelGGL((k_gauge_pack<GF_SX24>), dim3(nb), dim3(BLAS_BLOCK), 0, st, dst, src, g, absmax); break;
-    default: return hipErrorInvalidValue;
-    }
+bool gauge_pack_needs_max(int gf) { return gf == GF_FIX16 || gf == GF_FIX32; }
+
+#define HISQ_DISPATCH_GF(gf, CALL)                                                    \
+    do {                                                                              \
+        switch (gf) {                                                                 \
+        case GF_F64: { constexpr int GFc = GF_F64; CALL; } break;                    \
+        case GF_F32: { constexpr int GFc = GF_F32; CALL; } break;                    \
+        case GF_FIX16: { constexpr int GFc = GF_FIX16; CALL; } break;                \
+        case GF_FIX32: { constexpr int GFc = GF_FIX32; CALL; } break;                \
+        case GF_SX24: { constexpr int GFc = GF_SX24; CALL; } break;                  \
+        default: return hipErrorInvalidValue;                                         \
+        }                                                                             \
+    } while (0)
+
+hipError_t launch_gauge_pack(char *dst, const double *src, const Geom &g, int gf, const double *absmax, double *partial,
+                             int *nblocks, hipStream_t st) {
+    const int nb = blas_blocks(8 * (size_t)g.vh);
+    *nblocks = nb;
+    HISQ_DISPATCH_GF(gf, hipLaunchKernelGGL((k_gauge_pack<GFc>), dim3(nb), dim3(BLAS_BLOCK), 0, st, dst, src, g, absmax, partial));
     return hipGetLastError();
 }
 
@@ -1265,28 +1313,19 @@ hipError_t launch_long_check(const double *src, const Geom &g, double *partial, 
     return hipGetLastError();
 }
 
-hipError_t launch_gauge_pack8(char *dst, const double *src, const Geom &g, int gf, double sign, double lmax,
-                              hipStream_t st) {
+hipError_t launch_gauge_pack8(char *dst, const double *src, const Geom &g, int gf, const LinkStats *ls, hipStream_t st) {
     const int nb = blas_blocks((size_t)8 * g.vh);
     switch (gf) {
-    case GF_F64: hipLaunchKernelGGL((k_gauge_pack8<GF_F64>), dim3(nb), dim3(BLAS_BLOCK), 0, st, dst, src, g, sign, lmax); break;
-    case GF_FIX32: hipLaunchKernelGGL((k_gauge_pack8<GF_FIX32>), dim3(nb), dim3(BLAS_BLOCK), 0, st, dst, src, g, sign, lmax); break;
+    case GF_F64: hipLaunchKernelGGL((k_gauge_pack8<GF_F64>), dim3(nb), dim3(BLAS_BLOCK), 0, st, dst, src, g, ls); break;
+    case GF_FIX32: hipLaunchKernelGGL((k_gauge_pack8<GF_FIX32>), dim3(nb), dim3(BLAS_BLOCK), 0, st, dst, src, g, ls); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_gauge_pack12(char *dst, const double *src, const Geom &g, int gf, double coef, double umax,
-                               hipStream_t st) {
+hipError_t launch_gauge_pack12(char *dst, const double *src, const Geom &g, int gf, const LinkStats *ls, hipStream_t st) {
     const int nb = blas_blocks(8 * (size_t)g.vh);
-    switch (gf) {
-    case GF_F64: hipLaunchKernelGGL((k_gauge_pack12<GF_F64>), dim3(nb), dim3(BLAS_BLOCK), 0, st, dst, src, g, coef, umax); break;
-    case GF_F32: hipLaunchKernelGGL((k_gauge_pack12<GF_F32>), dim3(nb), dim3(BLAS_BLOCK), 0, st, dst, src, g, coef, umax); break;
-    case GF_FIX16: hipLaunchKernelGGL((k_gauge_pack12<GF_FIX16>), dim3(nb), dim3(BLAS_BLOCK), 0, st, dst, src, g, coef, umax); break;
-    case GF_FIX32: hipLaunchKernelGGL((k_gauge_pack12<GF_FIX32>), dim3(nb), dim3(BLAS_BLOCK), 0, st, dst, src, g, coef, umax); break;
-    case GF_SX24: hipLaunchKernelGGL((k_gauge_pack12<GF_SX24>), dim3(nb), dim3(BLAS_BLOCK), 0, st, dst, src, g, coef, umax); break;
-    default: return hipErrorInvalidValue;
-    }
+    HISQ_DISPATCH_GF(gf, hipLaunchKernelGGL((k_gauge_pack12<GFc>), dim3(nb), dim3(BLAS_BLOCK), 0, st, dst, src, g, ls));
     return hipGetLastError();
 }
 

@@ -5,10 +5,8 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
-#include <algorithm>
 #include <cstring>
 #include <mutex>
-#include <vector>
 
 #include "hisq_internal.h"
 
@@ -95,7 +93,7 @@ void gauge_args(DslashArgs &a, const hisq_gauge *g) {
 namespace {
 std::mutex g_scratch_mu;
 LibScratch g_scratch[64];
-constexpr size_t SCRATCH_DOUBLES = 16384;
+constexpr size_t SCRATCH_DOUBLES = (size_t)BLAS_MAX_BLOCKS * (2 + LINK_CHECK_VALUES) + 64;
 }  // namespace
 
 hisq_status lib_scratch(LibScratch **out) {
@@ -206,58 +204,59 @@ extern "C" hisq_status hisq_gauge_pack_recon(hisq_gauge *g, void *fat_dst, void 
     std::lock_guard<std::mutex> lk(mu);
     const Geom geo = make_geom(dims);
     const size_t nreal = (size_t)4 * 2 * geo.vh * 18;
-    double *part = ls->dev;                       // partial maxima
-    double *mx = ls->dev + ls->ndev - 2;          // the two global maxima
-    int nb = 0;
-    HISQ_TRY_HIP(launch_absmax(fat_src, nreal, part, &nb, st));
-    HISQ_TRY_HIP(launch_reduce_max(part, nb, mx, st));
-    HISQ_TRY_HIP(launch_absmax(long_src, nreal, part, &nb, st));
-    HISQ_TRY_HIP(launch_reduce_max(part, nb, mx + 1, st));
-    HISQ_TRY_HIP(hipMemcpyAsync(ls->host, mx, 2 * sizeof(double), hipMemcpyDeviceToHost, st));
-    HISQ_TRY_HIP(hipStreamSynchronize(st));
-    const double fmax_ = ls->host[0], lmax_ = ls->host[1];
-    if (!std::isfinite(fmax_) || !std::isfinite(lmax_))
-        return set_error(HISQ_ERANGE, "hisq_gauge_pack: non-finite link element");
-    HISQ_TRY_HIP(launch_gauge_pack((char *)fat_dst, fat_src, geo, gauge_fmt, mx, st));
-    double long_scale = lmax_, coeff = 1.0;
-    if (long_recon == HISQ_RECON_18) {
-        HISQ_TRY_HIP(launch_gauge_pack((char *)long_dst, long_src, geo, gauge_fmt, mx + 1, st));
+    // scratch: block maxima of the fat and the long field, the long check's
+    // tuples, then [fat max, long max, LinkStats], copied to the host at the end
+    double *pfat = ls->dev, *plng = pfat + BLAS_MAX_BLOCKS, *pchk = plng + BLAS_MAX_BLOCKS;
+    double *mx = pchk + (size_t)BLAS_MAX_BLOCKS * LINK_CHECK_VALUES;
+    LinkStats *lsd = (LinkStats *)(mx + 2);
+    const bool scaled = gauge_pack_needs_max(gauge_fmt), full = long_recon == HISQ_RECON_18;
+    int nf = 0, nl = 0, nc = 0;
+    // Each field is read once where its packed values do not depend on the whole
+    // field (IEEE and shared-exponent formats, 18 reals), else twice: 604 MB a
+    // read at 32^4, 108 us.
+    if (scaled) {
+        HISQ_TRY_HIP(launch_absmax(fat_src, nreal, pfat, &nf, st));
+        HISQ_TRY_HIP(launch_link_stats(nullptr, mx, pfat, nf, nullptr, 0, st));
+    }
+    HISQ_TRY_HIP(launch_gauge_pack((char *)fat_dst, fat_src, geo, gauge_fmt, mx, pfat, &nf, st));
+    if (full) {
+        if (scaled) {
+            HISQ_TRY_HIP(launch_absmax(long_src, nreal, plng, &nl, st));
+            HISQ_TRY_HIP(launch_link_stats(nullptr, mx + 1, plng, nl, nullptr, 0, st));
+        }
+        HISQ_TRY_HIP(launch_gauge_pack((char *)long_dst, long_src, geo, gauge_fmt, mx + 1, plng, &nl, st));
+        if (!scaled) HISQ_TRY_HIP(launch_link_stats(nullptr, mx + 1, plng, nl, nullptr, 0, st));
     } else {
         // verify L = lambda * sigma * phase * SU(3) and find lambda, sigma and max |U|
-        int nbc = 0;
-        HISQ_TRY_HIP(launch_long_check(long_src, geo, part, &nbc, st));
-        std::vector<double> ck((size_t)7 * nbc);
-        HISQ_TRY_HIP(hipMemcpyAsync(ck.data(), part, ck.size() * sizeof(double), hipMemcpyDeviceToHost, st));
-        HISQ_TRY_HIP(hipStreamSynchronize(st));
-        double mn = 1e300, mxl = 0.0, np = 0.0, nn = 0.0, defect = 0.0, imr = 0.0, umax = 0.0;
-        for (int b = 0; b < nbc; b++) {
-            const double *c = &ck[(size_t)7 * b];
-            mn = std::min(mn, c[0]);
-            mxl = std::max(mxl, c[1]);
-            np += c[2];
-            nn += c[3];
-            defect = std::max(defect, c[4]);
-            imr = std::max(imr, c[5]);
-            umax = std::max(umax, c[6]);
-        }
+        HISQ_TRY_HIP(launch_long_check(long_src, geo, pchk, &nc, st));
+        HISQ_TRY_HIP(launch_link_stats(lsd, nullptr, nullptr, 0, pchk, nc, st));
+        if (long_recon == HISQ_RECON_8)
+            HISQ_TRY_HIP(launch_gauge_pack8((char *)long_dst, long_src, geo, gauge_fmt, lsd, st));
+        else
+            HISQ_TRY_HIP(launch_gauge_pack12((char *)long_dst, long_src, geo, gauge_fmt, lsd, st));
+    }
+    if (!scaled) HISQ_TRY_HIP(launch_link_stats(nullptr, mx, pfat, nf, nullptr, 0, st));
+    HISQ_TRY_HIP(hipMemcpyAsync(ls->host, mx, 2 * sizeof(double) + sizeof(LinkStats), hipMemcpyDeviceToHost, st));
+    HISQ_TRY_HIP(hipStreamSynchronize(st));
+    const LinkStats *c = (const LinkStats *)(ls->host + 2);
+    const double fmax_ = ls->host[0], lmax_ = full ? ls->host[1] : c->long_max;
+    if (!std::isfinite(fmax_) || !std::isfinite(lmax_))
+        return set_error(HISQ_ERANGE, "hisq_gauge_pack: non-finite link element");
+    double long_scale = lmax_, coeff = 1.0;
+    if (!full) {
         const double tol = gauge_fmt == HISQ_GAUGE_F64 ? 1e-13
                            : (gauge_fmt == HISQ_GAUGE_F32 || gauge_fmt == HISQ_GAUGE_SX24) ? 1e-7
                            : gauge_fmt == HISQ_GAUGE_FIX16 ? 1e-5 : 1e-9;
-        const double lam = 0.5 * (mn + mxl);
-        if (!(lam > 0.0) || (mxl - mn) > tol * lam || defect > tol || imr > tol || (np > 0 && nn > 0))
+        const double lam = 0.5 * (c->lam_min + c->lam_max);
+        if (!(lam > 0.0) || (c->lam_max - c->lam_min) > tol * lam || c->defect > tol || c->imr > tol ||
+            (c->npos > 0 && c->nneg > 0))
             return set_error(HISQ_EINVAL,
                              "hisq_gauge_pack_recon: long links are not lambda*phase*SU(3) within %g "
                              "(lambda in [%g,%g], unitarity defect %g, |Im det|/|det| %g, sign counts %g/%g)",
-                             tol, mn, mxl, defect, imr, np, nn);
-        coeff = np > 0 ? lam : -lam;
-        if (long_recon == HISQ_RECON_8) {
-            HISQ_TRY_HIP(launch_gauge_pack8((char *)long_dst, long_src, geo, gauge_fmt, np > 0 ? 1.0 : -1.0, lmax_, st));
-        } else {
-            long_scale = umax;
-            HISQ_TRY_HIP(launch_gauge_pack12((char *)long_dst, long_src, geo, gauge_fmt, coeff, umax, st));
-        }
+                             tol, c->lam_min, c->lam_max, c->defect, c->imr, c->npos, c->nneg);
+        coeff = c->coeff;
+        if (long_recon == HISQ_RECON_12) long_scale = c->umax;
     }
-    HISQ_TRY_HIP(hipStreamSynchronize(st));
     for (int k = 0; k < 4; k++) g->dims[k] = dims[k];
     g->fmt = gauge_fmt;
     g->fat = fat_dst;
