@@ -749,7 +749,7 @@ BlLayout bl_layout(const Geom &g, int l, const hisq_fmt &f) {
     L.fb64 = al256(spinor_field_bytes(g.vh, SF_F64));
     const size_t nbl = (size_t)blas_blocks(2 * (size_t)g.vh);
     // the operator's partials: two per block of the largest one-system launch, both parities
-    L.dpart = 4 * (size_t)std::max(dslash_blocks(g.vh, 128), 8 * g.T * slab_tiles(g, 1, 128));
+    L.dpart = 4 * (size_t)std::max(dslash_blocks(g.vh, 64), 8 * g.T * slab_tiles(g, 1, 64));
     L.vpart = nbl * (2 * BL_MAXL + 1);
     L.part_doubles = L.dpart + 3 * L.vpart;
     L.nvec = 2 * (l + 1) + 1;   // r_0..r_l, u_0..u_l, shadow

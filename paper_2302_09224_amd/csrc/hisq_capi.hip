@@ -301,7 +301,7 @@ extern "C" hisq_status hisq_dslash_multi(int n, void *const *out, const void *co
     memset(&m, 0, sizeof(m));
     m.n = n;
     int lr = -1;
-    long long blocks = 0;
+    long long sites = 0;
     for (int i = 0; i < n; i++) {
         if (!g[i]) return set_error(HISQ_EINVAL, "hisq_dslash_multi: null gauge %d", i);
         HISQ_TRY(dslash_common(out[i], in[i], g[i], parity, fmt, "hisq_dslash_multi"));
@@ -314,11 +314,19 @@ extern "C" hisq_status hisq_dslash_multi(int n, void *const *out, const void *co
             if (out[i] == out[k] || out[i] == in[k] || in[i] == out[k])
                 return set_error(HISQ_EINVAL, "hisq_dslash_multi: lattice %d aliases lattice %d", i, k);
         m.a[i] = base_args(g[i], out[i], in[i], parity);
+        sites += m.a[i].g.vh;
+    }
+    m.xcd = sites > MULTI_SPREAD;
+    m.block = m.xcd ? 128 : 64;
+    long long blocks = 0;
+    for (int i = 0; i < n; i++) {
         m.boff[i] = (int)blocks;
-        blocks += (m.a[i].g.vh + MULTI_BLOCK - 1) / MULTI_BLOCK;
+        // whole eighths in the XCD order
+        blocks += m.xcd ? dslash_blocks(m.a[i].g.vh, m.block) : (m.a[i].g.vh + m.block - 1) / m.block;
         if (blocks > 0x7fffffff) return set_error(HISQ_EINVAL, "hisq_dslash_multi: too many sites");
     }
     m.boff[n] = (int)blocks;
+    for (int i = n + 1; i <= HISQ_MAX_LATTICES; i++) m.boff[i] = 0x7fffffff;
     HISQ_TRY_HIP(launch_dslash_multi(m, fmt, lr, (hipStream_t)stream));
     return HISQ_OK;
 }

@@ -63,10 +63,13 @@ bool tuning_enabled() {
     return !(e && e[0] == '0');
 }
 
-// a launch shape the kernels are instantiated for, for a block of c right-hand sides
-bool shape_ok(const hisq_fmt &f, int c, const DslashTile &t) {
+// a launch shape the kernels are instantiated for, for a block of c right-hand sides;
+// wave_blocks: also blocks of one wave, which the tuner chooses on small lattices
+// (not a shape of hisq_tune_set).  With more than eight lanes to a site they would
+// leave more partials than dslash_max_blocks.
+bool shape_ok(const hisq_fmt &f, int c, const DslashTile &t, bool wave_blocks = false) {
     bool ok = t.nr >= 1 && t.rg >= 1 && t.nr * t.rg == c && (t.nr & (t.nr - 1)) == 0 && (t.rg & (t.rg - 1)) == 0;
-    ok = ok && (t.block == 128 || t.block == 256) && t.grid >= 0 && t.grid % 8 == 0 && t.sweep >= 0 && t.sweep <= 2;
+    ok = ok && (t.block == 128 || t.block == 256 || (wave_blocks && t.block == 64 && t.rg <= 8)) && t.grid >= 0 && t.grid % 8 == 0 && t.sweep >= 0 && t.sweep <= 2;
     const bool mfma = t.stage == 5 && t.rg == 4 && t.nr <= 4 && f.compute == 32;   // the matrix-core path
     return ok && (mfma || (t.nr == 1 ? (t.stage == 1 || t.stage == 2 || t.stage == 4 || t.stage == 8 ||
                                         t.stage == -1 || t.stage == -2)
@@ -136,7 +139,7 @@ hisq_status read_tune_file(const char *path, const std::string &tag, bool apply,
         const bool pow2 = c >= 1 && c <= 16 && (c & (c - 1)) == 0;
         if (!dims_ok(dims) || !triplet_ok(f) || (recon != 8 && recon != 12 && recon != 18) ||
             !recon_ok(f, recon, c > 1) || !pow2 || (red != 0 && red != 1) ||
-            (c > 1 && !has_batched_form(f)) || !shape_ok(f, c, t)) {
+            (c > 1 && !has_batched_form(f)) || !shape_ok(f, c, t, true)) {
             st = set_error(HISQ_EIO, "tune cache %s: line %d names an unsupported key or shape", path, lineno);
             break;
         }
@@ -191,10 +194,17 @@ void cache_append(const TuneKey &k, const DslashTile &t, float ms) {
 // candidate shapes for a block of c right-hand sides (c a power of two <= 16)
 // grids: 0 = one tile per block; 256*k = a persistent grid of k blocks per CU
 // slab_ok: the lattice is deep enough in z for the z-slab order (one plane per XCD at least)
-std::vector<DslashTile> candidates(int c, bool batched_ok, bool fp32, bool slab_ok) {
+// spread: few sites per parity (SPREAD_SITES): smaller blocks too, which reach more
+// compute units (2768 sites of F64 with two-row long links: 14.7 us in blocks of 256,
+// 9.1 of 128, 6.7 of 64; at 32^3x16 blocks of 64 lose up to 13 %)
+constexpr int SPREAD_SITES = 65536;
+std::vector<DslashTile> candidates(int c, bool batched_ok, bool fp32, bool slab_ok, bool spread) {
     std::vector<DslashTile> v;
     const int nsweep = slab_ok ? 3 : 2;
     if (c == 1) {
+        if (spread)
+            for (int st : {1, 2, 4, 8, -1, -2})
+                for (int sw = 0; sw < nsweep; sw++) v.push_back(DslashTile{1, 1, st, 64, 0, sw});
         for (int st : {1, 2, 4, 8, -1, -2})
             for (int blk : {128, 256})
                 for (int per_cu : {0, 4, 8})
@@ -206,6 +216,15 @@ std::vector<DslashTile> candidates(int c, bool batched_ok, bool fp32, bool slab_
     for (int nr : {1, 2, 4, 8, 16}) {
         if (nr > c) break;
         const int rg = c / nr;
+        if (spread)
+            for (int blk : {64, 128}) {
+                if (blk == 64 && rg > 8) continue;
+                for (int sw = 0; sw < nsweep; sw++) {
+                    v.push_back(DslashTile{nr, rg, 1, blk, 0, sw});
+                    if (nr == 1) v.push_back(DslashTile{nr, rg, 2, blk, 0, sw});
+                    if (nr > 1 && nr <= 8) v.push_back(DslashTile{nr, rg, -1, blk, 0, sw});
+                }
+            }
         for (int grid : {0, 2048})
             for (int sw = 0; sw < nsweep; sw++) {
                 v.push_back(DslashTile{nr, rg, 1, 256, grid, sw});
@@ -305,7 +324,7 @@ DslashTile tile_for(const hisq_fmt &f, const Geom &g, int c, const DslashArgs *p
     // every candidate three times, then the three fastest ten times each (a
     // single noisy sample does not decide between shapes a few per cent apart)
     std::vector<std::pair<float, DslashTile>> timed;
-    for (const DslashTile &t : candidates(c, batched_ok, f.compute == 32, g.Z >= 8)) {
+    for (const DslashTile &t : candidates(c, batched_ok, f.compute == 32, g.Z >= 8, g.vh <= SPREAD_SITES)) {
         const float ms = time_tile(p, f, t, st);
         if (ms > 0.f) timed.emplace_back(ms, t);
     }

@@ -1159,17 +1159,21 @@ __global__ void __launch_bounds__(256) k_dslash(DslashArgs A, int rhs0, int rg, 
 
 // Several lattices in one launch (Sec. 1 "Block solvers": small problems filling
 // the device together): block b belongs to the lattice l with boff[l] <= b <
-// boff[l+1] and covers its sites (b - boff[l]) * MULTI_BLOCK + lane.
-template <int GF, int SF, class R, int STAGE, int LR>
-__global__ void __launch_bounds__(MULTI_BLOCK) k_dslash_multi(MultiArgs M) {
+// boff[l+1].
+constexpr int MULTI_STAGE = -2;
+template <int GF, int SF, class R, int LR>
+__global__ void __launch_bounds__(128) k_dslash_multi(MultiArgs M) {
     int l = 0;
-    while (l + 1 < M.n && (int)blockIdx.x >= M.boff[l + 1]) l++;
+#pragma unroll
+    for (int i = 1; i < HISQ_MAX_LATTICES; i++) l += (int)blockIdx.x >= M.boff[i] ? 1 : 0;
     const DslashArgs &A = M.a[l];
-    const int s = ((int)blockIdx.x - M.boff[l]) * MULTI_BLOCK + (int)threadIdx.x;
+    int b = (int)blockIdx.x - M.boff[l];
+    if (M.xcd) b = xcd_block(b, M.boff[l + 1] - M.boff[l]);
+    const int s = b * (int)blockDim.x + (int)threadIdx.x;
     if (s >= A.g.vh) return;
     const R acoef[1] = {(R)A.a};
     double red[1] = {0.0}, redi = 0.0;
-    dslash_site<GF, SF, R, 1, STAGE, false, LR>(A, s, 0, 1, 1u, acoef, red, redi);
+    dslash_site<GF, SF, R, 1, MULTI_STAGE, false, LR>(A, s, 0, 1, 1u, acoef, red, redi);
 }
 
 // ---------------------------------------------------------------------------
@@ -1179,11 +1183,11 @@ __global__ void __launch_bounds__(MULTI_BLOCK) k_dslash_multi(MultiArgs M) {
 template <int GF, int SF, class R>
 hipError_t launch_multi(const MultiArgs &m, int long_recon, hipStream_t st) {
     const int nb = m.boff[m.n];
-    if (long_recon != 12 && long_recon != 18) return hipErrorInvalidValue;
+    if ((long_recon != 12 && long_recon != 18) || (m.block != 64 && m.block != 128)) return hipErrorInvalidValue;
     if (long_recon == 12)
-        hipLaunchKernelGGL((k_dslash_multi<GF, SF, R, 4, 12>), dim3(nb), dim3(MULTI_BLOCK), 0, st, m);
+        hipLaunchKernelGGL((k_dslash_multi<GF, SF, R, 12>), dim3(nb), dim3(m.block), 0, st, m);
     else
-        hipLaunchKernelGGL((k_dslash_multi<GF, SF, R, 4, 18>), dim3(nb), dim3(MULTI_BLOCK), 0, st, m);
+        hipLaunchKernelGGL((k_dslash_multi<GF, SF, R, 18>), dim3(nb), dim3(m.block), 0, st, m);
     return hipGetLastError();
 }
 
@@ -1231,7 +1235,8 @@ hipError_t launch_cfg(const DslashArgs &a, int rhs0, int rg, int block, int grid
 // rg must be a power of two <= 16 and nr*rg <= 16 (the per-group reduction)
 template <int GF, int SF, class R, bool BATCHED>
 hipError_t launch_tile(const DslashArgs &a, int rhs0, const DslashTile &t, hipStream_t st, int *nblocks) {
-    if (t.rg < 1 || t.rg > 16 || (t.rg & (t.rg - 1)) || t.nr * t.rg > 16 || (t.block != 128 && t.block != 256) ||
+    if (t.rg < 1 || t.rg > 16 || (t.rg & (t.rg - 1)) || t.nr * t.rg > 16 ||
+        (t.block != 128 && t.block != 256 && !(t.block == 64 && t.rg <= 8)) ||
         t.grid < 0 || (t.grid & 7) || t.sweep < 0 || t.sweep > 2)
         return hipErrorInvalidValue;
     switch (t.nr * 100 + t.stage) {

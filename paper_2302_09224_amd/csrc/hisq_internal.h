@@ -132,12 +132,19 @@ struct DslashPlan {
 void gauge_args(DslashArgs &a, const hisq_gauge *g);
 
 // Several independent lattices in one launch: lattice l owns blocks
-// [boff[l], boff[l+1]) of MULTI_BLOCK lanes, one output site per lane.
-constexpr int MULTI_BLOCK = 256;
+// [boff[l], boff[l+1]) of `block` lanes, one output site per lane.
+// Few sites are spread over the compute units in blocks of one wave, in order
+// (5536 sites in three lattices: F64 14.9 us in blocks of 256, 9.6 of 128, 6.7 of
+// 64; F32 10.5, 7.6, 5.8).  More than MULTI_SPREAD sites (256 CUs of four waves)
+// fill the device anyway and take blocks of 128, each XCD an eighth of every
+// lattice, whose neighbours then meet in its own L2 (8^4 + 12^4 + 16^4 + 24^4:
+// INT20 22.2 -> 20.5 us, F32 48.6 -> 45.2, F64 79.8 -> 78.4).
+constexpr long MULTI_SPREAD = 65536;
 struct MultiArgs {
     DslashArgs a[HISQ_MAX_LATTICES];
-    int boff[HISQ_MAX_LATTICES + 1];
+    int boff[HISQ_MAX_LATTICES + 1];   // beyond n: no block reaches them
     int n;
+    int block, xcd;
 };
 static_assert(sizeof(MultiArgs) <= 4096, "kernel argument block too large");
 hipError_t launch_dslash_multi(const MultiArgs &m, const hisq_fmt &f, int long_recon, hipStream_t st);
