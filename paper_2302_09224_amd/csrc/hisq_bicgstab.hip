@@ -34,9 +34,13 @@
 #include <mutex>
 #include <vector>
 
-#include "hisq_internal.h"
+#include "hisq_dslash_kernels.h"
 
 namespace hisq {
+
+using dsl::SpinRaw;
+using dsl::spin_decode;
+using dsl::spin_load;
 
 namespace {
 
@@ -158,6 +162,17 @@ __global__ void __launch_bounds__(BL_BLOCK) k_bl_dir(VecList u, VecList r, BlCtl
                                                      size_t fb) {
     __shared__ double lds[3 * BL_WAVES];
     if (c->stop < 0) return;
+    // the first site's words are on their way while the partials are added up
+    char *ui = u.p[blockIdx.y];
+    const char *ri = r.p[blockIdx.y];
+    size_t i = bl_tid();
+    SpinRaw<SF> y0, x0;
+    auto fetch = [&](size_t k) {
+        const size_t h = k >= vh ? 1 : 0, s = k - h * vh;
+        y0 = spin_load<SF>(ui + h * fb, vh, s);
+        x0 = spin_load<SF>(ri + h * fb, vh, s);
+    };
+    if (i < 2 * vh) fetch(i);
     double v[3];
     if (nv == 3) {
         all_sums<3>(in.p, in.n, v, lds);
@@ -183,11 +198,10 @@ __global__ void __launch_bounds__(BL_BLOCK) k_bl_dir(VecList u, VecList r, BlCtl
     bl_mul(alpha, rho1, t);
     bl_div(t, rho0, beta);
     const R br = (R)-beta[0], bi = (R)-beta[1];
-    char *ui = u.p[blockIdx.y];
-    const char *ri = r.p[blockIdx.y];
-    for (size_t i = bl_tid(); i < 2 * vh; i += bl_stride()) {
+    for (; i < 2 * vh; i += bl_stride()) {
         const size_t h = i >= vh ? 1 : 0, s = i - h * vh;
-        const CVec<R> y = SpinorIO<SF, R>::load(ui + h * fb, vh, s), x = SpinorIO<SF, R>::load(ri + h * fb, vh, s);
+        const CVec<R> y = spin_decode<R>(y0), x = spin_decode<R>(x0);
+        if (i + bl_stride() < 2 * vh) fetch(i + bl_stride());
         CVec<R> o;
 #pragma unroll
         for (int q = 0; q < 3; q++) {
@@ -205,6 +219,21 @@ __global__ void __launch_bounds__(BL_BLOCK) k_bl_res(VecList u, VecList r, char 
                                                      size_t vh, size_t fb, size_t fb64) {
     __shared__ double lds[2 * BL_WAVES];
     if (c->stop < 0) return;
+    const int k = blockIdx.y;
+    size_t i = bl_tid();
+    SpinRaw<SF> r0, u0;   // row j + 1: u_0 alone
+    SpinRaw<SF_F64> x0;
+    auto fetch = [&](size_t t) {
+        const size_t h = t >= vh ? 1 : 0, s = t - h * vh;
+        if (k <= j) {
+            r0 = spin_load<SF>(r.p[k] + h * fb, vh, s);
+            u0 = spin_load<SF>(u.p[k + 1] + h * fb, vh, s);
+        } else {
+            u0 = spin_load<SF>(u.p[0] + h * fb, vh, s);
+            x0 = spin_load<SF_F64>(x64 + h * fb64, vh, s);
+        }
+    };
+    if (i < 2 * vh) fetch(i);
     double gam[2], alpha[2];
     all_sums<2>(in.p, in.n, gam, lds);
     const bool bad = bl_zero(gam) || !bl_finite(gam);
@@ -219,17 +248,19 @@ __global__ void __launch_bounds__(BL_BLOCK) k_bl_res(VecList u, VecList r, char 
         }
     }
     if (bad) return;
-    const int k = blockIdx.y;
     const double an[2] = {-alpha[0], -alpha[1]};
-    for (size_t i = bl_tid(); i < 2 * vh; i += bl_stride()) {
-        const size_t h = i >= vh ? 1 : 0, s = i - h * vh;
+    for (; i < 2 * vh; i += bl_stride()) {
+        const size_t h = i >= vh ? 1 : 0, s = i - h * vh, nx = i + bl_stride();
+        const CVec<R> uv = spin_decode<R>(u0);
         if (k <= j) {
-            CVec<R> o = SpinorIO<SF, R>::load(r.p[k] + h * fb, vh, s);
-            bl_axpy<R>(o, an, SpinorIO<SF, R>::load(u.p[k + 1] + h * fb, vh, s));
+            CVec<R> o = spin_decode<R>(r0);
+            if (nx < 2 * vh) fetch(nx);
+            bl_axpy<R>(o, an, uv);
             (void)SpinorIO<SF, R>::store(r.p[k] + h * fb, vh, s, o);
         } else {
-            CVec<double> x = SpinorIO<SF_F64, double>::load(x64 + h * fb64, vh, s);
-            bl_xaxpy<R>(x, alpha, SpinorIO<SF, R>::load(u.p[0] + h * fb, vh, s));
+            CVec<double> x = spin_decode<double>(x0);
+            if (nx < 2 * vh) fetch(nx);
+            bl_xaxpy<R>(x, alpha, uv);
             SpinorIO<SF_F64, double>::store(x64 + h * fb64, vh, s, x);
         }
     }
@@ -268,6 +299,16 @@ __global__ void __launch_bounds__(BL_BLOCK) k_bl_mgs(VecList r, BlCtl *c, Sums i
     __shared__ double lds[NP * BL_WAVES], tl[M][2];
     if (c->stop < 0) return;
     const int m = l - i + 1;
+    size_t t = bl_tid();
+    SpinRaw<SF> w0, wp, w[M];
+    auto fetch = [&](size_t k) {
+        const size_t h = k >= vh ? 1 : 0, s = k - h * vh;
+        w0 = spin_load<SF>(r.p[0] + h * fb, vh, s);
+        if (i > 1) wp = spin_load<SF>(r.p[i - 1] + h * fb, vh, s);
+#pragma unroll
+        for (int q = 0; q < M; q++) w[q] = spin_load<SF>(r.p[min(i + q, l)] + h * fb, vh, s);
+    };
+    if (t < 2 * vh) fetch(t);
     if (i > 1) {
         // the previous row's m + 1 vectors left 2 m + 3 sums
         if (in.n == 1) {
@@ -294,13 +335,14 @@ __global__ void __launch_bounds__(BL_BLOCK) k_bl_mgs(VecList r, BlCtl *c, Sums i
     double acc[NV];
 #pragma unroll
     for (int k = 0; k < NV; k++) acc[k] = 0.0;
-    for (size_t t = bl_tid(); t < 2 * vh; t += bl_stride()) {
+    for (; t < 2 * vh; t += bl_stride()) {
         const size_t h = t >= vh ? 1 : 0, s = t - h * vh;
         CVec<R> v[M], prev;
-        const CVec<R> r0 = SpinorIO<SF, R>::load(r.p[0] + h * fb, vh, s);
-        if (i > 1) prev = SpinorIO<SF, R>::load(r.p[i - 1] + h * fb, vh, s);
+        const CVec<R> r0 = spin_decode<R>(w0);
+        if (i > 1) prev = spin_decode<R>(wp);
 #pragma unroll
-        for (int k = 0; k < M; k++) v[k] = SpinorIO<SF, R>::load(r.p[min(i + k, l)] + h * fb, vh, s);
+        for (int k = 0; k < M; k++) v[k] = spin_decode<R>(w[k]);
+        if (t + bl_stride() < 2 * vh) fetch(t + bl_stride());
         if (i > 1) {
 #pragma unroll
             for (int k = 0; k < M; k++) {

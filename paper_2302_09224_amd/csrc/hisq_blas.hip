@@ -13,9 +13,13 @@
 #include <mutex>
 #include <utility>
 
-#include "hisq_internal.h"
+#include "hisq_dslash_kernels.h"
 
 namespace hisq {
+
+using dsl::SpinRaw;
+using dsl::spin_decode;
+using dsl::spin_load;
 
 int blas_blocks(size_t n) {
     size_t nb = (n + BLAS_BLOCK - 1) / BLAS_BLOCK;
@@ -457,12 +461,20 @@ __global__ void k_norm2_f64(const char *v, size_t n, double *partial) {
 
 // r -= alpha A p with alpha = rho / <p,Ap>, every block adding up the <p,Ap>
 // partials of the preceding Dslash itself (Sums): one launch instead of a
-// one-block kernel and this one.
+// one-block kernel and this one (16^4, F32: 4.4 + 4.1 us before, 4.6 us now).
+// A site's words are loaded before they are needed: the first one's before the
+// partials are added up, which on a small lattice is most of the launch.
 template <int SF, class R>
 __global__ void __launch_bounds__(BLAS_BLOCK) k_cg_axpy(char *r, const char *ap, SolverCtrl *ctl, Sums pap, size_t n,
                                                         double *partial, int jb, Guard gd, char *r_copy) {
     __shared__ double lds[2 * (BLAS_BLOCK / 64)];
     if (!gd.pass()) return;
+    size_t s = gtid();
+    SpinRaw<SF> r0, a0;
+    if (s < n) {
+        r0 = spin_load<SF>(r, n, s);
+        a0 = spin_load<SF>(ap, n, s);
+    }
     double pv[1];
     all_sums<1>(pap.p, pap.n, pv, lds);
     const double pi = pv[0], rho = ctl->rho;
@@ -498,9 +510,12 @@ __global__ void __launch_bounds__(BLAS_BLOCK) k_cg_axpy(char *r, const char *ap,
     if (bad) return;
     const R a = (R)alpha;
     double acc[2] = {0.0, 0.0};
-    for (size_t s = gtid(); s < n; s += gstride()) {
-        CVec<R> ro = SpinorIO<SF, R>::load(r, n, s);
-        CVec<R> av = SpinorIO<SF, R>::load(ap, n, s);
+    for (; s < n; s += gstride()) {
+        const CVec<R> ro = spin_decode<R>(r0), av = spin_decode<R>(a0);
+        if (const size_t sn = s + gstride(); sn < n) {
+            r0 = spin_load<SF>(r, n, sn);
+            a0 = spin_load<SF>(ap, n, sn);
+        }
         CVec<R> rn;
 #pragma unroll
         for (int c = 0; c < 3; c++) {
@@ -735,14 +750,22 @@ __global__ void __launch_bounds__(BLAS_BLOCK) k_cg_pupdate(char *pd, const char 
                                                            int jb, Guard gd) {
     __shared__ double lds[2 * (BLAS_BLOCK / 64)];
     if (!gd.pass()) return;
+    size_t s = gtid();
+    SpinRaw<SF> r0, p0;
+    if (s < n) {
+        r0 = spin_load<SF>(r, n, s);
+        if (!FLUSH) p0 = spin_load<SF>(ps, n, s);
+    }
     double v[2], beta = 0.0;
     all_sums<2>(rr.p, rr.n, v, lds);
     if (!cg_scalars(ctl, v[0], v[1], pp, gd.j, multishift, jb, blockIdx.x == 0 && threadIdx.x < 64, beta)) return;
     const R b = (R)beta;
     double acc[1] = {0.0};
-    for (size_t s = gtid(); s < n; s += gstride()) {
-        const CVec<R> rv = SpinorIO<SF, R>::load(r, n, s);
+    for (; s < n; s += gstride()) {
+        const CVec<R> rv = spin_decode<R>(r0);
         CVec<R> pv;
+        const size_t sn = s + gstride();
+        if (sn < n) r0 = spin_load<SF>(r, n, sn);
         if constexpr (FLUSH) {
             constexpr int LOAD_GROUP = load_group<SF>();
             CVec<double> x = SpinorIO<SF_F64, double>::load(x64, n, s);
@@ -767,7 +790,8 @@ __global__ void __launch_bounds__(BLAS_BLOCK) k_cg_pupdate(char *pd, const char 
             }
             SpinorIO<SF_F64, double>::store(x64, n, s, x);
         } else {
-            pv = SpinorIO<SF, R>::load(ps, n, s);
+            pv = spin_decode<R>(p0);
+            if (sn < n) p0 = spin_load<SF>(ps, n, sn);
         }
         CVec<R> o;
 #pragma unroll
@@ -945,6 +969,14 @@ __global__ void __launch_bounds__(BLAS_BLOCK) k_bcg_axpy(char *r, const char *ap
     if (!gd.pass()) return;
     const int j = bcol(cols);
     if (!ctl->bactive[j]) return;
+    r += j * fs;
+    ap += j * fs;
+    size_t s = gtid();
+    SpinRaw<SF> r0, a0;
+    if (s < n) {
+        r0 = spin_load<SF>(r, n, s);
+        a0 = spin_load<SF>(ap, n, s);
+    }
     double pv[1];
     all_sums<1>(pap.p + j * pap.stride, pap.n, pv, lds);
     const double pi = pv[0];
@@ -957,12 +989,13 @@ __global__ void __launch_bounds__(BLAS_BLOCK) k_bcg_axpy(char *r, const char *ap
         ctl->bru[j] = ctl->bwarm[j] = 0;   // the last reliable update is over
     }
     const R a = (R)alpha;
-    r += j * fs;
-    ap += j * fs;
     double acc[2] = {0.0, 0.0};
-    for (size_t s = gtid(); s < n; s += gstride()) {
-        CVec<R> ro = SpinorIO<SF, R>::load(r, n, s);
-        CVec<R> av = SpinorIO<SF, R>::load(ap, n, s);
+    for (; s < n; s += gstride()) {
+        const CVec<R> ro = spin_decode<R>(r0), av = spin_decode<R>(a0);
+        if (const size_t sn = s + gstride(); sn < n) {
+            r0 = spin_load<SF>(r, n, sn);
+            a0 = spin_load<SF>(ap, n, sn);
+        }
         CVec<R> rn;
 #pragma unroll
         for (int c = 0; c < 3; c++) {
@@ -1038,15 +1071,24 @@ __global__ void __launch_bounds__(BLAS_BLOCK) k_bcg_pupdate(char *pd, const char
     if (!ctl->bactive[j]) return;
     const PCoef<R> k{R(1), R(0), (R)ctl->bpb[j]};
     const size_t off = j * fs;
-    for (size_t s = gtid(); s < n; s += gstride()) {
-        const CVec<R> rv = SpinorIO<SF, R>::load(r + off, n, s);
+    size_t s = gtid();
+    SpinRaw<SF> r0, p0;
+    if (s < n) {
+        r0 = spin_load<SF>(r + off, n, s);
+        if (!FLUSH) p0 = spin_load<SF>(ps + off, n, s);
+    }
+    for (; s < n; s += gstride()) {
+        const CVec<R> rv = spin_decode<R>(r0);
         CVec<R> pv;
+        const size_t sn = s + gstride();
+        if (sn < n) r0 = spin_load<SF>(r + off, n, sn);
         if constexpr (FLUSH) {
             CVec<double> x = SpinorIO<SF_F64, double>::load(x64 + j * fs64, n, s);
             pv = bflush_site<SF, R>(x, ring, off, count, ctl, j, n, s);
             SpinorIO<SF_F64, double>::store(x64 + j * fs64, n, s, x);
         } else {
-            pv = SpinorIO<SF, R>::load(ps + off, n, s);
+            pv = spin_decode<R>(p0);
+            if (sn < n) p0 = spin_load<SF>(ps + off, n, sn);
         }
         (void)SpinorIO<SF, R>::store(pd + off, n, s, pstep<R>(k, rv, pv));
     }
