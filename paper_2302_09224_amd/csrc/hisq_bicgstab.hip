@@ -902,6 +902,7 @@ extern "C" hisq_status hisq_bicgstab_solve(double *x, const double *b, const his
         ps.out = B.r.p[1];
         ps.in = B.r.p[0] + L.fb;
         B.plan_s = dslash_plan(sloppy, g, 1, &ps, B.st);
+        dslash_keep_links(sloppy, g, ps.long_recon, B.plan_s);
         B.nb_s = dslash_tile_blocks(g, B.plan_s.tile[0]);
         const hisq_fmt f64 = {HISQ_GAUGE_F64, HISQ_SPINOR_F64, 64};
         DslashArgs p64 = B.dargs(g64, SF_F64);

@@ -105,8 +105,10 @@ template <class R> __device__ __forceinline__ void mdv_sub(CVec<R> &acc, const M
 // ---------------------------------------------------------------------------
 
 template <class T> __device__ __forceinline__ T ld(const char *p) { return *reinterpret_cast<const T *>(p); }
-// streaming load (links are read once per application): non-temporal hint
-template <class T> __device__ __forceinline__ T ld_nt(const char *p) {
+// load of a link word: streaming (links are read once per application: non-temporal
+// hint), or KEEP: an ordinary load, which leaves the line in the memory-side cache
+template <class T, bool KEEP> __device__ __forceinline__ T ld_link(const char *p) {
+    if constexpr (KEEP) return *reinterpret_cast<const T *>(p);
     return __builtin_nontemporal_load(reinterpret_cast<const T *>(p));
 }
 template <class T> __device__ __forceinline__ void st(char *p, T v) { *reinterpret_cast<T *>(p) = v; }

@@ -9,6 +9,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -57,6 +58,7 @@ inline int tune_id(const hisq_fmt &f, int long_recon) {
 }
 std::mutex g_tune_mu;
 std::map<TuneKey, std::pair<DslashTile, float>> g_tuned;
+std::set<TuneKey> g_fixed;   // the keys of g_tuned whose shape hisq_tune_set fixed
 
 bool tuning_enabled() {
     const char *e = getenv("HISQ_TUNE");
@@ -64,15 +66,16 @@ bool tuning_enabled() {
 }
 
 // a launch shape the kernels are instantiated for, for a block of c right-hand sides;
-// wave_blocks: also blocks of one wave, which the tuner chooses on small lattices
-// (not a shape of hisq_tune_set).  With more than eight lanes to a site they would
-// leave more partials than dslash_max_blocks.
-bool shape_ok(const hisq_fmt &f, int c, const DslashTile &t, bool wave_blocks = false) {
+// tuner: also the shapes that only the library chooses (hisq_tune_set refuses them): links
+// kept in the memory-side cache, and on small lattices blocks of one wave (with more
+// than eight lanes to a site these would leave more partials than dslash_max_blocks).
+bool shape_ok(const hisq_fmt &f, int c, const DslashTile &t, bool tuner = false) {
     bool ok = t.nr >= 1 && t.rg >= 1 && t.nr * t.rg == c && (t.nr & (t.nr - 1)) == 0 && (t.rg & (t.rg - 1)) == 0;
-    ok = ok && (t.block == 128 || t.block == 256 || (wave_blocks && t.block == 64 && t.rg <= 8)) && t.grid >= 0 && t.grid % 8 == 0 && t.sweep >= 0 && t.sweep <= 2;
+    ok = ok && (t.block == 128 || t.block == 256 || (tuner && t.block == 64 && t.rg <= 8)) && t.grid >= 0 && t.grid % 8 == 0 && t.sweep >= 0 && t.sweep <= 2;
+    const bool kept = t.stage == -12 || t.stage == -22 || t.stage == -32 || t.stage == -42;
     const bool mfma = t.stage == 5 && t.rg == 4 && t.nr <= 4 && f.compute == 32;   // the matrix-core path
     return ok && (mfma || (t.nr == 1 ? (t.stage == 1 || t.stage == 2 || t.stage == 4 || t.stage == 8 ||
-                                        t.stage == -1 || t.stage == -2)
+                                        t.stage == -1 || t.stage == -2 || (tuner && t.rg == 1 && kept))
                                      : (t.stage == 1 || (t.stage == -1 && t.nr <= 8))));
 }
 
@@ -149,9 +152,10 @@ hisq_status read_tune_file(const char *path, const std::string &tag, bool apply,
     if (st != HISQ_OK) return st;
     if (apply)
         for (const auto &e : got) {
-            if (replace)
+            if (replace) {
                 g_tuned[e.first] = std::make_pair(e.second, -1.f);
-            else
+                g_fixed.erase(e.first);
+            } else
                 g_tuned.emplace(e.first, std::make_pair(e.second, -1.f));
         }
     if (nloaded) *nloaded = (int)got.size();
@@ -198,13 +202,18 @@ void cache_append(const TuneKey &k, const DslashTile &t, float ms) {
 // compute units (2768 sites of F64 with two-row long links: 14.7 us in blocks of 256,
 // 9.1 of 128, 6.7 of 64; at 32^3x16 blocks of 64 lose up to 13 %)
 constexpr int SPREAD_SITES = 65536;
-std::vector<DslashTile> candidates(int c, bool batched_ok, bool fp32, bool slab_ok, bool spread) {
+// small_links: links_stay()
+std::vector<DslashTile> candidates(int c, bool batched_ok, bool fp32, bool slab_ok, bool spread, bool small_links) {
     std::vector<DslashTile> v;
     const int nsweep = slab_ok ? 3 : 2;
     if (c == 1) {
         if (spread)
             for (int st : {1, 2, 4, 8, -1, -2})
                 for (int sw = 0; sw < nsweep; sw++) v.push_back(DslashTile{1, 1, st, 64, 0, sw});
+        if (small_links)
+            for (int blk : {64, 128, 256})
+                for (int sw = 0; sw < nsweep; sw++)
+                    if (spread || blk > 64) v.push_back(DslashTile{1, 1, -42, blk, 0, sw});
         for (int st : {1, 2, 4, 8, -1, -2})
             for (int blk : {128, 256})
                 for (int per_cu : {0, 4, 8})
@@ -239,6 +248,21 @@ std::vector<DslashTile> candidates(int c, bool batched_ok, bool fp32, bool slab_
             for (int sw = 0; sw < nsweep; sw++) v.push_back(DslashTile{c / 4, 4, 5, 256, grid, sw});
     return v;
 }
+
+// bytes of a lattice's links, both parities
+double all_link_bytes(const hisq_fmt &f, int recon, const Geom &g) {
+    const int fat = gauge_matrix_bytes(f.gauge);
+    const int lng = recon == 12 ? gauge_matrix_bytes12(f.gauge) : recon == 8 ? gauge_matrix_bytes8(f.gauge) : fat;
+    return 8.0 * g.vh * (fat + lng);
+}
+
+// Links so small that several such fields stay in the memory-side cache: then any
+// application may find them there, and the tuner also times the loads that keep them
+// (normal operator in F32 on 12x10x14x18, 35 MB: 12.3 -> 11.0 us).  A single application
+// on larger links streams them, since they may have been read long ago: three fields of
+// 767 MB in F64 in turn took 145.8 us each, 152.4 with one direction kept.
+constexpr double LLC_BYTES = 256 * 1048576.0;
+bool links_stay(const hisq_fmt &f, int recon, const Geom &g) { return all_link_bytes(f, recon, g) <= LLC_BYTES / 4; }
 
 DslashTile default_tile(int c) {
     if (c == 1) return DslashTile{1, 1, 8, 256, 0, 0};
@@ -324,7 +348,8 @@ DslashTile tile_for(const hisq_fmt &f, const Geom &g, int c, const DslashArgs *p
     // every candidate three times, then the three fastest ten times each (a
     // single noisy sample does not decide between shapes a few per cent apart)
     std::vector<std::pair<float, DslashTile>> timed;
-    for (const DslashTile &t : candidates(c, batched_ok, f.compute == 32, g.Z >= 8, g.vh <= SPREAD_SITES)) {
+    for (const DslashTile &t : candidates(c, batched_ok, f.compute == 32, g.Z >= 8, g.vh <= SPREAD_SITES,
+                                          links_stay(f, probe->long_recon, g))) {
         const float ms = time_tile(p, f, t, st);
         if (ms > 0.f) timed.emplace_back(ms, t);
     }
@@ -400,6 +425,25 @@ DslashPlan dslash_plan_lookup(const hisq_fmt &f, const Geom &g, int nrhs, int lo
     return plan;
 }
 
+// A solver applies the operator on the same links in every iteration.  Its launches keep
+// the links of as many directions as fit the memory-side cache, four fifths of it since
+// the solver's vectors pass through too: CG with 0, 1, 2, ... directions kept, of 252 MB
+// of INT20 links (32^4, two-row) 39.4, 36.4, 34.8, 35.2, 35.6 ms; of 503 MB in F32 (32^4,
+// two-row) 61.7, 55.8, 59.3 ms; of 318 MB in F64 (24^4, two-row) 33.3, 30.2, 28.2, 28.8 ms;
+// of 1006 MB in F64 (32^4, no direction by this rule) 114.4, 116.6 ms.  Where the tuner
+// had the choice (links_stay) it stands, as does a shape that hisq_tune_set fixed.
+void dslash_keep_links(const hisq_fmt &f, const Geom &g, int long_recon, DslashPlan &plan) {
+    if (links_stay(f, long_recon, g) || plan.n != 1 || plan.tile[0].nr * plan.tile[0].rg != 1) return;
+    const int k = (int)std::min(4.0, 0.8 * LLC_BYTES / (0.25 * all_link_bytes(f, long_recon, g)));
+    if (k < 1 || plan.tile[0].stage < -2) return;
+    {
+        std::lock_guard<std::mutex> lk(g_tune_mu);
+        if (g_fixed.count(TuneKey{tune_id(f, long_recon), g.X, g.Y, g.Z, g.T, 1, 0})) return;
+    }
+    plan.tile[0].stage = -(10 * k + 2);
+    plan.tile_red[0] = plan.tile[0];
+}
+
 hipError_t launch_dslash_multi(const MultiArgs &m, const hisq_fmt &f, int long_recon, hipStream_t st) {
     switch (triplet_key(f)) {
     case GF_F64 * 100 + SF_F64 * 10 + 1: return dslash_multi_double(m, long_recon, st);
@@ -452,6 +496,7 @@ hisq_status tune_set_impl(const char *who, hisq_fmt fmt, const int dims[4], int 
     for (int red = fused ? 1 : 0; red < (rhs_block > 1 ? 2 : 1); red++) {
         const TuneKey key{tune_id(fmt, long_recon), dims[0], dims[1], dims[2], dims[3], rhs_block, red};
         g_tuned[key] = std::make_pair(DslashTile{nr, rg, stage, block, grid, sweep}, -1.f);
+        g_fixed.insert(key);
     }
     return HISQ_OK;
 }
@@ -472,6 +517,7 @@ extern "C" hisq_status hisq_tune_set_fused(hisq_fmt fmt, const int dims[4], int 
 extern "C" void hisq_tune_clear(void) {
     std::lock_guard<std::mutex> lk(hisq::g_tune_mu);
     hisq::g_tuned.clear();
+    hisq::g_fixed.clear();
     hisq::g_cache_read = true;   // a cleared table is not refilled from HISQ_TUNE_CACHE
 }
 

@@ -7,7 +7,8 @@
 // for the sites x of one parity (the stencil the paper benchmarks, Secs. 5.2-5.3).
 //
 // The kernel is bound by HBM bandwidth: every link matrix is read exactly once
-// per application (non-temporal loads: it is not reused), while each input
+// per application (non-temporal loads, but where a solver's links fit the
+// memory-side cache: kept_dirs), while each input
 // spinor is read by up to 16 neighbouring sites and comes from L2 / the MALL
 // after its first use.  The XCD-aware block order keeps the +-3 neighbours of a
 // contiguous site range inside one XCD's L2.
@@ -30,6 +31,7 @@
 // right-hand side), which fuses the solver's xpay and first reduction.
 #pragma once
 #include <type_traits>
+#include <utility>
 
 #include "hisq_internal.h"
 
@@ -49,42 +51,29 @@ template <> struct LinkRaw<GF_FIX32> { u32x4 w[4]; u32x2 t; };
 // r, word 4 of row r in 4-byte plane r after the three 16-byte planes
 template <> struct LinkRaw<GF_SX24> { u32x4 w[3]; unsigned t[3]; };
 
-template <int GF> __device__ __forceinline__ LinkRaw<GF> link_load(const char *sub, size_t vh, size_t s);
-
-template <> __device__ __forceinline__ LinkRaw<GF_F64> link_load<GF_F64>(const char *sub, size_t vh, size_t s) {
-    LinkRaw<GF_F64> L;
+template <int GF, bool KEEP> __device__ __forceinline__ LinkRaw<GF> link_load(const char *sub, size_t vh, size_t s) {
+    LinkRaw<GF> L;
+    if constexpr (GF == GF_F64) {
 #pragma unroll
-    for (int k = 0; k < 9; k++) L.w[k] = ld_nt<f64x2>(sub + k * 16 * vh + 16 * s);
-    return L;
-}
-template <> __device__ __forceinline__ LinkRaw<GF_F32> link_load<GF_F32>(const char *sub, size_t vh, size_t s) {
-    LinkRaw<GF_F32> L;
+        for (int k = 0; k < 9; k++) L.w[k] = ld_link<f64x2, KEEP>(sub + k * 16 * vh + 16 * s);
+    } else if constexpr (GF == GF_F32) {
 #pragma unroll
-    for (int k = 0; k < 4; k++) L.w[k] = ld_nt<f32x4>(sub + k * 16 * vh + 16 * s);
-    L.t = ld_nt<f32x2>(sub + 64 * vh + 8 * s);
-    return L;
-}
-template <> __device__ __forceinline__ LinkRaw<GF_FIX16> link_load<GF_FIX16>(const char *sub, size_t vh, size_t s) {
-    LinkRaw<GF_FIX16> L;
-    L.w[0] = ld_nt<u32x4>(sub + 16 * s);
-    L.w[1] = ld_nt<u32x4>(sub + 16 * vh + 16 * s);
-    L.t = ld_nt<unsigned>(sub + 32 * vh + 4 * s);
-    return L;
-}
-template <> __device__ __forceinline__ LinkRaw<GF_FIX32> link_load<GF_FIX32>(const char *sub, size_t vh, size_t s) {
-    LinkRaw<GF_FIX32> L;
+        for (int k = 0; k < 4; k++) L.w[k] = ld_link<f32x4, KEEP>(sub + k * 16 * vh + 16 * s);
+        L.t = ld_link<f32x2, KEEP>(sub + 64 * vh + 8 * s);
+    } else if constexpr (GF == GF_FIX16) {
+        L.w[0] = ld_link<u32x4, KEEP>(sub + 16 * s);
+        L.w[1] = ld_link<u32x4, KEEP>(sub + 16 * vh + 16 * s);
+        L.t = ld_link<unsigned, KEEP>(sub + 32 * vh + 4 * s);
+    } else if constexpr (GF == GF_FIX32) {
 #pragma unroll
-    for (int k = 0; k < 4; k++) L.w[k] = ld_nt<u32x4>(sub + k * 16 * vh + 16 * s);
-    L.t = ld_nt<u32x2>(sub + 64 * vh + 8 * s);
-    return L;
-}
-
-template <> __device__ __forceinline__ LinkRaw<GF_SX24> link_load<GF_SX24>(const char *sub, size_t vh, size_t s) {
-    LinkRaw<GF_SX24> L;
+        for (int k = 0; k < 4; k++) L.w[k] = ld_link<u32x4, KEEP>(sub + k * 16 * vh + 16 * s);
+        L.t = ld_link<u32x2, KEEP>(sub + 64 * vh + 8 * s);
+    } else if constexpr (GF == GF_SX24) {
 #pragma unroll
-    for (int r = 0; r < 3; r++) L.w[r] = ld_nt<u32x4>(sub + r * 16 * vh + 16 * s);
+        for (int r = 0; r < 3; r++) L.w[r] = ld_link<u32x4, KEEP>(sub + r * 16 * vh + 16 * s);
 #pragma unroll
-    for (int r = 0; r < 3; r++) L.t[r] = ld_nt<unsigned>(sub + 48 * vh + r * 4 * vh + 4 * s);
+        for (int r = 0; r < 3; r++) L.t[r] = ld_link<unsigned, KEEP>(sub + 48 * vh + r * 4 * vh + 4 * s);
+    }
     return L;
 }
 
@@ -165,38 +154,26 @@ template <> struct LinkRaw12<GF_FIX16> { u32x4 w; u32x2 t; };
 template <> struct LinkRaw12<GF_FIX32> { u32x4 w[3]; };
 template <> struct LinkRaw12<GF_SX24> { u32x4 w[2]; unsigned t[2]; };
 
-template <int GF> __device__ __forceinline__ LinkRaw12<GF> link_load12(const char *sub, size_t vh, size_t s);
-template <> __device__ __forceinline__ LinkRaw12<GF_F64> link_load12<GF_F64>(const char *sub, size_t vh, size_t s) {
-    LinkRaw12<GF_F64> L;
+template <int GF, bool KEEP> __device__ __forceinline__ LinkRaw12<GF> link_load12(const char *sub, size_t vh, size_t s) {
+    LinkRaw12<GF> L;
+    if constexpr (GF == GF_F64) {
 #pragma unroll
-    for (int k = 0; k < 6; k++) L.w[k] = ld_nt<f64x2>(sub + k * 16 * vh + 16 * s);
-    return L;
-}
-template <> __device__ __forceinline__ LinkRaw12<GF_F32> link_load12<GF_F32>(const char *sub, size_t vh, size_t s) {
-    LinkRaw12<GF_F32> L;
+        for (int k = 0; k < 6; k++) L.w[k] = ld_link<f64x2, KEEP>(sub + k * 16 * vh + 16 * s);
+    } else if constexpr (GF == GF_F32) {
 #pragma unroll
-    for (int k = 0; k < 3; k++) L.w[k] = ld_nt<f32x4>(sub + k * 16 * vh + 16 * s);
-    return L;
-}
-template <> __device__ __forceinline__ LinkRaw12<GF_FIX16> link_load12<GF_FIX16>(const char *sub, size_t vh, size_t s) {
-    LinkRaw12<GF_FIX16> L;
-    L.w = ld_nt<u32x4>(sub + 16 * s);
-    L.t = ld_nt<u32x2>(sub + 16 * vh + 8 * s);
-    return L;
-}
-template <> __device__ __forceinline__ LinkRaw12<GF_FIX32> link_load12<GF_FIX32>(const char *sub, size_t vh, size_t s) {
-    LinkRaw12<GF_FIX32> L;
+        for (int k = 0; k < 3; k++) L.w[k] = ld_link<f32x4, KEEP>(sub + k * 16 * vh + 16 * s);
+    } else if constexpr (GF == GF_FIX16) {
+        L.w = ld_link<u32x4, KEEP>(sub + 16 * s);
+        L.t = ld_link<u32x2, KEEP>(sub + 16 * vh + 8 * s);
+    } else if constexpr (GF == GF_FIX32) {
 #pragma unroll
-    for (int k = 0; k < 3; k++) L.w[k] = ld_nt<u32x4>(sub + k * 16 * vh + 16 * s);
-    return L;
-}
-
-template <> __device__ __forceinline__ LinkRaw12<GF_SX24> link_load12<GF_SX24>(const char *sub, size_t vh, size_t s) {
-    LinkRaw12<GF_SX24> L;
+        for (int k = 0; k < 3; k++) L.w[k] = ld_link<u32x4, KEEP>(sub + k * 16 * vh + 16 * s);
+    } else if constexpr (GF == GF_SX24) {
 #pragma unroll
-    for (int r = 0; r < 2; r++) L.w[r] = ld_nt<u32x4>(sub + r * 16 * vh + 16 * s);
+        for (int r = 0; r < 2; r++) L.w[r] = ld_link<u32x4, KEEP>(sub + r * 16 * vh + 16 * s);
 #pragma unroll
-    for (int r = 0; r < 2; r++) L.t[r] = ld_nt<unsigned>(sub + 32 * vh + r * 4 * vh + 4 * s);
+        for (int r = 0; r < 2; r++) L.t[r] = ld_link<unsigned, KEEP>(sub + 32 * vh + r * 4 * vh + 4 * s);
+    }
     return L;
 }
 
@@ -280,17 +257,15 @@ template <int GF> struct LinkRaw8 { unsigned unused; };   // formats without thi
 template <> struct LinkRaw8<GF_F64> { f64x2 w[4]; };
 template <> struct LinkRaw8<GF_FIX32> { u32x4 w[2]; };
 
-template <int GF> __device__ __forceinline__ LinkRaw8<GF> link_load8(const char *sub, size_t vh, size_t s);
-template <> __device__ __forceinline__ LinkRaw8<GF_F64> link_load8<GF_F64>(const char *sub, size_t vh, size_t s) {
-    LinkRaw8<GF_F64> L;
+template <int GF, bool KEEP> __device__ __forceinline__ LinkRaw8<GF> link_load8(const char *sub, size_t vh, size_t s) {
+    LinkRaw8<GF> L;
+    if constexpr (GF == GF_F64) {
 #pragma unroll
-    for (int k = 0; k < 4; k++) L.w[k] = ld_nt<f64x2>(sub + k * 16 * vh + 16 * s);
-    return L;
-}
-template <> __device__ __forceinline__ LinkRaw8<GF_FIX32> link_load8<GF_FIX32>(const char *sub, size_t vh, size_t s) {
-    LinkRaw8<GF_FIX32> L;
+        for (int k = 0; k < 4; k++) L.w[k] = ld_link<f64x2, KEEP>(sub + k * 16 * vh + 16 * s);
+    } else if constexpr (GF == GF_FIX32) {
 #pragma unroll
-    for (int k = 0; k < 2; k++) L.w[k] = ld_nt<u32x4>(sub + k * 16 * vh + 16 * s);
+        for (int k = 0; k < 2; k++) L.w[k] = ld_link<u32x4, KEEP>(sub + k * 16 * vh + 16 * s);
+    }
     return L;
 }
 
@@ -692,6 +667,22 @@ __device__ __forceinline__ void site_epilogue(const DslashArgs &A, int s, ColF c
     }
 }
 
+// f(0), f(1), ... with the index as a compile-time constant
+template <class F, int... K>
+__device__ __forceinline__ void unrolled(std::integer_sequence<int, K...>, const F &f) {
+    (f(std::integral_constant<int, K>()), ...);
+}
+
+// Stage -(10 k + 2): stage -2 with the links of the first k directions loaded so that
+// they stay in the memory-side cache (256 MB), which serves them at the next application
+// while HBM serves the others.  Without k the links pass it by: on links that fit it the
+// non-temporal loads cost more than they save elsewhere, and on links that do not, all
+// kept evict each other.  One application, k = 0, 1, 2, 3, 4 (us): F32 24^4, 191 MB of
+// links, 37.5, 35.6, 32.9, 31.9, 30.8; F32 32^4, 604 MB, 110, 96, 105, 110, 115; INT20
+// two-row 32^4, 252 MB, 50.6, 45.3, 42.7, 42.8, 43.2; F64 two-row 24^4, 318 MB, 62.7,
+// 57.8, 53.1, 51.2, 57.8; INT30 eight-parameter 32^3x64, 872 MB, 162, 146, 169, 169, 174.
+constexpr int kept_dirs(int stage) { return stage < -2 && -stage % 10 == 2 ? -stage / 10 : 0; }
+
 // One output site s for the lane's right-hand sides c0 + j*cs, j < NR (those
 // in `live`): the 16 hops, the epilogue out = b*D(in) + a*x + c*y, the packed
 // store, and the optional reduction into red[].
@@ -726,13 +717,13 @@ __device__ __forceinline__ void dslash_site(const DslashArgs &A, int s, int c0, 
             if (LR == 12 && (h & 2)) {
                 const int mu = h >> 2;
                 const int tl = (mu == 3 && (h & 1)) ? wrap_add(c.t, -3, g.T) : c.t;
-                const LinkRaw12<GF> Lr = link_load12<GF>(A.lng + (size_t)(2 * mu + lpar) * lsub, vh, ls);
+                const LinkRaw12<GF> Lr = link_load12<GF, false>(A.lng + (size_t)(2 * mu + lpar) * lsub, vh, ls);
 #pragma unroll
                 for (int j = 0; j < NR; j++) Pr[j] = ((live >> j) & 1u) ? spin_load<SF>(in_col(j), vh, ss) : SpinRaw<SF>{};
                 U = hop_link12<SF>(Lr, gl, lc * (R)long_phase(mu, c.x, c.y, c.z, tl, g.T), f);
             } else {
                 const char *field = (h & 2) ? A.lng : A.fat;
-                const LinkRaw<GF> Lr = link_load<GF>(field + (size_t)(2 * (h >> 2) + lpar) * sub, vh, ls);
+                const LinkRaw<GF> Lr = link_load<GF, false>(field + (size_t)(2 * (h >> 2) + lpar) * sub, vh, ls);
 #pragma unroll
                 for (int j = 0; j < NR; j++) Pr[j] = ((live >> j) & 1u) ? spin_load<SF>(in_col(j), vh, ss) : SpinRaw<SF>{};
                 U = hop_link<SF>(Lr, (h & 2) ? gl : gf, f);
@@ -752,7 +743,7 @@ __device__ __forceinline__ void dslash_site(const DslashArgs &A, int s, int c0, 
     // applied; STAGE < 0: -STAGE hops per stage, double-buffered, the next
     // stage's loads issued before this stage's arithmetic so that every wave
     // keeps loads in flight while it computes
-    constexpr int SB = STAGE < 0 ? -STAGE : STAGE;
+    constexpr int KD = kept_dirs(STAGE), SB = KD ? 2 : STAGE < 0 ? -STAGE : STAGE;
     constexpr bool PIPE = STAGE < 0;
     constexpr int NBUF = PIPE ? 2 : 1;
     constexpr int NST = (NR > 8 && STAGE == 1) ? 0 : 16 / SB;
@@ -772,22 +763,26 @@ __device__ __forceinline__ void dslash_site(const DslashArgs &A, int s, int c0, 
 #pragma unroll
         for (int j = 0; j < NR; j++) colp[j] = (NR == 1 || ((live >> j) & 1u)) ? in_col(j) : first;
     }
-    auto load_stage = [&](int h0, int bf) __attribute__((always_inline)) {
+    // kept: a constant, since the hint of a load is fixed when it is written (two loads that
+    // differ in it alone, on the arms of a branch, become one without it)
+    auto load_stage = [&](int h0, int bf, auto kept) __attribute__((always_inline)) {
+        constexpr bool KEEP = kept;
 #pragma unroll
         for (int i = 0; i < SB; i++) {
             const int h = h0 + i;
             const int ss = hop_spinor_site(n, h);
             const int ls = (h & 1) ? ss : s;
             const int lpar = (h & 1) ? q : p;
+            const size_t lo = (size_t)(2 * (h >> 2) + lpar);
             if constexpr (LR == 8) {
                 if (h & 2)
-                    L8[bf][i] = link_load8<GF>(A.lng + (size_t)(2 * (h >> 2) + lpar) * lsub, vh, ls);
+                    L8[bf][i] = link_load8<GF, KEEP>(A.lng + lo * lsub, vh, ls);
                 else
-                    L[bf][i] = link_load<GF>(A.fat + (size_t)(2 * (h >> 2) + lpar) * sub, vh, ls);
+                    L[bf][i] = link_load<GF, KEEP>(A.fat + lo * sub, vh, ls);
             } else if (LR == 12 && (h & 2)) {
-                L12[bf][i] = link_load12<GF>(A.lng + (size_t)(2 * (h >> 2) + lpar) * lsub, vh, ls);
+                L12[bf][i] = link_load12<GF, KEEP>(A.lng + lo * lsub, vh, ls);
             } else {
-                L[bf][i] = link_load<GF>(((h & 2) ? A.lng : A.fat) + (size_t)(2 * (h >> 2) + lpar) * sub, vh, ls);
+                L[bf][i] = link_load<GF, KEEP>(((h & 2) ? A.lng : A.fat) + lo * sub, vh, ls);
             }
 #pragma unroll
             for (int j = 0; j < NR; j++) P[bf][i][j] = spin_load<SF>(colp[j], vh, ss);
@@ -817,16 +812,27 @@ __device__ __forceinline__ void dslash_site(const DslashArgs &A, int s, int c0, 
             }
         }
     };
-    if (PIPE && NST > 0) load_stage(0, 0);
+    if constexpr (KD > 0) {
+        load_stage(0, 0, std::true_type());
+        unrolled(std::make_integer_sequence<int, NST>(), [&](auto kc) __attribute__((always_inline)) {
+            constexpr int k = kc, h1 = (k + 1) * SB;
+            if constexpr (k + 1 < NST) load_stage(h1, (k + 1) % NBUF, std::bool_constant<(h1 >> 2) < KD>());
+            __builtin_amdgcn_sched_barrier(0);
+            apply_stage(k * SB, k % NBUF);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    } else {
+        if (PIPE && NST > 0) load_stage(0, 0, std::false_type());
 #pragma unroll
-    for (int k = 0; k < NST; k++) {
-        if (!PIPE)
-            load_stage(k * SB, 0);
-        else if (k + 1 < NST)
-            load_stage((k + 1) * SB, (k + 1) % NBUF);
-        __builtin_amdgcn_sched_barrier(0);
-        apply_stage(k * SB, k % NBUF);
-        if (PIPE) __builtin_amdgcn_sched_barrier(0);
+        for (int k = 0; k < NST; k++) {
+            if (!PIPE)
+                load_stage(k * SB, 0, std::false_type());
+            else if (k + 1 < NST)
+                load_stage((k + 1) * SB, (k + 1) % NBUF, std::false_type());
+            __builtin_amdgcn_sched_barrier(0);
+            apply_stage(k * SB, k % NBUF);
+            if (PIPE) __builtin_amdgcn_sched_barrier(0);
+        }
     }
     site_epilogue<SF, R, NR, RED>(A, s, [&](int j) { return colmap(A, c0 + j * cs); }, live, acoef, acc, red, redi);
 }
@@ -953,14 +959,14 @@ __device__ __forceinline__ void dslash_site_mfma(const DslashArgs &A, int s, boo
         const bool back = (h & 1) != 0;
         float ur[3], ui[3], f;
         if (LR == 12 && (h & 2)) {
-            const LinkRaw12<GF> L = link_load12<GF>(A.lng + (size_t)(2 * (h >> 2) + lpar) * lsub, vh, ls);
+            const LinkRaw12<GF> L = link_load12<GF, false>(A.lng + (size_t)(2 * (h >> 2) + lpar) * lsub, vh, ls);
             const float c = lc * (back ? n.lsb[h >> 2] : n.lsf[h >> 2]);
             if (back)
                 lane_link12<SF, GF, true>(L, gl, c, qs, ur, ui, f);
             else
                 lane_link12<SF, GF, false>(L, gl, c, qs, ur, ui, f);
         } else {
-            const LinkRaw<GF> L = link_load<GF>(((h & 2) ? A.lng : A.fat) + (size_t)(2 * (h >> 2) + lpar) * sub, vh, ls);
+            const LinkRaw<GF> L = link_load<GF, false>(((h & 2) ? A.lng : A.fat) + (size_t)(2 * (h >> 2) + lpar) * sub, vh, ls);
             if (back)
                 lane_link<SF, GF, true>(L, (h & 2) ? gl : gf, qs, ur, ui, f);
             else
@@ -1199,15 +1205,17 @@ hipError_t launch_cfg(const DslashArgs &a, int rhs0, int rg, int block, int grid
     if (a.both && ((a.red == RED_NONE && !a.guard.stop) || NR != 1 || rg != 1)) return hipErrorInvalidValue;
     if (a.red == RED_CDOT && (NR != 1 || rg != 1)) return hipErrorInvalidValue;
     const dim3 grid2(nb, a.both ? 2 : 1);
+    // kept links: the guarded form alone, which passes without a flag to read
+    const bool guarded = a.guard.stop || kept_dirs(STAGE);
     if (a.long_recon == 8) {
         if constexpr (NR == 1 && std::is_same<R, double>::value && (GF == GF_F64 || GF == GF_FIX32) &&
                       STAGE != MFMA_STAGE) {
             if (rg != 1) return hipErrorInvalidValue;
             if (a.red != RED_NONE)
                 hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, true, true, 8>), grid2, dim3(block), 0, st, a, rhs0, rg, sweep);
-            else if (a.guard.stop)
+            else if (guarded)
                 hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, true, 8>), grid2, dim3(block), 0, st, a, rhs0, rg, sweep);
-            else
+            else if constexpr (!kept_dirs(STAGE))
                 hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, false, 8>), grid2, dim3(block), 0, st, a, rhs0, rg, sweep);
             return hipGetLastError();
         }
@@ -1216,16 +1224,16 @@ hipError_t launch_cfg(const DslashArgs &a, int rhs0, int rg, int block, int grid
     if (a.long_recon == 12) {
         if (a.red != RED_NONE)
             hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, true, true, 12>), grid2, dim3(block), 0, st, a, rhs0, rg, sweep);
-        else if (a.guard.stop)
+        else if (guarded)
             hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, true, 12>), grid2, dim3(block), 0, st, a, rhs0, rg, sweep);
-        else
+        else if constexpr (!kept_dirs(STAGE))
             hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, false, 12>), grid2, dim3(block), 0, st, a, rhs0, rg, sweep);
     } else {
         if (a.red != RED_NONE)
             hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, true, true, 18>), grid2, dim3(block), 0, st, a, rhs0, rg, sweep);
-        else if (a.guard.stop)
+        else if (guarded)
             hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, true, 18>), grid2, dim3(block), 0, st, a, rhs0, rg, sweep);
-        else
+        else if constexpr (!kept_dirs(STAGE))
             hipLaunchKernelGGL((k_dslash<GF, SF, R, NR, STAGE, false, false, 18>), grid2, dim3(block), 0, st, a, rhs0, rg, sweep);
     }
     return hipGetLastError();
@@ -1242,6 +1250,10 @@ hipError_t launch_tile(const DslashArgs &a, int rhs0, const DslashTile &t, hipSt
     switch (t.nr * 100 + t.stage) {
     case 99: return launch_cfg<GF, SF, R, 1, -1>(a, rhs0, t.rg, t.block, t.grid, t.sweep, st, nblocks);
     case 98: return launch_cfg<GF, SF, R, 1, -2>(a, rhs0, t.rg, t.block, t.grid, t.sweep, st, nblocks);
+    case 88: return launch_cfg<GF, SF, R, 1, -12>(a, rhs0, t.rg, t.block, t.grid, t.sweep, st, nblocks);
+    case 78: return launch_cfg<GF, SF, R, 1, -22>(a, rhs0, t.rg, t.block, t.grid, t.sweep, st, nblocks);
+    case 68: return launch_cfg<GF, SF, R, 1, -32>(a, rhs0, t.rg, t.block, t.grid, t.sweep, st, nblocks);
+    case 58: return launch_cfg<GF, SF, R, 1, -42>(a, rhs0, t.rg, t.block, t.grid, t.sweep, st, nblocks);
     case 101: return launch_cfg<GF, SF, R, 1, 1>(a, rhs0, t.rg, t.block, t.grid, t.sweep, st, nblocks);
     case 102: return launch_cfg<GF, SF, R, 1, 2>(a, rhs0, t.rg, t.block, t.grid, t.sweep, st, nblocks);
     case 104: return launch_cfg<GF, SF, R, 1, 4>(a, rhs0, t.rg, t.block, t.grid, t.sweep, st, nblocks);

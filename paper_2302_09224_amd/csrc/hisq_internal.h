@@ -174,6 +174,8 @@ DslashPlan dslash_plan(const hisq_fmt &f, const Geom &g, int nrhs, const DslashA
 // the plan from the shapes already in the table (tuned, fixed or loaded), else
 // the default shapes: never tunes, reads no file, allocates nothing
 DslashPlan dslash_plan_lookup(const hisq_fmt &f, const Geom &g, int nrhs, int long_recon);
+// the plan of an operator (one right-hand side) that a solver applies in every iteration
+void dslash_keep_links(const hisq_fmt &f, const Geom &g, int long_recon, DslashPlan &plan);
 // launch a plan; nblocks[j] receives the block count used for right-hand side j
 hipError_t launch_dslash(const DslashArgs &a, const hisq_fmt &f, const DslashPlan &plan, hipStream_t st,
                          int *nblocks);

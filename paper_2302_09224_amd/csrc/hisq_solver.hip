@@ -263,6 +263,7 @@ struct Run {
         const hisq_fmt f64 = {HISQ_GAUGE_F64, HISQ_SPINOR_F64, 64};
         DslashArgs ps = dargs(gs, B->ts, B->rs, 1);
         plan_s = dslash_plan(fmt, g, 1, &ps, st);
+        dslash_keep_links(fmt, g, ps.long_recon, plan_s);
         nb_s = dslash_tile_blocks(g, plan_s.tile[0]);
         DslashArgs p64 = dargs(g64, B->t64, B->x64, 1);
         plan_64 = dslash_plan(f64, g, 1, &p64, st);
