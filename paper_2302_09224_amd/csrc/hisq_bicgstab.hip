@@ -18,7 +18,7 @@
 //   l passes of the modified Gram-Schmidt (row i: r_j -= tau_{i-1,j} r_{i-1} for j >= i, and
 //   the dot products with r_i in the same pass), the closing updates, the cycle's record.
 // (As a launch per operation a cycle of l = 4 took 108 launches; 16^4 with 20-bit
-// spinors, m = 0.05 to 1e-12: 39 -> 15.7 ms.)
+// spinors, m = 0.05 to 1e-12: 39 -> 15.3 ms.)
 // A cycle whose |r_0|^2 asks for a reliable update, or that breaks down, lowers
 // the guard of the cycles behind it; the host reads each cycle's record from
 // pinned memory, with the next cycle already enqueued.
