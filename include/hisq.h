@@ -506,7 +506,14 @@ void hisq_tune_clear(void);
  * the first shape lookup of the process (if it exists; keys already fixed by
  * hisq_tune_set or hisq_tune_load keep their shapes) and every shape the
  * autotuner chooses afterwards is appended to it, so later processes on the
- * same device and runtime do not tune again. */
+ * same device and runtime do not tune again.
+ * Besides the shapes of hisq_tune_set a line may hold blocks of 64 threads and,
+ * for nr == rg == 1, the stages -12, -22, -32 and -42 (as -2, the links of
+ * 1..4 directions kept in the memory-side cache), which the autotuner chooses
+ * itself.  A solver's iterated operator on one right-hand side takes block,
+ * grid and sweep of a tuned or loaded shape, and one of these stages where the
+ * links fit (the same results bit for bit); a shape of hisq_tune_set is used
+ * as it is. */
 hisq_status hisq_tune_save(const char *path);
 hisq_status hisq_tune_load(const char *path, int *nloaded);
 
