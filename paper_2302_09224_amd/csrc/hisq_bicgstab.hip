@@ -485,9 +485,9 @@ __global__ void __launch_bounds__(BL_BLOCK) k_bl_restart(char *r0, char *rt, int
 }
 
 // The record of a cycle (op 0; in: the closing updates' partials), of a true
-// residual (op 1; in: |b - M x|^2 partials) or of |b|^2 (op 2), and what it
-// decides: a cycle that asks for a reliable update closes the cycles behind it,
-// a true residual opens them again.
+// residual (op 1; in: |b - M x|^2 partials) or of |b|^2 (op 2: the target is
+// tol^2 |b|^2 from then on), and what it decides: a cycle that asks for a
+// reliable update closes the cycles behind it, a true residual opens them again.
 __global__ void k_bl_record(BlCtl *c, Sums in, int op, BlHost *host) {
     __shared__ double lds[16 * 3];
     const bool ran = op != 0 || c->stop == 0;
@@ -519,6 +519,8 @@ __global__ void k_bl_record(BlCtl *c, Sums in, int op, BlHost *host) {
     } else if (op == 1) {
         c->rmax2 = v[2];
         if (!c->broke) c->stop = 0;
+    } else if (op == 2) {
+        c->tol2 *= v[2];   // tol^2 |b|^2
     }
     const unsigned long long seq = c->seq + 1;
     c->seq = seq;
@@ -915,7 +917,7 @@ extern "C" hisq_status hisq_bicgstab_solve(double *x, const double *b, const his
     hipLaunchKernelGGL(k_bl_split, dim3(B.nbl), dim3(BL_BLOCK), 0, B.st, x64, x, g, L.fb64);
     hipLaunchKernelGGL(k_bl_split, dim3(B.nbl), dim3(BL_BLOCK), 0, B.st, b64, b, g, L.fb64);
     HISQ_TRY_HIP(hipGetLastError());
-    {   // rho0 = 1, alpha = 0, omega = 1 (entering a cycle: -omega rho0); tol2 becomes tol^2 |b|^2 with |b|^2
+    {   // rho0 = 1, alpha = 0, omega = 1 (entering a cycle: -omega rho0); tol2 is multiplied by |b|^2 in its record
         BlCtl c0;
         memset(&c0, 0, sizeof(c0));
         c0.rho_c[0] = -1.0;
