@@ -371,7 +371,7 @@ size_t hisq_bicgstab_workspace_bytes(const int dims[4], int l, hisq_fmt sloppy);
  * stats: iters = operator applications (2 per BiCG step), reliable_updates,
  * true_resid, seconds.  p->maxiter bounds the operator applications
  * (HISQ_ENOCONV beyond, x is the last iterate); HISQ_EBREAKDOWN when a BiCG
- * or minimal-residual denominator vanishes.  Runs on a library-owned stream
+ * or minimal-residual denominator vanishes or a residual is not finite.  Runs on a library-owned stream
  * ordered after `stream` and returns when x is written: every scalar of the
  * method is formed on the device, each cycle (l BiCG steps and the
  * minimal-residual step) is enqueued as a whole (replayed as a captured

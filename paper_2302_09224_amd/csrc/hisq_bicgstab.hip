@@ -518,6 +518,10 @@ __global__ void k_bl_record(BlCtl *c, Sums in, int op, BlHost *host) {
         }
     } else if (op == 1) {
         c->rmax2 = v[2];
+        if (!__builtin_isfinite(v[2])) {
+            c->broke = 2;
+            c->stop = -1;
+        }
         if (!c->broke) c->stop = 0;
     } else if (op == 2) {
         c->tol2 *= v[2];   // tol^2 |b|^2
@@ -948,7 +952,9 @@ extern "C" hisq_status hisq_bicgstab_solve(double *x, const double *b, const his
         sto->status = HISQ_OK;
         return HISQ_OK;
     }
-    if (r2 > tol2) {
+    if (!std::isfinite(b2) || !std::isfinite(r2)) {
+        status = set_error(HISQ_EBREAKDOWN, "bicgstab: non-finite initial residual");
+    } else if (r2 > tol2) {
         HISQ_TRY(B.restart(r64, true));
         HISQ_TRY_HIP(hipMemsetAsync(B.u.p[0], 0, 2 * L.fb, B.st));
         hipGraphExec_t exec = nullptr;
@@ -1024,6 +1030,10 @@ extern "C" hisq_status hisq_bicgstab_solve(double *x, const double *b, const his
             pace.reset();
             HISQ_TRY(B.residual64(r64, x64, b64, &r2));
             rus++;
+            if (!std::isfinite(r2)) {
+                status = set_error(HISQ_EBREAKDOWN, "bicgstab: non-finite true residual");
+                break;
+            }
             if (r2 <= tol2) break;
             HISQ_TRY(B.restart(r64, false));
         }
