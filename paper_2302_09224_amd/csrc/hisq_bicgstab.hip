@@ -56,10 +56,10 @@ struct VecList {
 };
 
 // device scalars of one solve (complex values as re, im).  A kernel reads no
-// field that its own first block writes.
+// field that its own first block writes, but for stop (see Guard).
 struct BlCtl {
-    int stop;     // guard of every kernel of a cycle: 0 while running, below after a breakdown (-1) or when a
-                  // reliable update is due (-2)
+    int stop;     // guard of a cycle's launches, which run up to this one: STOP_NEVER while the method goes on, the
+                  // launch that broke down, -1 once its cycle is recorded, -2 when a reliable update is due
     int broke;    // 1: a BiCG or minimal-residual denominator vanished, 2: non-finite residual
     int due;      // the last cycle asked for a reliable update
     int cycles;   // completed
@@ -144,9 +144,9 @@ template <class R> __device__ __forceinline__ double bl_norm(const CVec<R> &w) {
 }
 
 // sums of block partials too many for every block of the consumer (one block, fixed order)
-template <int NV> __global__ void k_bl_sum(const double *partial, int n, double *out, const int *stop) {
+template <int NV> __global__ void k_bl_sum(const double *partial, int n, double *out, Guard gd) {
     __shared__ double lds[16 * NV];
-    if (stop && *stop < 0) return;
+    if (!gd.pass()) return;
     double v[NV];
     all_sums<NV>(partial, n, v, lds);
     if (threadIdx.x == 0) {
@@ -159,9 +159,9 @@ template <int NV> __global__ void k_bl_sum(const double *partial, int n, double 
 // beta = alpha rho1 / rho0, u_i = r_i - beta u_i; block row i <= j.
 template <int SF, class R>
 __global__ void __launch_bounds__(BL_BLOCK) k_bl_dir(VecList u, VecList r, BlCtl *c, Sums in, int nv, int j, size_t vh,
-                                                     size_t fb) {
+                                                     size_t fb, Guard gd) {
     __shared__ double lds[3 * BL_WAVES];
-    if (c->stop < 0) return;
+    if (!gd.pass()) return;
     // the first site's words are on their way while the partials are added up
     char *ui = u.p[blockIdx.y];
     const char *ri = r.p[blockIdx.y];
@@ -190,7 +190,7 @@ __global__ void __launch_bounds__(BL_BLOCK) k_bl_dir(VecList u, VecList r, BlCtl
         c->rho[j][1] = rho1[1];
         if (bad) {
             c->broke = 1;
-            c->stop = -1;
+            c->stop = gd.j;
         }
     }
     if (bad) return;
@@ -216,9 +216,9 @@ __global__ void __launch_bounds__(BL_BLOCK) k_bl_dir(VecList u, VecList r, BlCtl
 // r_i -= alpha u_{i+1} (block row i <= j) and x += alpha u_0 (row j + 1).
 template <int SF, class R>
 __global__ void __launch_bounds__(BL_BLOCK) k_bl_res(VecList u, VecList r, char *x64, BlCtl *c, Sums in, int j,
-                                                     size_t vh, size_t fb, size_t fb64) {
+                                                     size_t vh, size_t fb, size_t fb64, Guard gd) {
     __shared__ double lds[2 * BL_WAVES];
-    if (c->stop < 0) return;
+    if (!gd.pass()) return;
     const int k = blockIdx.y;
     size_t i = bl_tid();
     SpinRaw<SF> r0, u0;   // row j + 1: u_0 alone
@@ -241,7 +241,7 @@ __global__ void __launch_bounds__(BL_BLOCK) k_bl_res(VecList u, VecList r, char 
     if (bl_first()) {
         if (bad) {
             c->broke = 1;
-            c->stop = -1;
+            c->stop = gd.j;
         } else {
             c->alpha[j][0] = alpha[0];
             c->alpha[j][1] = alpha[1];
@@ -267,15 +267,16 @@ __global__ void __launch_bounds__(BL_BLOCK) k_bl_res(VecList u, VecList r, char 
 }
 
 // the scalars of a finished row i: sigma_i = |r_i|^2, gamma'_i = <r_i, r_0> / sigma_i, tau_ij =
-// <r_i, r_j> / sigma_i; v: <r_0, r_i>, |r_i|^2, <r_i, r_{i+1}>, ...  Returns false when sigma_i vanishes.
-__device__ __forceinline__ bool bl_row(BlCtl *c, const double *v, int i, int l) {
+// <r_i, r_j> / sigma_i; v: <r_0, r_i>, |r_i|^2, <r_i, r_{i+1}>, ...  Returns false when sigma_i
+// vanishes, and launch `here` is then the last of the cycle.
+__device__ __forceinline__ bool bl_row(BlCtl *c, const double *v, int i, int l, int here) {
     const double s2 = v[2];
     const bool bad = !(s2 > 0.0) || !__builtin_isfinite(s2);
     if (bl_first()) {
         c->sigma[i] = s2;
         if (bad) {
             c->broke = 1;
-            c->stop = -1;
+            c->stop = here;
         } else {
             c->gp[i][0] = v[0] / s2;
             c->gp[i][1] = -v[1] / s2;
@@ -294,10 +295,10 @@ __device__ __forceinline__ bool bl_row(BlCtl *c, const double *v, int i, int l) 
 // partial[block * (2 m + 1) + k]: <r_0, r_i>, |r_i|^2, <r_i, r_{i+1}>, ...
 template <int SF, class R, int M>
 __global__ void __launch_bounds__(BL_BLOCK) k_bl_mgs(VecList r, BlCtl *c, Sums in, int i, int l, size_t vh, size_t fb,
-                                                     double *partial) {
+                                                     double *partial, Guard gd) {
     constexpr int NV = 2 * M + 1, NP = 2 * (M + 1) + 1;
     __shared__ double lds[NP * BL_WAVES], tl[M][2];
-    if (c->stop < 0) return;
+    if (!gd.pass()) return;
     const int m = l - i + 1;
     size_t t = bl_tid();
     SpinRaw<SF> w0, wp, w[M];
@@ -323,7 +324,7 @@ __global__ void __launch_bounds__(BL_BLOCK) k_bl_mgs(VecList r, BlCtl *c, Sums i
             }
         }
         __syncthreads();
-        const bool ok = bl_row(c, lds, i - 1, l);
+        const bool ok = bl_row(c, lds, i - 1, l, gd.j);
         if (!ok) return;
         if (threadIdx.x < M) {
             const int k = threadIdx.x;
@@ -374,12 +375,12 @@ __global__ void __launch_bounds__(BL_BLOCK) k_bl_mgs(VecList r, BlCtl *c, Sums i
 template <int SF, class R>
 __global__ void __launch_bounds__(BL_BLOCK) k_bl_close(VecList u, VecList r, const char *rt, char *x64, BlCtl *c,
                                                        Sums in, int l, size_t vh, size_t fb, size_t fb64,
-                                                       double *partial) {
+                                                       double *partial, Guard gd) {
     __shared__ double lds[3 * BL_WAVES], gm[BL_MAXL + 1][2], cx[BL_MAXL][2], cu[BL_MAXL][2], cr[BL_MAXL][2];
-    if (c->stop < 0) return;
+    if (!gd.pass()) return;
     double v[3];
     all_sums<3>(in.p, in.n, v, lds);   // <r_0, r_l>, |r_l|^2
-    if (!bl_row(c, v, l, l)) return;
+    if (!bl_row(c, v, l, l, gd.j)) return;
     if (threadIdx.x == 0) {
         gm[l][0] = v[0] / v[2];
         gm[l][1] = -v[1] / v[2];
@@ -490,7 +491,7 @@ __global__ void __launch_bounds__(BL_BLOCK) k_bl_restart(char *r0, char *rt, int
 // reliable update closes the cycles behind it, a true residual opens them again.
 __global__ void k_bl_record(BlCtl *c, Sums in, int op, BlHost *host) {
     __shared__ double lds[16 * 3];
-    const bool ran = op != 0 || c->stop == 0;
+    const bool ran = op != 0 || c->stop == STOP_NEVER;
     double v[3] = {0.0, 0.0, 0.0};
     if (ran) {
         if (op == 0) {
@@ -522,9 +523,11 @@ __global__ void k_bl_record(BlCtl *c, Sums in, int op, BlHost *host) {
             c->broke = 2;
             c->stop = -1;
         }
-        if (!c->broke) c->stop = 0;
+        if (!c->broke) c->stop = STOP_NEVER;
     } else if (op == 2) {
         c->tol2 *= v[2];   // tol^2 |b|^2
+    } else if (c->stop >= 0) {
+        c->stop = -1;      // broken down in this cycle: those behind it do nothing
     }
     const unsigned long long seq = c->seq + 1;
     c->seq = seq;
@@ -608,13 +611,16 @@ struct Bl {
     double alg = 0.0;
     BlCtl *ctl = nullptr;         // device scalars
     const int *stopp = nullptr;   // &ctl->stop
+    int at = 0;                   // of the cycle's next guarded launch
     BlHost *host = nullptr;
 
+    Guard guard() { return Guard{stopp, at++, 0}; }
+
     // block partials for the next kernel: as they are when few, else added up in a launch
-    template <int NV> hisq_status sums(const double *partial, int n, bool guarded, Sums *out) {
+    template <int NV> hisq_status sums(const double *partial, int n, Sums *out) {
         *out = Sums{partial, n};
         if (n * NV <= SUMS_DIRECT) return HISQ_OK;
-        hipLaunchKernelGGL((k_bl_sum<NV>), dim3(1), dim3(1024), 0, st, partial, n, ctl->red, guarded ? stopp : nullptr);
+        hipLaunchKernelGGL((k_bl_sum<NV>), dim3(1), dim3(1024), 0, st, partial, n, ctl->red, guard());
         HISQ_TRY_HIP(hipGetLastError());
         *out = Sums{ctl->red, 1};
         return HISQ_OK;
@@ -625,14 +631,14 @@ struct Bl {
         *out = Sums{partial, nbl};
         if (nbl <= 512 && nv > 3) return HISQ_OK;
         switch (nv) {
-        case 3: return sums<3>(partial, nbl, true, out);
-        case 5: return sums<5>(partial, nbl, true, out);
-        case 7: return sums<7>(partial, nbl, true, out);
-        case 9: return sums<9>(partial, nbl, true, out);
-        case 11: return sums<11>(partial, nbl, true, out);
-        case 13: return sums<13>(partial, nbl, true, out);
-        case 15: return sums<15>(partial, nbl, true, out);
-        case 17: return sums<17>(partial, nbl, true, out);
+        case 3: return sums<3>(partial, nbl, out);
+        case 5: return sums<5>(partial, nbl, out);
+        case 7: return sums<7>(partial, nbl, out);
+        case 9: return sums<9>(partial, nbl, out);
+        case 11: return sums<11>(partial, nbl, out);
+        case 13: return sums<13>(partial, nbl, out);
+        case 15: return sums<15>(partial, nbl, out);
+        case 17: return sums<17>(partial, nbl, out);
         default: return set_error(HISQ_EINVAL, "bicgstab: l out of range");
         }
     }
@@ -660,7 +666,7 @@ struct Bl {
         a.in = in;
         a.x = in;
         a.a = 2.0 * mass;
-        a.guard = Guard{stopp, 0, 0};
+        a.guard = guard();
         if (dot) {
             a.red = RED_CDOT;
             a.z = rt;
@@ -674,7 +680,7 @@ struct Bl {
     template <int M> hisq_status mgs_row(int i, const Sums &in, double *out) {
         HISQ_BL_DISPATCH(f.spinor, f.compute,
                          hipLaunchKernelGGL((k_bl_mgs<SFc, Rc, M>), dim3(nbl), dim3(BL_BLOCK), 0, st, r, ctl, in, i, l,
-                                            vh, fb, out));
+                                            vh, fb, out, guard()));
         HISQ_TRY_HIP(hipGetLastError());
         return HISQ_OK;
     }
@@ -683,21 +689,22 @@ struct Bl {
     hisq_status enq_cycle(char *x64) {
         const double bs = spinor_site_bytes(f.spinor);
         Sums in;
+        at = 0;
         for (int j = 0; j < l; j++) {
             const int nv = j ? 2 : 3;
             if (j)
-                HISQ_TRY(sums<2>(dpart, 2 * nb_s, true, &in));
+                HISQ_TRY(sums<2>(dpart, 2 * nb_s, &in));
             else
-                HISQ_TRY(sums<3>(vpart[0], nbl, true, &in));
+                HISQ_TRY(sums<3>(vpart[0], nbl, &in));
             HISQ_BL_DISPATCH(f.spinor, f.compute,
                              hipLaunchKernelGGL((k_bl_dir<SFc, Rc>), dim3(nbl, j + 1), dim3(BL_BLOCK), 0, st, u, r, ctl,
-                                                in, nv, j, vh, fb));
+                                                in, nv, j, vh, fb, guard()));
             HISQ_TRY_HIP(hipGetLastError());
             HISQ_TRY(matvec(u.p[j + 1], u.p[j], true));
-            HISQ_TRY(sums<2>(dpart, 2 * nb_s, true, &in));
+            HISQ_TRY(sums<2>(dpart, 2 * nb_s, &in));
             HISQ_BL_DISPATCH(f.spinor, f.compute,
                              hipLaunchKernelGGL((k_bl_res<SFc, Rc>), dim3(nbl, j + 2), dim3(BL_BLOCK), 0, st, u, r, x64,
-                                                ctl, in, j, vh, fb, fb64));
+                                                ctl, in, j, vh, fb, fb64, guard()));
             HISQ_TRY_HIP(hipGetLastError());
             HISQ_TRY(matvec(r.p[j + 1], r.p[j], j + 1 < l));
             alg += 2.0 * vh * ((j + 1) * 6.0 * bs + bs + 96.0);
@@ -721,7 +728,7 @@ struct Bl {
         }
         HISQ_BL_DISPATCH(f.spinor, f.compute,
                          hipLaunchKernelGGL((k_bl_close<SFc, Rc>), dim3(nbl, 2), dim3(BL_BLOCK), 0, st, u, r, rt, x64,
-                                            ctl, in, l, vh, fb, fb64, vpart[0]));
+                                            ctl, in, l, vh, fb, fb64, vpart[0], guard()));
         HISQ_TRY_HIP(hipGetLastError());
         alg += 2.0 * vh * (bs * (2.0 * l + 5.0) + 96.0);
         HISQ_TRY(record(Sums{vpart[0], nbl}, 0));
@@ -924,6 +931,7 @@ extern "C" hisq_status hisq_bicgstab_solve(double *x, const double *b, const his
     {   // rho0 = 1, alpha = 0, omega = 1 (entering a cycle: -omega rho0); tol2 is multiplied by |b|^2 in its record
         BlCtl c0;
         memset(&c0, 0, sizeof(c0));
+        c0.stop = STOP_NEVER;
         c0.rho_c[0] = -1.0;
         c0.delta2 = q.delta > 0 ? q.delta * q.delta : 0.0;
         c0.tol2 = tol * tol;
@@ -1024,7 +1032,7 @@ extern "C" hisq_status hisq_bicgstab_solve(double *x, const double *b, const his
             s.lead = rec.lead;
             s.k = cycles;
             pace.update(s);
-            if (rec.stop == 0) continue;
+            if (rec.stop == STOP_NEVER) continue;
             // ---- reliable update ----
             inflight = 0;   // the cycle behind, if any, does nothing; its record is skipped
             pace.reset();

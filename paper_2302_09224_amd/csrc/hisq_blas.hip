@@ -505,12 +505,8 @@ __global__ void __launch_bounds__(BLAS_BLOCK) k_cg_axpy(char *r, const char *ap,
             ctl->o_zeta_prev[t] = ctl->zeta_prev[t];
         }
         if (t == 0) {
-            ctl->pi = pi;
-            if (bad) {
-                ctl->stop = gd.j - 1;
-                ctl->reason = STOP_BREAKDOWN;
-                ctl->breakdown = 1;
-            } else {
+            ctl->pi = pi;   // a breakdown ends the block in k_cg_pupdate
+            if (!bad) {
                 ctl->alpha = alpha;
                 ctl->alpha_buf[jb] = alpha;
                 ctl->o_k = ctl->k;
@@ -562,6 +558,15 @@ __global__ void __launch_bounds__(BLAS_BLOCK) k_cg_axpy(char *r, const char *ap,
 __device__ __forceinline__ bool cg_scalars(SolverCtrl *c, double rn, double g, const double *pp, int j, int multishift,
                                            int jb, bool writer, double &beta_out) {
     const int lane = threadIdx.x & 63;
+    const double pi = c->pi;
+    if (!(pi > 0.0) || !__builtin_isfinite(pi)) {   // <p,Ap>: the residual was not updated
+        if (writer && lane == 0) {
+            c->stop = j;
+            c->reason = STOP_BREAKDOWN;
+            c->breakdown = 1;
+        }
+        return false;
+    }
     const int k = c->o_k + 1;
     const double rho = c->o_rho;
     if (!__builtin_isfinite(rn) || !__builtin_isfinite(g)) {
@@ -624,7 +629,7 @@ __device__ __forceinline__ bool cg_scalars(SolverCtrl *c, double rn, double g, c
         // previous update.
         const double p2 = *pp;   // |p_k|^2 from the update that produced p_k
         rnorm = sqrt(rn);
-        anorm = p2 > 0.0 ? fmax(c->o_anorm, c->pi / p2) : c->o_anorm;
+        anorm = p2 > 0.0 ? fmax(c->o_anorm, pi / p2) : c->o_anorm;
         const double e = c->eps_s * (rnorm + fabs(c->alpha) * anorm * sqrt(p2));
         dev = sqrt(c->o_dev * c->o_dev + e * e);
         const double th = sqrt(c->eps_s);

@@ -578,14 +578,17 @@ template <int NV> __device__ __forceinline__ void all_sums(const double *partial
     __syncthreads();
 }
 
-// Solver iteration guard: a kernel that belongs to iteration j of a block of
-// iterations runs iff j < *stop (strict) or j <= *stop; the solver's scalar
-// kernels lower *stop to end a block early (reliable update, convergence).
-// *stop is written only by earlier kernels of the stream, never during a
-// guarded dispatch, and is read first thing: a plain load the compiler turns
-// into one scalar load per wave (the packet processor invalidates the scalar
-// cache between dispatches), so the wave's vector loads do not queue behind a
-// coherent vector load of the flag.
+// Solver iteration guard: a kernel that belongs to step j of a unit (an iteration
+// of CG, a launch of a BiCGStab cycle) runs iff j < *stop (strict) or j <= *stop;
+// the kernels lower *stop to end a unit early (reliable update, convergence,
+// breakdown).  A kernel that does so from one of its blocks while others may still
+// be reading *stop lowers it to its own j and is itself guarded by j <= *stop:
+// whichever value a wave reads, all waves of the launch pass (a block whose waves
+// disagreed would miss the shares of those that left), and what the launch leaves
+// undone is decided from values that all its blocks share.  *stop is read first
+// thing, by a plain load the compiler turns into one scalar load per wave (the
+// packet processor invalidates the scalar cache between dispatches), so the wave's
+// vector loads do not queue behind a coherent vector load of the flag.
 struct Guard {
     const int *stop;
     int j;

@@ -1,5 +1,6 @@
 """BiCGStab(l) where it cannot go on: the status, what it counts, and the iterate it hands back."""
-import numpy as np
+import ctypes
+
 import pytest
 import torch
 
@@ -29,3 +30,37 @@ def test_non_finite_input_is_a_breakdown(where, bad):
     with pytest.raises(hisq.HisqError) as e:
         hisq.bicgstab_solve(b, g64, gs, MASS, sloppy="single", x0=x0)
     assert e.value.status == -5
+
+
+def raw_solve(hisq, b, x, g64, gs, mass, tol, l, sloppy):
+    """(status, stats), x overwritten: what a caller has in hand after a status that the binding raises for"""
+    f = hisq.fmt(sloppy)
+    n = hisq.hisq_bicgstab_workspace_bytes(g64.dims, l, f)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    st, p = hisq.hisq_solver_stats(), hisq.hisq_solver_params_default()
+    status = hisq.load().hisq_bicgstab_solve(
+        ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(b.data_ptr()), ctypes.byref(g64.desc), ctypes.byref(gs.desc),
+        mass, tol, l, f, ctypes.byref(p), ctypes.c_void_p(ws.data_ptr()), n, ctypes.byref(st), None)
+    return status, st.as_dict()
+
+
+# M = 2m without links: the first step leaves r_0 = 0 exactly (m a power of two), so l = 1 ends in the closing
+# updates (|r_1|^2 = 0) and l = 4 in its second step (<r~, u_2> = 0); the larger lattices hold more blocks than
+# fit the device at once
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (16, 16, 16, 24), (24, 24, 24, 48)])
+@pytest.mark.parametrize("l", [1, 4])
+def test_iterate_handed_back(dims, l):
+    hisq = need_gpu()
+    V = oracle.volume(dims)
+    zero = torch.zeros((4, V, 3, 3), dtype=torch.complex128, device="cuda")
+    g64, gs = hisq.pack_gauge(zero, zero, dims, hisq.GAUGE_F64), hisq.pack_gauge(zero, zero, dims, hisq.GAUGE_F32)
+    b = inputs.gaussian_spinor(V, inputs.SOURCE_SEED, device="cuda")
+    x = torch.zeros_like(b)
+    torch.cuda.synchronize()
+    status, st = raw_solve(hisq, b, x, g64, gs, 0.125, 1e-12, l, "single")
+    assert status == -5 and "breakdown" in hisq.hisq_last_error(), st
+    # alpha = <r~, r_0> / <r~, u_1>, 4 but for the rounding of two sums of squares in different orders, each at most
+    # 100 additions deep
+    want = 4.0 * b.to(torch.complex64).to(torch.complex128)
+    assert bool(((x - want).abs() <= 2.0 ** -44 * want.abs()).all())
+    assert st["true_resid"] <= 2.0 ** -24

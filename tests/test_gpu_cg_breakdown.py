@@ -1,0 +1,51 @@
+"""CG and batched CG on an operator that is not positive definite: the status, what
+it counts, and the iterate it hands back."""
+import pytest
+import torch
+
+import oracle
+from gpu_util import need_gpu
+from paper_2302_09224_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+DIMS, MASS = (8, 8, 8, 12), 0.05
+
+
+def solve(hisq, sloppy, shift, nrhs=0, **opts):
+    """(status, stats, x0, x)"""
+    fat, lng = inputs.make_links(DIMS, "near_unit", device="cuda")
+    f, vh = hisq.fmt(sloppy), oracle.volume(DIMS) // 2
+    g64, gs = hisq.pack_gauge(fat, lng, DIMS, hisq.GAUGE_F64), hisq.pack_gauge(fat, lng, DIMS, f.gauge)
+    b = torch.view_as_real(inputs.gaussian_spinor(vh, inputs.RHS_SEED, nrhs=max(1, nrhs)).cuda())
+    x0 = 0.5 * b
+    x, p = x0.clone(), hisq.hisq_solver_params_default()
+    for k, v in opts.items():
+        setattr(p, k, v)
+    n = hisq.hisq_cg_batched_workspace_bytes(DIMS, nrhs, f, p) if nrhs else hisq.hisq_cg_workspace_bytes(DIMS, f, p)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    if nrhs:
+        status, st = hisq.hisq_cg_solve_batched(x, b, nrhs, g64.desc, gs.desc, MASS, shift, 1e-10, f, p, ws, n)
+    else:
+        status, st = hisq.hisq_cg_solve(x, b, g64.desc, gs.desc, MASS, shift, 1e-10, f, p, ws, n)
+    return status, st.as_dict(), x0, x
+
+
+# negative definite: <p, A p> < 0 at once; ring lengths at which the first iteration is the last slot, or is not
+@pytest.mark.parametrize("graph", [0, 1])
+@pytest.mark.parametrize("grad_buffer", [1, 8])
+@pytest.mark.parametrize("sloppy", ["single", "half"])
+def test_first_step(sloppy, grad_buffer, graph):
+    hisq = need_gpu()
+    status, st, x0, x = solve(hisq, sloppy, -50.0, grad_buffer=grad_buffer, use_graph=graph)
+    assert status == -5 and st["iters"] == 0, st
+    assert torch.equal(x, x0)
+
+
+# indefinite: <p, A p> changes sign after some iterations
+@pytest.mark.parametrize("grad_buffer", [1, 3, 8])
+def test_later_step(grad_buffer):
+    hisq = need_gpu()
+    status, st, _, x = solve(hisq, "double", -6.0, grad_buffer=grad_buffer, delta=0.0)
+    assert status == -5 and st["iters"] > 0, st
+    assert bool(torch.isfinite(x).all())
