@@ -1015,11 +1015,9 @@ extern "C" hisq_status hisq_bicgstab_solve(double *x, const double *b, const his
             BlRecord rec;
             HISQ_TRY(B.wait(B.host->launched - (unsigned long long)inflight + 1, &rec));
             inflight--;
-            if (rec.cycles > cycles) {
-                cycles = rec.cycles;
-                B.matvecs += 2 * l;
-                B.alg += cyc_alg;
-            }
+            cycles = rec.cycles;
+            B.matvecs += 2 * l;   // of a cycle that broke down too
+            B.alg += cyc_alg;
             if (rec.broke == 2) {
                 status = set_error(HISQ_EBREAKDOWN, "bicgstab: non-finite residual");
                 break;

@@ -64,3 +64,4 @@ def test_iterate_handed_back(dims, l):
     want = 4.0 * b.to(torch.complex64).to(torch.complex128)
     assert bool(((x - want).abs() <= 2.0 ** -44 * want.abs()).all())
     assert st["true_resid"] <= 2.0 ** -24
+    assert st["iters"] == 2 * l and st["dslash_sloppy"] == 4 * l     # whole cycles, the last one included
