@@ -55,7 +55,7 @@ template <int NV> __global__ void k_bfin_sum(SolverCtrl *c, BSums in, BCols cols
 
 // beta and the decisions of one iteration: block b for its system, then the
 // block that arrives last for all of them
-enum { BF_RU = 1, BF_CONV = 2, BF_BAD = 4 };
+enum { BF_RU = 1, BF_CONV = 2, BF_BAD = 4, BF_PAP = 8 };   // BF_PAP: BF_BAD found in <p,Ap>
 __global__ void k_bfin_beta(SolverCtrl *c, BSums rr, int nrhs, BCols cols, Guard gd) {
     __shared__ double lds[2 * (FIN_THREADS / 64)];
     if (!gd.pass()) return;
@@ -67,7 +67,9 @@ __global__ void k_bfin_beta(SolverCtrl *c, BSums rr, int nrhs, BCols cols, Guard
     if (c->bactive[j]) {
         const double rn = v[0], g = v[1], pi = c->bpi[j];
         c->bk[j] += 1;
-        if (!(pi > 0.0) || !__builtin_isfinite(pi) || !__builtin_isfinite(rn) || !__builtin_isfinite(g)) {
+        if (!(pi > 0.0) || !__builtin_isfinite(pi)) {
+            flag = BF_BAD | BF_PAP;
+        } else if (!__builtin_isfinite(rn) || !__builtin_isfinite(g)) {
             flag = BF_BAD;
         } else {
             const double rho = c->brho[j];
@@ -89,7 +91,11 @@ __global__ void k_bfin_beta(SolverCtrl *c, BSums rr, int nrhs, BCols cols, Guard
     for (int i = 0; i < cols.n; i++) all |= c->bflag[(int)((cols.map >> (4 * i)) & 15ull)];
     int reason = (all & BF_BAD) ? STOP_BREAKDOWN : (all & BF_RU) ? STOP_RU : (all & BF_CONV) ? STOP_CONV : STOP_NONE;
     if (reason == STOP_BREAKDOWN) c->breakdown = 1;
-    const int k = c->k + 1;
+    if (all & BF_PAP) {   // no system's step counts when one of them had no step to take
+        for (int i = 0; i < nrhs; i++)
+            if (c->bactive[i]) c->bk[i] -= 1;
+    }
+    const int k = c->k + ((all & BF_PAP) ? 0 : 1);
     c->k = k;
     if (reason == STOP_NONE && k >= c->maxiter) {
         reason = STOP_MAXITER;

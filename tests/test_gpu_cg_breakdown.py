@@ -49,3 +49,12 @@ def test_later_step(grad_buffer):
     status, st, _, x = solve(hisq, "double", -6.0, grad_buffer=grad_buffer, delta=0.0)
     assert status == -5 and st["iters"] > 0, st
     assert bool(torch.isfinite(x).all())
+
+
+# a step that no system can take does not count, as in a lone solve
+@pytest.mark.parametrize("nrhs", [1, 3, 12])
+def test_batched_first_step(nrhs):
+    hisq = need_gpu()
+    status, st, x0, x = solve(hisq, "half", -50.0, nrhs=nrhs)
+    assert status == -5 and st["iters"] == 0 and st["refine_iters"][:nrhs] == [0] * nrhs, st
+    assert torch.equal(x, x0)
