@@ -717,6 +717,8 @@ extern "C" hisq_status hisq_cg_solve(double *x, const double *b, const hisq_gaug
     HISQ_TRY_HIP(launch_spinor_pack(B.x64, x, g.vh, SF_F64, R.st));
     HISQ_TRY_HIP(launch_spinor_pack(B.b64, b, g.vh, SF_F64, R.st));
     hisq_status s = cg_core(R, q, tol, 1, nullptr, 0.0, nullptr);
+    // b = 0: x = 0 whatever the initial guess
+    if (s == HISQ_OK && R.last.b2 == 0.0) HISQ_TRY_HIP(hipMemsetAsync(B.x64, 0, spinor_field_bytes(g.vh, SF_F64), R.st));
     if (s == HISQ_OK || s == HISQ_ENOCONV || s == HISQ_EBREAKDOWN) {
         hipError_t e = launch_spinor_unpack(x, B.x64, g.vh, SF_F64, R.st);
         if (e != hipSuccess && s == HISQ_OK) s = set_error(HISQ_EHIP, "unpack: %s", hipGetErrorString(e));

@@ -58,3 +58,24 @@ def test_batched_first_step(nrhs):
     status, st, x0, x = solve(hisq, "half", -50.0, nrhs=nrhs)
     assert status == -5 and st["iters"] == 0 and st["refine_iters"][:nrhs] == [0] * nrhs, st
     assert torch.equal(x, x0)
+
+
+@pytest.mark.parametrize("solver", ["cg", "batched", "multishift", "bicgstab"])
+def test_zero_source(solver):
+    """x = 0 whatever the initial guess"""
+    hisq = need_gpu()
+    fat, lng = inputs.make_links(DIMS, "near_unit", device="cuda")
+    g64, gs = hisq.pack_gauge(fat, lng, DIMS, hisq.GAUGE_F64), hisq.pack_gauge(fat, lng, DIMS, hisq.GAUGE_F32)
+    n = oracle.volume(DIMS) // (1 if solver == "bicgstab" else 2)
+    x0 = inputs.gaussian_spinor(n, inputs.RHS_SEED, device="cuda")
+    b = torch.zeros_like(x0)
+    if solver == "cg":
+        x, st = hisq.cg_solve(b, g64, gs, MASS, x0=x0)
+    elif solver == "batched":
+        x, st = hisq.cg_solve_batched(torch.stack([b, b]), g64, gs, MASS, sloppy="single", x0=torch.stack([x0, x0]))
+    elif solver == "bicgstab":
+        x, st = hisq.bicgstab_solve(b, g64, gs, MASS, x0=x0)
+    else:
+        x, st = hisq.multishift_cg_solve(b, [0.0, 0.1], 1e-10, g64, gs, gs, MASS, ref_fmt="single")
+        x = torch.stack(x)
+    assert st["status"] == "HISQ_OK" and not bool(x.any()), st
