@@ -135,7 +135,9 @@ size_t hisq_spinor_bytes(long nsites, int spinor_fmt);
  * Fixed-point formats scale each field by its own global max real component
  * (Sec. 2 footnote); q = round-half-even(u * Q / max), Q = 2^15-1 or 2^31-1.
  * FP32 rounds to nearest.  Synchronises `stream` (the scales are returned in *g).
- * Errors: EINVAL (dims/format/null), EALIGN, ERANGE (non-finite link), EHIP. */
+ * Errors: EINVAL (dims/format/null), EALIGN, ERANGE (non-finite link), EHIP.
+ * Links that are refused (here, or below for their form) leave the destinations
+ * and *g as they were. */
 hisq_status hisq_gauge_pack(hisq_gauge *g, void *fat_dst, void *long_dst,
                             const double *fat_src, const double *long_src,
                             const int dims[4], int gauge_fmt, void *stream);

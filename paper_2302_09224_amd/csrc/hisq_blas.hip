@@ -101,9 +101,10 @@ __global__ void k_absmax(const double *src, size_t n, double *partial) {
 }
 
 // Packed links are stored past the caches: they are not read again here, and the memory-
-// side cache is left to the canonical links, which the fixed-point formats and the
-// compressed long links read twice (FIX16 24^3x32 260 -> 229 us, FIX32 with eight-
-// parameter long links 32^4 615 -> 573 us, F64 24^4 315 -> 290 us).
+// side cache is left to the canonical links, which every call reads twice (for the scales
+// and the verdict, then to pack).  A call with ordinary stores and with these: FIX16 two-row
+// 24^3x32 254 and 237 us, FIX32 with eight-parameter long links 32^4 591 and 560 us, F32
+// 32^4 603 and 573 us, F64 24^4 255 and 238 us.
 template <class T> __device__ __forceinline__ void st_nt(char *p, T v) {
     __builtin_nontemporal_store(v, reinterpret_cast<T *>(p));
 }
@@ -125,18 +126,13 @@ __device__ __forceinline__ void sx24_store_row(char *base, size_t vh, size_t s, 
     st_nt<unsigned>(base + nrow * 16 * vh + r * 4 * vh + 4 * s, w[4]);
 }
 
-// canonical FP64 links [4][V][3][3] -> packed sub-fields (mu, parity).  The
-// fixed-point formats need the field's maximum first; the others (their values
-// do not depend on it) leave its block partials here, in the pass that reads
-// the links anyway.
-template <int GF> constexpr bool pack_needs_max() { return GF == GF_FIX16 || GF == GF_FIX32; }
-template <int GF> __global__ void k_gauge_pack(char *dst, const double *src, Geom g, const double *absmax, double *partial) {
-    __shared__ double lds[16];
-    double top = 0.0;
+// canonical FP64 links [4][V][3][3] -> packed sub-fields (mu, parity)
+template <int GF> __global__ void k_gauge_pack(char *dst, const double *src, Geom g, const LinkStats *ls, int lng) {
+    if (ls->verdict != LINKS_OK) return;
     const size_t V = 2 * (size_t)g.vh;
     const size_t vh = g.vh;
     const size_t sub = (size_t)gauge_matrix_bytes(GF) * vh;
-    const double m = pack_needs_max<GF>() ? *absmax : 0.0;
+    const double m = lng ? ls->long_max : ls->fat_max;
     const double c = GF == GF_FIX16 ? (m > 0.0 ? 32767.0 / m : 0.0) : (m > 0.0 ? 2147483647.0 / m : 0.0);
     for (size_t idx = gtid(); idx < 4 * V; idx += gstride()) {
         const int mu = (int)(idx / V);
@@ -149,20 +145,17 @@ template <int GF> __global__ void k_gauge_pack(char *dst, const double *src, Geo
         const int par = (x + y + z + t) & 1;
         const size_t s = site >> 1;
         char *base = dst + (size_t)(2 * mu + par) * sub;
-        // The whole link before the first store: loads behind a store, which might alias
-        // the link, had the formats that also take its maximum read it twice and wait
-        // nine times (F32 32^4 658 -> 392 us, 4.6 TB/s; F64 24^4 290 -> 196 us, 4.9 TB/s;
-        // SX24 two-row 32x28x28x24 359 -> 297 us)
+        // The whole link before the first store: a load behind a store, which might alias
+        // the link, waits for it (a call with loads between the stores and with these: F32
+        // 32^4 731 and 573 us, F64 24^4 331 and 238 us, SX24 32x28x28x24 371 and 330 us;
+        // the fixed-point formats convert a link before they store it and stay as they are).
+        // 573 us is 3.0 GB at 5.3 TB/s.
         double u[18];
 #pragma unroll
         for (int k = 0; k < 9; k++) {
             const f64x2 w = ld<f64x2>((const char *)(src + idx * 18 + 2 * k));
             u[2 * k] = w.x;
             u[2 * k + 1] = w.y;
-        }
-        if (!pack_needs_max<GF>()) {
-#pragma unroll
-            for (int k = 0; k < 18; k++) top = max_finite(top, u[k]);
         }
         if (GF == GF_F64) {
 #pragma unroll
@@ -215,10 +208,6 @@ template <int GF> __global__ void k_gauge_pack(char *dst, const double *src, Geo
             t2.y = q[17];
             st_nt<u32x2>(base + 64 * vh + 8 * s, t2);
         }
-    }
-    if (!pack_needs_max<GF>()) {
-        top = block_max(top, lds);
-        if (threadIdx.x == 0) partial[blockIdx.x] = top;
     }
 }
 
@@ -302,25 +291,27 @@ __global__ void k_long_check(const double *src, Geom g, double *partial) {
     }
 }
 
-// the field's statistics from the block partials: *max (NULL: none) from nmax
-// maxima, then the long check (check NULL: none) from ncheck tuples.  One block,
-// wave k for value k.
-__global__ void k_link_stats(LinkStats *out, double *max, const double *pmax, int nmax, const double *pcheck, int ncheck) {
+// the fields' statistics and the verdict from the block partials.  One block, wave k
+// for value k of the long check, the last wave for the fat field; long fields of 18
+// reals (plong) have the maximum alone.
+__global__ void k_link_stats(LinkStats *out, const double *pfat, int nfat, const double *plong, const double *pcheck,
+                             int nlong, double tol) {
+    __shared__ double lds[LC + 1];
     const int k = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (max && k == LC) {
-        double m = 0.0;
-        for (int i = lane; i < nmax; i += 64) m = fmax(m, pmax[i]);
-        for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
-        if (lane == 0) *max = m;
+    const bool fat = k == LC, top = fat || (!pcheck && k == LC - 1);
+    double w = k == 0 ? 1e300 : 0.0;
+    if (top) {
+        const double *p = fat ? pfat : plong;
+        const int n = fat ? nfat : nlong;
+        for (int i = lane; i < n; i += 64) w = fmax(w, p[i]);
+    } else if (pcheck) {
+        for (int i = lane; i < nlong; i += 64) w = lc_join(k, w, pcheck[LC * i + k]);
     }
-    if (!pcheck) return;
-    __shared__ double lds[LC];
-    if (k < LC) {
-        double w = k == 0 ? 1e300 : 0.0;
-        for (int i = lane; i < ncheck; i += 64) w = lc_join(k, w, pcheck[LC * i + k]);
-        for (int o = 32; o > 0; o >>= 1) w = lc_join(k, w, __shfl_xor(w, o, 64));
-        if (lane == 0) lds[k] = w;
+    for (int o = 32; o > 0; o >>= 1) {
+        const double v = __shfl_xor(w, o, 64);
+        w = top ? fmax(w, v) : lc_join(k, w, v);
     }
+    if (lane == 0) lds[k] = w;
     __syncthreads();
     if (threadIdx.x) return;
     out->lam_min = lds[0];
@@ -331,13 +322,22 @@ __global__ void k_link_stats(LinkStats *out, double *max, const double *pmax, in
     out->imr = lds[5];
     out->umax = lds[6];
     out->long_max = lds[7];
+    out->fat_max = lds[8];
     const double lam = 0.5 * (lds[0] + lds[1]);
     out->coeff = lds[2] > 0 ? lam : -lam;
+    int verdict = LINKS_OK;
+    if (!__builtin_isfinite(lds[7]) || !__builtin_isfinite(lds[8]))
+        verdict = LINKS_NON_FINITE;
+    else if (pcheck && (!(lam > 0.0) || (lds[1] - lds[0]) > tol * lam || lds[4] > tol || lds[5] > tol ||
+                        (lds[2] > 0 && lds[3] > 0)))
+        verdict = LINKS_OTHER_FORM;
+    out->verdict = verdict;
 }
 
 // two rows of U = L / (lambda * sigma * phase) into the 12-real sub-fields;
 // fixed-point formats scale by umax (the global max |component| of U)
 template <int GF> __global__ void k_gauge_pack12(char *dst, const double *src, Geom g, const LinkStats *ls) {
+    if (ls->verdict != LINKS_OK) return;
     const double coef = ls->coeff, umax = ls->umax;
     const size_t V = 2 * (size_t)g.vh;
     const size_t vh = g.vh;
@@ -419,6 +419,7 @@ __device__ __noinline__ double phase_param(double x, double y) {
 // W10, then phase_param of W00 and of W20.  F64: four 16-byte planes; FIX32:
 // two planes, the entries scaled by lmax, the phase parameters by 1.
 template <int GF> __global__ void k_gauge_pack8(char *dst, const double *src, Geom g, const LinkStats *ls) {
+    if (ls->verdict != LINKS_OK) return;
     const double sign = ls->npos > 0 ? 1.0 : -1.0, lmax = ls->long_max;
     const size_t V = 2 * (size_t)g.vh;
     const size_t vh = g.vh;
@@ -1343,13 +1344,11 @@ hipError_t launch_absmax(const double *src, size_t n, double *partial, int *nblo
     return hipGetLastError();
 }
 
-hipError_t launch_link_stats(LinkStats *out, double *max, const double *pmax, int nmax, const double *pcheck, int ncheck,
-                             hipStream_t st) {
-    hipLaunchKernelGGL(k_link_stats, dim3(1), dim3(64 * (LC + 1)), 0, st, out, max, pmax, nmax, pcheck, ncheck);
+hipError_t launch_link_stats(LinkStats *out, const double *pfat, int nfat, const double *plong, const double *pcheck,
+                             int nlong, double tol, hipStream_t st) {
+    hipLaunchKernelGGL(k_link_stats, dim3(1), dim3(64 * (LC + 1)), 0, st, out, pfat, nfat, plong, pcheck, nlong, tol);
     return hipGetLastError();
 }
-
-bool gauge_pack_needs_max(int gf) { return gf == GF_FIX16 || gf == GF_FIX32; }
 
 #define HISQ_DISPATCH_GF(gf, CALL)                                                    \
     do {                                                                              \
@@ -1363,11 +1362,10 @@ bool gauge_pack_needs_max(int gf) { return gf == GF_FIX16 || gf == GF_FIX32; }
         }                                                                             \
     } while (0)
 
-hipError_t launch_gauge_pack(char *dst, const double *src, const Geom &g, int gf, const double *absmax, double *partial,
-                             int *nblocks, hipStream_t st) {
+hipError_t launch_gauge_pack(char *dst, const double *src, const Geom &g, int gf, const LinkStats *ls, bool lng,
+                             hipStream_t st) {
     const int nb = blas_blocks(8 * (size_t)g.vh);
-    *nblocks = nb;
-    HISQ_DISPATCH_GF(gf, hipLaunchKernelGGL((k_gauge_pack<GFc>), dim3(nb), dim3(BLAS_BLOCK), 0, st, dst, src, g, absmax, partial));
+    HISQ_DISPATCH_GF(gf, hipLaunchKernelGGL((k_gauge_pack<GFc>), dim3(nb), dim3(BLAS_BLOCK), 0, st, dst, src, g, ls, lng ? 1 : 0));
     return hipGetLastError();
 }
 

@@ -94,6 +94,7 @@ namespace {
 std::mutex g_scratch_mu;
 LibScratch g_scratch[64];
 constexpr size_t SCRATCH_DOUBLES = (size_t)BLAS_MAX_BLOCKS * (2 + LINK_CHECK_VALUES) + 64;
+static_assert(sizeof(LinkStats) <= 64 * sizeof(double), "LinkStats outgrows the scratch");
 }  // namespace
 
 hisq_status lib_scratch(LibScratch **out) {
@@ -205,66 +206,48 @@ extern "C" hisq_status hisq_gauge_pack_recon(hisq_gauge *g, void *fat_dst, void 
     const Geom geo = make_geom(dims);
     const size_t nreal = (size_t)4 * 2 * geo.vh * 18;
     // scratch: block maxima of the fat and the long field, the long check's
-    // tuples, then [fat max, long max, LinkStats], copied to the host at the end
+    // tuples, then LinkStats, copied to the host at the end
     double *pfat = ls->dev, *plng = pfat + BLAS_MAX_BLOCKS, *pchk = plng + BLAS_MAX_BLOCKS;
-    double *mx = pchk + (size_t)BLAS_MAX_BLOCKS * LINK_CHECK_VALUES;
-    LinkStats *lsd = (LinkStats *)(mx + 2);
-    const bool scaled = gauge_pack_needs_max(gauge_fmt), full = long_recon == HISQ_RECON_18;
-    int nf = 0, nl = 0, nc = 0;
-    // Each field is read once where its packed values do not depend on the whole
-    // field (IEEE and shared-exponent formats, 18 reals), else twice: 604 MB a
-    // read at 32^4, 108 us.
-    if (scaled) {
-        HISQ_TRY_HIP(launch_absmax(fat_src, nreal, pfat, &nf, st));
-        HISQ_TRY_HIP(launch_link_stats(nullptr, mx, pfat, nf, nullptr, 0, st));
-    }
-    HISQ_TRY_HIP(launch_gauge_pack((char *)fat_dst, fat_src, geo, gauge_fmt, mx, pfat, &nf, st));
-    if (full) {
-        if (scaled) {
-            HISQ_TRY_HIP(launch_absmax(long_src, nreal, plng, &nl, st));
-            HISQ_TRY_HIP(launch_link_stats(nullptr, mx + 1, plng, nl, nullptr, 0, st));
-        }
-        HISQ_TRY_HIP(launch_gauge_pack((char *)long_dst, long_src, geo, gauge_fmt, mx + 1, plng, &nl, st));
-        if (!scaled) HISQ_TRY_HIP(launch_link_stats(nullptr, mx + 1, plng, nl, nullptr, 0, st));
-    } else {
-        // verify L = lambda * sigma * phase * SU(3) and find lambda, sigma and max |U|
-        HISQ_TRY_HIP(launch_long_check(long_src, geo, pchk, &nc, st));
-        HISQ_TRY_HIP(launch_link_stats(lsd, nullptr, nullptr, 0, pchk, nc, st));
-        if (long_recon == HISQ_RECON_8)
-            HISQ_TRY_HIP(launch_gauge_pack8((char *)long_dst, long_src, geo, gauge_fmt, lsd, st));
-        else
-            HISQ_TRY_HIP(launch_gauge_pack12((char *)long_dst, long_src, geo, gauge_fmt, lsd, st));
-    }
-    if (!scaled) HISQ_TRY_HIP(launch_link_stats(nullptr, mx, pfat, nf, nullptr, 0, st));
-    HISQ_TRY_HIP(hipMemcpyAsync(ls->host, mx, 2 * sizeof(double) + sizeof(LinkStats), hipMemcpyDeviceToHost, st));
+    LinkStats *lsd = (LinkStats *)(pchk + (size_t)BLAS_MAX_BLOCKS * LINK_CHECK_VALUES);
+    const bool full = long_recon == HISQ_RECON_18;
+    const double tol = gauge_fmt == HISQ_GAUGE_F64 ? 1e-13
+                       : (gauge_fmt == HISQ_GAUGE_F32 || gauge_fmt == HISQ_GAUGE_SX24) ? 1e-7
+                       : gauge_fmt == HISQ_GAUGE_FIX16 ? 1e-5 : 1e-9;
+    // Both fields are read before either is packed, since a refused call leaves the
+    // destinations as they were: the packing kernels look at the verdict and return, so the
+    // host waits once, at the end.  Compressed long links: one pass verifies
+    // L = lambda * sigma * phase * SU(3) and finds lambda, sigma, max |U| and max |L|.
+    int nf = 0, nl = 0;
+    HISQ_TRY_HIP(launch_absmax(fat_src, nreal, pfat, &nf, st));
+    if (full)
+        HISQ_TRY_HIP(launch_absmax(long_src, nreal, plng, &nl, st));
+    else
+        HISQ_TRY_HIP(launch_long_check(long_src, geo, pchk, &nl, st));
+    HISQ_TRY_HIP(launch_link_stats(lsd, pfat, nf, full ? plng : nullptr, full ? nullptr : pchk, nl, tol, st));
+    HISQ_TRY_HIP(launch_gauge_pack((char *)fat_dst, fat_src, geo, gauge_fmt, lsd, false, st));
+    if (full)
+        HISQ_TRY_HIP(launch_gauge_pack((char *)long_dst, long_src, geo, gauge_fmt, lsd, true, st));
+    else if (long_recon == HISQ_RECON_8)
+        HISQ_TRY_HIP(launch_gauge_pack8((char *)long_dst, long_src, geo, gauge_fmt, lsd, st));
+    else
+        HISQ_TRY_HIP(launch_gauge_pack12((char *)long_dst, long_src, geo, gauge_fmt, lsd, st));
+    HISQ_TRY_HIP(hipMemcpyAsync(ls->host, lsd, sizeof(LinkStats), hipMemcpyDeviceToHost, st));
     HISQ_TRY_HIP(hipStreamSynchronize(st));
-    const LinkStats *c = (const LinkStats *)(ls->host + 2);
-    const double fmax_ = ls->host[0], lmax_ = full ? ls->host[1] : c->long_max;
-    if (!std::isfinite(fmax_) || !std::isfinite(lmax_))
-        return set_error(HISQ_ERANGE, "hisq_gauge_pack: non-finite link element");
-    double long_scale = lmax_, coeff = 1.0;
-    if (!full) {
-        const double tol = gauge_fmt == HISQ_GAUGE_F64 ? 1e-13
-                           : (gauge_fmt == HISQ_GAUGE_F32 || gauge_fmt == HISQ_GAUGE_SX24) ? 1e-7
-                           : gauge_fmt == HISQ_GAUGE_FIX16 ? 1e-5 : 1e-9;
-        const double lam = 0.5 * (c->lam_min + c->lam_max);
-        if (!(lam > 0.0) || (c->lam_max - c->lam_min) > tol * lam || c->defect > tol || c->imr > tol ||
-            (c->npos > 0 && c->nneg > 0))
-            return set_error(HISQ_EINVAL,
-                             "hisq_gauge_pack_recon: long links are not lambda*phase*SU(3) within %g "
-                             "(lambda in [%g,%g], unitarity defect %g, |Im det|/|det| %g, sign counts %g/%g)",
-                             tol, c->lam_min, c->lam_max, c->defect, c->imr, c->npos, c->nneg);
-        coeff = c->coeff;
-        if (long_recon == HISQ_RECON_12) long_scale = c->umax;
-    }
+    const LinkStats *c = (const LinkStats *)ls->host;
+    if (c->verdict == LINKS_NON_FINITE) return set_error(HISQ_ERANGE, "hisq_gauge_pack: non-finite link element");
+    if (c->verdict == LINKS_OTHER_FORM)
+        return set_error(HISQ_EINVAL,
+                         "hisq_gauge_pack_recon: long links are not lambda*phase*SU(3) within %g "
+                         "(lambda in [%g,%g], unitarity defect %g, |Im det|/|det| %g, sign counts %g/%g)",
+                         tol, c->lam_min, c->lam_max, c->defect, c->imr, c->npos, c->nneg);
     for (int k = 0; k < 4; k++) g->dims[k] = dims[k];
     g->fmt = gauge_fmt;
     g->fat = fat_dst;
     g->lng = long_dst;
-    g->fat_max = fmax_;
-    g->long_max = long_scale;
+    g->fat_max = c->fat_max;
+    g->long_max = long_recon == HISQ_RECON_12 ? c->umax : c->long_max;
     g->long_recon = long_recon;
-    g->long_coeff = coeff;
+    g->long_coeff = full ? 1.0 : c->coeff;
     return HISQ_OK;
 }
 

@@ -193,25 +193,28 @@ hipError_t launch_spinor_pack(char *dst, const double *src, size_t n, int sf, hi
 hipError_t launch_spinor_unpack(double *dst, const char *src, size_t n, int sf, hipStream_t st);
 hipError_t launch_spinor_convert(char *dst, int sf_dst, const char *src, int sf_src, size_t n, hipStream_t st);
 hipError_t launch_absmax(const double *src, size_t n, double *partial, int *nblocks, hipStream_t st);
-// What the packing of the long links needs and checks, formed on the device so
-// that a pack call waits once, at its end: the long field's max |real
-// component| (infinite when one is not finite), lambda = |det L|^(1/3) over the
-// links, how many have which sign, the defects, max |component of U|, and the
-// coefficient (the mean of the extreme lambdas with the sign).
+// What the packing of links needs and checks, formed on the device so that a pack
+// call waits once, at its end: the fields' max |real component| (infinite when one
+// is not finite), lambda = |det L|^(1/3) over the long links, how many have which
+// sign, the defects, max |component of U|, the coefficient (the mean of the extreme
+// lambdas with the sign), and the verdict, on which the packing kernels do nothing
+// but for LINKS_OK.
+enum { LINKS_OK = 0, LINKS_NON_FINITE = 1, LINKS_OTHER_FORM = 2 };
 struct LinkStats {
-    double lam_min, lam_max, npos, nneg, defect, imr, umax, long_max, coeff;
+    double lam_min, lam_max, npos, nneg, defect, imr, umax, long_max, coeff, fat_max;
+    int verdict;
 };
 constexpr int LINK_CHECK_VALUES = 8;   // doubles per block of launch_long_check
-// fixed-point formats: *absmax first.  The others write the block maxima of the field to partial.
-hipError_t launch_gauge_pack(char *dst, const double *src, const Geom &g, int gf, const double *absmax, double *partial,
-                             int *nblocks, hipStream_t st);
-bool gauge_pack_needs_max(int gf);
+// the field of ls->long_max (lng) or ls->fat_max, 18 reals a link
+hipError_t launch_gauge_pack(char *dst, const double *src, const Geom &g, int gf, const LinkStats *ls, bool lng,
+                             hipStream_t st);
 hipError_t launch_norm2_f64(const char *v, size_t n, double *partial, int *nblocks, hipStream_t st);
 // two-row and eight-parameter long links: the checks of LinkStats per block
 hipError_t launch_long_check(const double *src, const Geom &g, double *partial, int *nblocks, hipStream_t st);
-// *max from nmax block maxima (max may be NULL), *out from ncheck blocks of launch_long_check (pcheck may be NULL)
-hipError_t launch_link_stats(LinkStats *out, double *max, const double *pmax, int nmax, const double *pcheck, int ncheck,
-                             hipStream_t st);
+// *out from the fat field's nfat block maxima, and for the long field from nlong block maxima
+// (plong; 18 reals) or nlong blocks of launch_long_check (pcheck; the form is required within tol)
+hipError_t launch_link_stats(LinkStats *out, const double *pfat, int nfat, const double *plong, const double *pcheck,
+                             int nlong, double tol, hipStream_t st);
 hipError_t launch_gauge_pack12(char *dst, const double *src, const Geom &g, int gf, const LinkStats *ls, hipStream_t st);
 // eight parameters of W = L * phase * sign (sign = +-1, the sign of the long-link
 // coefficient); fixed point scaled by the long field's max |real component|
