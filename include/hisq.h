@@ -512,7 +512,8 @@ void hisq_tune_clear(void);
  * Besides the shapes of hisq_tune_set a line may hold blocks of 64 threads and,
  * for nr == rg == 1, the stages -12, -22, -32 and -42 (as -2, the links of
  * 1..4 directions kept in the memory-side cache), which the autotuner chooses
- * itself.  A solver's iterated operator on one right-hand side takes block,
+ * itself; such a line has /2 after its architecture, so that versions of the
+ * library without these shapes skip it.  A solver's iterated operator on one right-hand side takes block,
  * grid and sweep of a tuned or loaded shape, and one of these stages where the
  * links fit (the same results bit for bit); a shape of hisq_tune_set is used
  * as it is. */

@@ -85,8 +85,12 @@ bool shape_ok(const hisq_fmt &f, int c, const DslashTile &t, bool tuner = false)
 //       nr rg stage block grid sweep <microseconds>
 // Lines of another format version, device architecture or HIP runtime
 // version are skipped on reading (their timings say nothing about this one).
+// A line whose shape hisq_tune_set does not take has kShapeSet appended to its
+// architecture: versions of the library that know only the shapes of hisq_tune_set
+// skip it as that of another device, where they would refuse the whole file.
 // ---------------------------------------------------------------------------
 constexpr int kTuneFileVersion = 1;
+const char kShapeSet[] = "/2";
 
 // "gfx950 <runtime version>" of the current device, or "" without one
 std::string device_tag() {
@@ -103,10 +107,14 @@ std::string device_tag() {
     return arch + " " + std::to_string(rv);
 }
 
+hisq_fmt tune_fmt(int id) { return hisq_fmt{id / 10000, (id / 1000) % 10, (id / 100) % 10 ? 64 : 32}; }
+
 std::string tune_line(const std::string &tag, const TuneKey &k, const DslashTile &t, float ms) {
+    std::string dev = tag;
+    if (!shape_ok(tune_fmt(std::get<0>(k)), std::get<5>(k), t)) dev.insert(dev.find(' '), kShapeSet);
     char line[320];
     snprintf(line, sizeof(line), "hisq-tune %d %s %d %d %d %d %d %d %d : %d %d %d %d %d %d %.3f\n", kTuneFileVersion,
-             tag.c_str(), std::get<0>(k), std::get<1>(k), std::get<2>(k), std::get<3>(k), std::get<4>(k),
+             dev.c_str(), std::get<0>(k), std::get<1>(k), std::get<2>(k), std::get<3>(k), std::get<4>(k),
              std::get<5>(k), std::get<6>(k), t.nr, t.rg, t.stage, t.block, t.grid, t.sweep, ms * 1e3);
     return std::string(line);
 }
@@ -134,8 +142,11 @@ hisq_status read_tune_file(const char *path, const std::string &tag, bool apply,
             st = set_error(HISQ_EIO, "tune cache %s: malformed line %d", path, lineno);
             break;
         }
-        if (ver != kTuneFileVersion || tag != std::string(arch) + " " + std::to_string(rv)) continue;
-        const hisq_fmt f{tid / 10000, (tid / 1000) % 10, (tid / 100) % 10 ? 64 : 32};
+        std::string dev = arch;
+        const size_t set = dev.size() - std::min(dev.size(), sizeof(kShapeSet) - 1);
+        if (dev.compare(set, std::string::npos, kShapeSet) == 0) dev.resize(set);
+        if (ver != kTuneFileVersion || tag != dev + " " + std::to_string(rv)) continue;
+        const hisq_fmt f = tune_fmt(tid);
         const int recon = tid % 100;
         const int dims[4] = {X, Y, Z, T};
         const DslashTile t{nr, rg, stage, block, grid, sweep};
