@@ -513,10 +513,12 @@ void hisq_tune_clear(void);
  * for nr == rg == 1, the stages -12, -22, -32 and -42 (as -2, the links of
  * 1..4 directions kept in the memory-side cache), which the autotuner chooses
  * itself; such a line has /2 after its architecture, so that versions of the
- * library without these shapes skip it.  A solver's iterated operator on one right-hand side takes block,
- * grid and sweep of a tuned or loaded shape, and one of these stages where the
- * links fit (the same results bit for bit); a shape of hisq_tune_set is used
- * as it is. */
+ * library without these shapes skip it.
+ * A solver's iterated operator on one right-hand side takes block, grid and sweep
+ * of a shape that the autotuner chose, in this process or the one that saved it,
+ * and one of these stages where the links fit (the same results bit for bit;
+ * hisq_tune_report names it).  A shape of hisq_tune_set, or of a line without a
+ * time, as a saved shape of hisq_tune_set is, is used as it is. */
 hisq_status hisq_tune_save(const char *path);
 hisq_status hisq_tune_load(const char *path, int *nloaded);
 

@@ -58,7 +58,7 @@ inline int tune_id(const hisq_fmt &f, int long_recon) {
 }
 std::mutex g_tune_mu;
 std::map<TuneKey, std::pair<DslashTile, float>> g_tuned;
-std::set<TuneKey> g_fixed;   // the keys of g_tuned whose shape hisq_tune_set fixed
+std::set<TuneKey> g_fixed;   // the keys of g_tuned whose shape a program fixed: by hisq_tune_set, or by a line without a time
 
 bool tuning_enabled() {
     const char *e = getenv("HISQ_TUNE");
@@ -126,7 +126,7 @@ std::string tune_line(const std::string &tag, const TuneKey &k, const DslashTile
 hisq_status read_tune_file(const char *path, const std::string &tag, bool apply, bool replace, int *nloaded) {
     FILE *fp = fopen(path, "r");
     if (!fp) return set_error(HISQ_EIO, "tune cache %s: cannot open", path);
-    std::vector<std::pair<TuneKey, DslashTile>> got;
+    std::vector<std::pair<TuneKey, std::pair<DslashTile, float>>> got;
     char line[512];
     int lineno = 0;
     hisq_status st = HISQ_OK;
@@ -157,17 +157,19 @@ hisq_status read_tune_file(const char *path, const std::string &tag, bool apply,
             st = set_error(HISQ_EIO, "tune cache %s: line %d names an unsupported key or shape", path, lineno);
             break;
         }
-        got.emplace_back(TuneKey{tid, X, Y, Z, T, c, red}, t);
+        got.emplace_back(TuneKey{tid, X, Y, Z, T, c, red}, std::make_pair(t, us > 0.f ? us * 1e-3f : -1.f));
     }
     fclose(fp);
     if (st != HISQ_OK) return st;
     if (apply)
         for (const auto &e : got) {
-            if (replace) {
-                g_tuned[e.first] = std::make_pair(e.second, -1.f);
+            if (!replace && g_tuned.count(e.first)) continue;
+            g_tuned[e.first] = e.second;
+            // the autotuner times what it chooses; a shape of hisq_tune_set is saved without a time
+            if (e.second.second > 0.f)
                 g_fixed.erase(e.first);
-            } else
-                g_tuned.emplace(e.first, std::make_pair(e.second, -1.f));
+            else
+                g_fixed.insert(e.first);
         }
     if (nloaded) *nloaded = (int)got.size();
     return HISQ_OK;
@@ -442,16 +444,21 @@ DslashPlan dslash_plan_lookup(const hisq_fmt &f, const Geom &g, int nrhs, int lo
 // of INT20 links (32^4, two-row) 39.4, 36.4, 34.8, 35.2, 35.6 ms; of 503 MB in F32 (32^4,
 // two-row) 61.7, 55.8, 59.3 ms; of 318 MB in F64 (24^4, two-row) 33.3, 30.2, 28.2, 28.8 ms;
 // of 1006 MB in F64 (32^4, no direction by this rule) 114.4, 116.6 ms.  Where the tuner
-// had the choice (links_stay) it stands, as does a shape that hisq_tune_set fixed.
-void dslash_keep_links(const hisq_fmt &f, const Geom &g, int long_recon, DslashPlan &plan) {
-    if (links_stay(f, long_recon, g) || plan.n != 1 || plan.tile[0].nr * plan.tile[0].rg != 1) return;
+// had the choice (links_stay) it stands, as does a shape that a program fixed (g_fixed).
+namespace {
+// the stage of a solver's launches where the table has t for key (g_tune_mu held)
+int solver_stage(const TuneKey &key, const hisq_fmt &f, const Geom &g, int long_recon, const DslashTile &t) {
+    if (t.nr * t.rg != 1 || t.stage < -2 || links_stay(f, long_recon, g) || g_fixed.count(key)) return t.stage;
     const int k = (int)std::min(4.0, 0.8 * LLC_BYTES / (0.25 * all_link_bytes(f, long_recon, g)));
-    if (k < 1 || plan.tile[0].stage < -2) return;
-    {
-        std::lock_guard<std::mutex> lk(g_tune_mu);
-        if (g_fixed.count(TuneKey{tune_id(f, long_recon), g.X, g.Y, g.Z, g.T, 1, 0})) return;
-    }
-    plan.tile[0].stage = -(10 * k + 2);
+    return k < 1 ? t.stage : -(10 * k + 2);
+}
+}  // namespace
+
+void dslash_keep_links(const hisq_fmt &f, const Geom &g, int long_recon, DslashPlan &plan) {
+    if (plan.n != 1) return;
+    std::lock_guard<std::mutex> lk(g_tune_mu);
+    plan.tile[0].stage = solver_stage(TuneKey{tune_id(f, long_recon), g.X, g.Y, g.Z, g.T, 1, 0}, f, g, long_recon,
+                                      plan.tile[0]);
     plan.tile_red[0] = plan.tile[0];
 }
 
@@ -569,13 +576,20 @@ extern "C" size_t hisq_tune_report(char *buf, size_t len) {
             char line[256];
             const auto &k = kv.first;
             const auto &t = kv.second.first;
-            snprintf(line, sizeof(line),
-                     "triplet %03d recon %d lattice %dx%dx%dx%d rhs-block %d%s: nr %d rg %d stage %d block %d grid %d "
-                     "sweep %d (%.1f us)\n",
-                     std::get<0>(k) / 100, std::get<0>(k) % 100, std::get<1>(k), std::get<2>(k), std::get<3>(k),
-                     std::get<4>(k), std::get<5>(k), std::get<6>(k) ? " reduction" : "",
-                     t.nr, t.rg, t.stage, t.block, t.grid, t.sweep, kv.second.second * 1e3);
+            const int dims[4] = {std::get<1>(k), std::get<2>(k), std::get<3>(k), std::get<4>(k)}, id = std::get<0>(k);
+            const int in_solver = std::get<6>(k) ? t.stage
+                                                 : hisq::solver_stage(k, hisq::tune_fmt(id), hisq::make_geom(dims),
+                                                                      id % 100, t);
+            const int n = snprintf(line, sizeof(line),
+                                   "triplet %03d recon %d lattice %dx%dx%dx%d rhs-block %d%s: nr %d rg %d stage %d block "
+                                   "%d grid %d sweep %d (%.1f us)",
+                                   id / 100, id % 100, dims[0], dims[1], dims[2], dims[3], std::get<5>(k),
+                                   std::get<6>(k) ? " reduction" : "", t.nr, t.rg, t.stage, t.block, t.grid, t.sweep,
+                                   kv.second.second * 1e3);
+            if (in_solver != t.stage)
+                snprintf(line + n, sizeof(line) - n, ", stage %d in a solver's iterations", in_solver);
             s += line;
+            s += '\n';
         }
     }
     if (buf && len) {

@@ -36,3 +36,31 @@ def test_lines_of_new_shapes_are_another_device_to_older_readers(tmp_path, shape
             assert hisq.hisq_tune_load(tmp_path / "o.txt") == n
     finally:
         hisq.hisq_tune_clear()
+
+
+# links of 111, 80 and 255 MB: all directions of the first two fit the solver's share of the memory-side cache and
+# three of the last, none of 1.0 GB; 17 MB are the tuner's choice
+RULE = [((20, 20, 20, 24), "single", 18, -42), ((20, 20, 20, 24), "int30", 8, -42), ((24, 24, 24, 32), "single", 18, -32),
+        ((32, 32, 32, 32), "double", 12, None), ((12, 10, 14, 18), "single", 18, None)]
+
+
+@pytest.mark.parametrize("dims,name,recon,stage", RULE)
+def test_stage_of_a_solver(tmp_path, dims, name, recon, stage):
+    hisq = need_gpu()
+    told = ", stage %s in a solver's iterations" % stage
+    try:
+        load_shape(hisq, tmp_path, name, recon, dims, 1, [0], (1, 1, -2, 128, 0, 0))     # timed: the tuner's
+        rep = hisq.hisq_tune_report()
+        assert (told in rep) if stage else ("solver" not in rep), rep
+        line, = saved(hisq, tmp_path)
+        assert float(line.split()[-1]) > 0 and hisq.hisq_tune_load(tmp_path / "s.txt") == 1
+        assert hisq.hisq_tune_report() == rep
+        # fixed by the program, here or in the process that saved it: as it is
+        hisq.hisq_tune_set(name, dims, 1, 1, 1, -2, 128, 0, long_recon=recon)
+        assert "stage -2 " in hisq.hisq_tune_report() and "solver" not in hisq.hisq_tune_report()
+        line, = saved(hisq, tmp_path)
+        hisq.hisq_tune_clear()
+        assert float(line.split()[-1]) < 0 and hisq.hisq_tune_load(tmp_path / "s.txt") == 1
+        assert "stage -2 " in hisq.hisq_tune_report() and "solver" not in hisq.hisq_tune_report()
+    finally:
+        hisq.hisq_tune_clear()
