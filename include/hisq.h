@@ -377,8 +377,9 @@ size_t hisq_bicgstab_workspace_bytes(const int dims[4], int l, hisq_fmt sloppy);
  * ordered after `stream` and returns when x is written: every scalar of the
  * method is formed on the device, each cycle (l BiCG steps and the
  * minimal-residual step) is enqueued as a whole (replayed as a captured
- * hipGraph when p->use_graph) and followed by one synchronisation, where the
- * reliable-update decision is taken. */
+ * hipGraph when p->use_graph) and ends in a record that the host reads, with the
+ * next cycle enqueued already; the device decides on a reliable update, the host
+ * then runs it. */
 hisq_status hisq_bicgstab_solve(double *x, const double *b, const hisq_gauge *g64, const hisq_gauge *gs,
                                 double mass, double tol, int l, hisq_fmt sloppy,
                                 const hisq_solver_params *p, void *ws, size_t ws_bytes,
@@ -402,7 +403,8 @@ hisq_status hisq_cg_solve_batched(double *x, const double *b, int nrhs, const hi
 
 /* Launch shapes chosen by the Dslash autotuner so far (one text line per
  * triplet, long-link storage, lattice and right-hand-side block: right-hand sides per lane, lanes
- * per site, hops per load stage, block size, measured time).  Writes at most
+ * per site, hops per load stage, block size, measured time, the stage of a solver's iterations
+ * where it is another one).  Writes at most
  * len bytes (NUL-terminated) into buf if buf is not NULL; returns the size the
  * full report needs.  The autotuner times each candidate shape with HIP events
  * on the first application of a shape key (never inside stream capture);

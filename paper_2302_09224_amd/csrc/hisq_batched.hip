@@ -209,12 +209,14 @@ struct BRun {
     long iters = 0, rus = 0, dsl = 0, d64 = 0;
     double alg = 0.0;
     hipGraphExec_t exec = nullptr;
-    // A Dslash launch over a set of field columns: the plan for the block padded
-    // to a power of two and the column map that deals the columns round-robin
-    // over the lane groups (column i of the set -> group i % rg, slot i / rg),
-    // so that the lanes of a site share the work of the longest-running systems.
-    // Launches with a fused reduction have their own tile, hence their own map;
-    // they write the partials that nl describes.
+    // A Dslash launch over a set of field columns: the plan for the block padded to a
+    // power of two, and the column map, column i of the set at launch index
+    // (i % rg) * nr + i / rg, of which the kernel computes index k in lane group k % rg,
+    // slot k / rg.  With nr == rg the columns so fill one lane group after another (12 of
+    // them in 4 x 4: three groups of four, the fourth idle, all four slots at work), where
+    // the dense map, which the tuner times, would leave the last slot dead in every lane.
+    // Launches with a fused reduction have their own tile, hence their own map; they write
+    // the partials that nl describes.
     struct Mapped {
         DslashPlan plan{};
         unsigned mask = 0;            // field columns in the launch

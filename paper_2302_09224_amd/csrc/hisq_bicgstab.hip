@@ -18,7 +18,7 @@
 //   l passes of the modified Gram-Schmidt (row i: r_j -= tau_{i-1,j} r_{i-1} for j >= i, and
 //   the dot products with r_i in the same pass), the closing updates, the cycle's record.
 // (As a launch per operation a cycle of l = 4 took 108 launches; 16^4 with 20-bit
-// spinors, m = 0.05 to 1e-12: 39 -> 15.3 ms.)
+// spinors, m = 0.05 to 1e-12: 39 -> 14.0 ms.)
 // A cycle whose |r_0|^2 asks for a reliable update, or that breaks down, lowers
 // the guard of the cycles behind it; the host reads each cycle's record from
 // pinned memory, with the next cycle already enqueued.
@@ -32,7 +32,6 @@
 #include <cmath>
 #include <cstring>
 #include <mutex>
-#include <vector>
 
 #include "hisq_dslash_kernels.h"
 
@@ -44,7 +43,6 @@ using dsl::spin_load;
 
 namespace {
 
-constexpr int BL_MAXK = 8;    // vectors combined or dotted in one pass
 constexpr int BL_BLOCK = 256;
 
 constexpr int BL_MAXL = HISQ_MAX_BICGSTAB_L;
@@ -61,7 +59,6 @@ struct BlCtl {
     int stop;     // guard of a cycle's launches, which run up to this one: STOP_NEVER while the method goes on, the
                   // launch that broke down, -1 once its cycle is recorded, -2 when a reliable update is due
     int broke;    // 1: a BiCG or minimal-residual denominator vanished, 2: non-finite residual
-    int due;      // the last cycle asked for a reliable update
     int cycles;   // completed
     unsigned long long seq;   // records published
     double rho_c[2], alpha_c[2];                            // entering the cycle

@@ -106,7 +106,6 @@ hisq_status lib_scratch(LibScratch **out) {
     if (!s.dev) {
         HISQ_TRY_HIP(hipMalloc((void **)&s.dev, SCRATCH_DOUBLES * sizeof(double)));
         HISQ_TRY_HIP(hipHostMalloc((void **)&s.host, 64 * sizeof(double), hipHostMallocDefault));
-        s.ndev = SCRATCH_DOUBLES;
     }
     *out = &s;
     return HISQ_OK;

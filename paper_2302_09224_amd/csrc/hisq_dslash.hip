@@ -271,9 +271,14 @@ double all_link_bytes(const hisq_fmt &f, int recon, const Geom &g) {
 
 // Links so small that several such fields stay in the memory-side cache: then any
 // application may find them there, and the tuner also times the loads that keep them
-// (normal operator in F32 on 12x10x14x18, 35 MB: 12.3 -> 11.0 us).  A single application
-// on larger links streams them, since they may have been read long ago: three fields of
-// 767 MB in F64 in turn took 145.8 us each, 152.4 with one direction kept.
+// (normal operator in F32 on 12x10x14x18, 17 MB: 12.3 -> 11.0 us).  It times them warm, as
+// a Krylov method of the program's own finds them; fields that take turns gain less while
+// the cache holds them all and lose beyond that.  The fastest streamed and the fastest kept
+// shape, us an application on one field, on 128 MB and on 1.5 GB of fields in turn: F32
+// 12x10x14x18 5.5/4.3, 6.2/5.7, 6.5/7.0; F64 two-row 12^3x14, 23 MB, 6.6/5.7, 7.3/6.7,
+// 7.7/8.2; INT20 two-row 16^2x24^2, 35 MB, 10.0/9.7, 10.5/10.3, 11.3/11.7.  A single
+// application on larger links streams them, since they may have been read long ago: three
+// fields of 767 MB in F64 in turn took 145.8 us each, 152.4 with one direction kept.
 constexpr double LLC_BYTES = 256 * 1048576.0;
 bool links_stay(const hisq_fmt &f, int recon, const Geom &g) { return all_link_bytes(f, recon, g) <= LLC_BYTES / 4; }
 

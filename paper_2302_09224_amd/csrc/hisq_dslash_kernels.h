@@ -755,8 +755,8 @@ __device__ __forceinline__ void dslash_site(const DslashArgs &A, int s, int c0, 
     // input column of each of the lane's right-hand sides, computed once per
     // site; a column the lane does not compute reads its first live column
     // (valid memory, a cache hit, never used), so the loads carry no branches
-    // and no zero fill; the arithmetic of a column is skipped when no lane of
-    // the wave computes it
+    // and no zero fill, but take their passes of the address unit; the arithmetic
+    // of a column is skipped when no lane of the wave computes it
     const char *colp[NR];
     {
         const char *first = in_col(NR == 1 ? 0 : __builtin_ctz(live));
@@ -1047,10 +1047,11 @@ __global__ void __launch_bounds__(256) k_dslash(DslashArgs A, int rhs0, int rg, 
     for (int j = 0; j < NR; j++) red[j] = 0.0;
     // The lane's right-hand sides (rg divides blockDim, so a lane keeps its
     // group in every tile): rhs0 + j*rg + grp, one column of each group of rg
-    // per lane, so that the live columns of a block (a prefix: the solvers
-    // compact them) leave whole groups dead in every lane, whose arithmetic
-    // the wave then skips.  Those at or beyond ncol (a block padded to a power
-    // of two) and those marked inactive are neither read nor written.
+    // per lane, so that where the live columns of a block are a prefix (a launch
+    // over consecutive fields) the others are dead in every lane, and the wave
+    // skips their arithmetic, though not their loads (dslash_site).  Those at or
+    // beyond ncol (a block padded to a power of two) and those marked inactive
+    // are neither read nor written.
     const int ncol = A.nrhs > 1 ? A.nrhs : 1;
     // Lanes and sites: the wave's 64 / rg sites are consecutive lanes, group after
     // group, so that each quad of lanes reads one 64-byte piece of one column.

@@ -237,7 +237,6 @@ struct SolverCtrl {
     double rho;      // |r|^2 of the iterated residual (stored values)
     double rho_prev; // |r|^2 before the last iteration's update (beta at a reliable update)
     double rho_new, gamma, pi, alpha, beta;
-    double pa_re, pa_im, pb;   // p_new = pa*r + pb*p
     double rmax2;    // max |r|^2 since the last reliable update
     double b2, tol2, delta2;
     double r2_true;  // |b - A x|^2 at the last true-residual computation
@@ -264,16 +263,16 @@ struct SolverCtrl {
     // The recurrence state as the iteration's residual update found it.  Every
     // block of the gradient update derives the iteration's scalars from these
     // copies while its first block writes the new values above, so no block
-    // reads what another one writes in the same launch.
+    // reads what another one writes in the same launch (but for stop, see Guard).
     int o_k, o_active_mask;
     double o_rho, o_rmax2, o_dev, o_rnorm_prev, o_anorm, o_alpha_prev, o_beta_prev;
     double o_zeta[HISQ_MAX_SHIFTS], o_zeta_prev[HISQ_MAX_SHIFTS];
-    unsigned long long seq;   // status records published so far (StatusBoard)
+    unsigned long long seq;   // status records published so far (Status)
     double red[8];   // sums of block partials too many for every consumer block to add up (SUMS_* offsets)
     int shift_stop_k[HISQ_MAX_SHIFTS];
     // batched CG: per right-hand side scalars
-    double brho[16], brho_prev[16], brho_new[16], bgamma[16], bpi[16], balpha[16], bbeta[16];
-    double bpa_re[16], bpa_im[16], bpb[16], brmax2[16], bb2[16], br2_true[16];
+    double brho[16], brho_prev[16], bpi[16], balpha[16], bbeta[16];
+    double bpb[16], brmax2[16], bb2[16], br2_true[16];
     double balpha_buf[HISQ_MAX_GRAD_BUFFER][16];
     double bc[16], bnc[16];  // 4m^2 + shift of system j, and its negative
     double btol2[16];        // tol_j^2
@@ -494,7 +493,6 @@ hisq_status batched_run(BatchedJob &J);
 
 struct LibScratch {
     double *dev;       // device doubles
-    size_t ndev;
     double *host;      // pinned host doubles
 };
 hisq_status lib_scratch(LibScratch **out);

@@ -5,10 +5,10 @@
 // the per-block partials of the preceding kernel summed in a fixed order.  No
 // iteration needs the host: the host enqueues units of iterations (optionally as
 // one captured hipGraph replayed per unit), the next one before the running one
-// has ended, and reads a status record that each unit leaves in host memory.  A kernel that decides to leave the
-// loop (reliable update due, convergence candidate, multi-shift phase done,
-// breakdown, iteration cap) lowers ctrl->stop, and every later kernel of the
-// block sees its guard fail and returns at once.  The host then performs the
+// has ended, and reads a status record that each unit leaves in host memory.  A
+// kernel that decides to leave the loop (reliable update due, convergence
+// candidate, multi-shift phase done, breakdown, iteration cap) lowers ctrl->stop,
+// and every later kernel of the block sees its guard fail and returns at once.  The host then performs the
 // reliable update (FP64 Dslash on the FP64 solution) and starts a new block.
 //
 // One CG iteration j of a block (slot jb = j mod N_b of the gradient buffer), four launches:
@@ -36,7 +36,6 @@
 #include <functional>
 #include <string>
 #include <thread>
-#include <vector>
 
 #include "hisq_internal.h"
 
@@ -338,7 +337,6 @@ struct Run {
     }
     double c_ = 0.0;
 
-    // bytes between the gradient slots of one shift's ring
     // the shifted systems' updates of the block's first `count` iterations
     hisq_status enq_shift_replay(int count, Guard gd) {
         SpinorList xl, pl, rl;
